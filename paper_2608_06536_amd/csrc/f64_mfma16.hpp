@@ -88,7 +88,7 @@ struct Tile16 {
     static constexpr int STAGE = A_DOUBLES + B_DOUBLES;
     static constexpr int LDS_DOUBLES = 2 * STAGE;
     static_assert(BM % WM == 0 && BN % WN == 0 && WM % 16 == 0 && WN % 16 == 0, "tile16");
-    static_assert(BK % 4 == 0 && (BM * BK / 4) % NTHR == 0 && (BN * BK / 4) % NTHR == 0, "tile16");
+    static_assert(BK % 4 == 0, "tile16");
 };
 
 template <class TL>
@@ -123,8 +123,22 @@ __device__ __forceinline__ int frag_slot(int i, int k)
 template <int T, int BK, int NTHR, class Op>
 struct BufLoader {
     static constexpr int G = Op::kContig ? 4 : 2;
-    static constexpr int NGRP = T * BK / G, NS = NGRP / NTHR, NSUB = BK / 4;
-    static_assert(NGRP % NTHR == 0, "operand tile and thread count");
+    static constexpr int NGRP = T * BK / G, NS = (NGRP + NTHR - 1) / NTHR, NSUB = BK / 4;
+    // memory and LDS instructions of one stage
+    static constexpr int NLOAD = NS * G / 2, NWRITE = NS * G / 2;
+    // Where the groups are no multiple of the threads, the last step's surplus
+    // threads load a group again (so that every thread has the same number of
+    // loads in flight) and do not write it; whole waves agree.
+    static_assert(NGRP % 64 == 0, "operand tile: whole waves of groups");
+    __device__ __forceinline__ static int group(int tid, int s)
+    {
+        const int g = tid + s * NTHR;
+        return NGRP % NTHR == 0 || g < NGRP ? g : g - NGRP;
+    }
+    __device__ __forceinline__ static bool owns(int tid, int s)
+    {
+        return NGRP % NTHR == 0 || tid + s * NTHR < NGRP;
+    }
     const char *base;      // segment 0
     int nbytes;            // extent of one segment (bit pattern of an unsigned)
     unsigned voff[NS];     // byte offset of the group at inner index 0 of the tile
@@ -150,7 +164,7 @@ struct BufLoader {
 #pragma unroll
         for (int s = 0; s < NS; s++) {
             int li, lk;
-            local(tid + s * NTHR, li, lk);
+            local(group(tid, s), li, lk);
             int i = i0 + li;
             if (Op::kContig)
                 i = i < op.ni ? i : op.ni - 1;       // rows past the end: clamped
@@ -181,15 +195,13 @@ struct BufLoader {
         }
     }
 
-    // Writes the stage into LDS.  With MASK, elements at local inner index
-    // kleft or beyond (possible in a tile's last stage only) are then
-    // overwritten with zero by the thread that wrote them, in a branch taken
-    // only by such a stage, so the other stages carry no selects.
-    template <bool MASK>
-    __device__ __forceinline__ void store(double *lds, int tid, int kleft) const
+    // Writes the stage into LDS.
+    __device__ __forceinline__ void store(double *lds, int tid) const
     {
 #pragma unroll
         for (int s = 0; s < NS; s++) {
+            if (!owns(tid, s))
+                continue;
             int li, lk;
             local(tid + s * NTHR, li, lk);
 #pragma unroll
@@ -198,17 +210,25 @@ struct BufLoader {
                 lds[frag_slot<NSUB>(i, k)] = raw[s][e];
             }
         }
-        if (MASK && kleft < BK) {
+    }
+
+    // Overwrites with zero what this thread wrote at local inner index kleft
+    // or beyond (a tile's last stage only).
+    __device__ __forceinline__ void zero_tail(double *lds, int tid, int kleft) const
+    {
+        if (kleft >= BK)
+            return;
 #pragma unroll
-            for (int s = 0; s < NS; s++) {
-                int li, lk;
-                local(tid + s * NTHR, li, lk);
+        for (int s = 0; s < NS; s++) {
+            if (!owns(tid, s))
+                continue;
+            int li, lk;
+            local(tid + s * NTHR, li, lk);
 #pragma unroll
-                for (int e = 0; e < G; e++) {
-                    const int i = Op::kContig ? li : li + e, k = Op::kContig ? lk + e : lk;
-                    if (k >= kleft)
-                        lds[frag_slot<NSUB>(i, k)] = 0.0;
-                }
+            for (int e = 0; e < G; e++) {
+                const int i = Op::kContig ? li : li + e, k = Op::kContig ? lk + e : lk;
+                if (k >= kleft)
+                    lds[frag_slot<NSUB>(i, k)] = 0.0;
             }
         }
     }
@@ -240,6 +260,7 @@ __device__ __forceinline__ int pk_row16(int a, int nao) { return (int)((i64)a * 
 template <int T, int BK, int NTHR>
 struct PackedLoader16 {
     static constexpr int NGRP = T * BK / 4, NS = NGRP / NTHR, NSUB = BK / 4;
+    static constexpr int NLOAD = 2 * NS, NWRITE = 2 * NS;
     static_assert(NGRP % NTHR == 0, "packed loader");
     const char *base;
     int nbytes, nao, i0, kb;
@@ -326,10 +347,8 @@ struct PackedLoader16 {
         }
     }
 
-    template <bool MASK>
-    __device__ __forceinline__ void store(double *lds, int tid, int) const
+    __device__ __forceinline__ void store(double *lds, int tid) const
     {
-        static_assert(!MASK, "a packed operand is used unmasked");
         if (mode == 1) {
 #pragma unroll
             for (int u = 0; u < 2 * NS; u++) {
@@ -349,6 +368,9 @@ struct PackedLoader16 {
             }
         }
     }
+
+    // a packed operand is used unmasked
+    __device__ __forceinline__ void zero_tail(double *, int, int) const {}
 };
 
 // The loader of each operand type.
@@ -361,88 +383,97 @@ struct LoaderOf<T, BK, NTHR, BufPackedSym> {
     typedef PackedLoader16<T, BK, NTHR> type;
 };
 
+// Workgroup barrier that waits for this wave's LDS accesses only, so that the
+// global loads of later stages stay in flight (__syncthreads() would drain
+// them).  Nothing is scheduled across it.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0), other counters free
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // acc += sum over segments g < nseg of sum over k in [k_begin, k_begin +
 // kdepth) of A_g(m0 + i, k) * B_g(n0 + j, k), where A_g is A with its base
 // moved by g segA elements (B_g likewise).  The stages of all segments form
 // one pipeline.
 //
-// Pipeline: two LDS stages and two register sets of global loads.  While
-// stage kt is multiplied out of LDS, the loads of stage kt + 2 are in flight
-// into one register set and stage kt + 1, loaded one stage earlier, is
-// written from the other set into the second LDS stage; one barrier per
-// stage.  A load therefore has a full stage of products to arrive before
-// its data are written to LDS (measured: 63.0 -> 65.1 TF on the
-// half-transform, against the compiler's own order, which sank the loads
-// below the products).
+// Bound by the FP64 matrix cores (64 cycles per instruction and SIMD), so
+// the schedule hides everything else behind them.  Two LDS stages; the
+// fragments of half a stage (8 inner indices) are read a half ahead of their
+// products.  While the first half of stage kt is multiplied, the second
+// half's fragments are read, stage kt + 1 (loaded a stage ago) is written to
+// the other LDS stage and the loads of stage kt + 2 take its registers; after
+// the stage's one barrier the second half is multiplied while stage kt + 1's
+// first fragments are read.  The scheduling groups place one LDS or memory
+// instruction after each matrix instruction: left to itself the compiler
+// bunches them at the head of the stage, where a wave has no products of its
+// own to cover them.  On products of depth 4000-12000 (512 x 512 outputs, four
+// densities) the 128 x 64 tile ran at 49.5, 58 and 60 TF with one, two and
+// three workgroups per CU before and at 60.5, 62.4 and 62.9 now; random
+// operands hold the clock below what constant ones reach (67 TF).
+//
+// A last stage (of each segment) with at most 8 inner indices skips its
+// second half.
 template <class TL, class OA, class OB, bool MASK>
 struct Gemm16 {
-    static constexpr int BK = TL::BK, NSUB = TL::NSUB;
+    static constexpr int BK = TL::BK, NSUB = TL::NSUB, NH = TL::NSUB / 2;
+    static_assert(NSUB % 2 == 0, "a stage has two halves");
     typedef typename LoaderOf<TL::BM, BK, TL::NTHR, OA>::type LA;
     typedef typename LoaderOf<TL::BN, BK, TL::NTHR, OB>::type LB;
+    // LDS reads of half a stage (pairs of 8-byte reads), LDS writes and loads
+    // of a stage, per wave
+    static constexpr int NREAD = TL::MA + TL::NB;
+    static constexpr int NMOVE = (LA::NLOAD + LB::NLOAD) > (LA::NWRITE + LB::NWRITE)
+                                     ? LA::NLOAD + LB::NLOAD
+                                     : LA::NWRITE + LB::NWRITE;
 
-    struct Seq {             // stage kt -> (segment, inner offset)
-        int nks, kdepth;
-        i64 sega, segb;      // bytes
-        __device__ __forceinline__ void at(int kt, int &g, int &kk) const
-        {
-            g = kt / nks;
-            kk = (kt - g * nks) * BK;
-        }
+    struct Half {
+        double a[NH][TL::MA], b[NH][TL::NB];
     };
-
-    __device__ static __forceinline__ void products(const double *lds, int cur, int fa, int fb,
-                                                    Acc16<TL> &acc)
+    __device__ static __forceinline__ void read(const double *pa, const double *pb, int h, Half &f)
     {
-        const double *pa = lds + cur * TL::STAGE + fa;
-        const double *pb = lds + cur * TL::STAGE + fb;
 #pragma unroll
-        for (int s = 0; s < NSUB; s++) {
-            double a[TL::MA], b[TL::NB];
+        for (int s = 0; s < NH; s++) {
 #pragma unroll
             for (int i = 0; i < TL::MA; i++)
-                a[i] = pa[(i * NSUB + s) * 68];
+                f.a[s][i] = pa[(i * NSUB + h * NH + s) * TL::BLK];
 #pragma unroll
             for (int j = 0; j < TL::NB; j++)
-                b[j] = pb[(j * NSUB + s) * 68];
+                f.b[s][j] = pb[(j * NSUB + h * NH + s) * TL::BLK];
+        }
+    }
+    __device__ static __forceinline__ void multiply(const Half &f, Acc16<TL> &acc)
+    {
+#pragma unroll
+        for (int s = 0; s < NH; s++)
 #pragma unroll
             for (int i = 0; i < TL::MA; i++)
 #pragma unroll
                 for (int j = 0; j < TL::NB; j++)
-                    acc.c[i][j] = mfma16(a[i], b[j], acc.c[i][j]);
+                    acc.c[i][j] = mfma16(f.a[s][i], f.b[s][j], acc.c[i][j]);
+    }
+    // one LDS read per matrix instruction, for half a stage's reads
+    __device__ static __forceinline__ void order_reads()
+    {
+#pragma unroll
+        for (int u = 0; u < NREAD; u++) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);    // LDS read
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    // matrix
         }
     }
-
-    // One stage: loads of stage kt + 2 into (la_n, lb_n); stage kt + 1,
-    // loaded one stage earlier, from (la_s, lb_s) into the LDS buffer the
-    // previous stage read (free since that stage's barrier); products of
-    // stage kt; barrier.
-    __device__ static __forceinline__ void stage(const OA &A, const OB &B, const Seq &q, int kt,
-                                                 int nk, double *lds, int fa, int fb, int tid,
-                                                 LA &la_n, LB &lb_n, const LA &la_s,
-                                                 const LB &lb_s, Acc16<TL> &acc)
+    // one LDS write and one load per matrix instruction
+    __device__ static __forceinline__ void order_moves()
     {
-        {
-            // Issued first and on every stage (past the end: the last stage
-            // again, never written to LDS).  The scheduling barrier keeps the
-            // compiler from sinking them below the products, and the fixed
-            // count per stage lets the wait before the LDS writes below cover
-            // the previous stage's loads only, so a load has a whole stage of
-            // products to arrive.
-            int g, kk;
-            q.at(kt + 2 < nk ? kt + 2 : nk - 1, g, kk);
-            la_n.load(A, g, kk, q.sega, tid);
-            lb_n.load(B, g, kk, q.segb, tid);
-            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < NMOVE; u++) {
+            __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);    // LDS write
+            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);    // memory read
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    // matrix
         }
-        if (kt + 1 < nk) {
-            int g, kk;
-            q.at(kt + 1, g, kk);
-            const int kleft = q.kdepth - kk;
-            la_s.template store<MASK>(lds + ((kt + 1) & 1) * TL::STAGE, tid, kleft);
-            lb_s.template store<MASK>(lds + ((kt + 1) & 1) * TL::STAGE + TL::A_DOUBLES, tid, kleft);
-        }
-        products(lds, kt & 1, fa, fb, acc);
-        __syncthreads();
     }
 
     __device__ static __forceinline__ void run(const OA &A, const OB &B, int m0, int n0,
@@ -452,41 +483,80 @@ struct Gemm16 {
         const int tid = threadIdx.x;
         const int lane = tid & 63, wave = tid >> 6;
         const int wr = wave / TL::WCOLS, wc = wave % TL::WCOLS;
-        Seq q;
-        q.nks = (kdepth + BK - 1) / BK;
-        q.kdepth = kdepth;
-        q.sega = segA * 8;
-        q.segb = segB * 8;
-        const int nk = q.nks * nseg;
+        const int nks = (kdepth + BK - 1) / BK, nk = nks * nseg;
+        const i64 sega = segA * 8, segb = segB * 8;      // bytes
         if (nk <= 0)
             return;
-        LA la0, la1;
-        LB lb0, lb1;
-        la0.init(A, m0, k_begin, tid);
-        lb0.init(B, n0, k_begin, tid);
-        la1 = la0;
-        lb1 = lb0;
-        la0.load(A, 0, 0, q.sega, tid);
-        lb0.load(B, 0, 0, q.segb, tid);
-        if (nk > 1) {
-            int g, kk;
-            q.at(1, g, kk);
-            la1.load(A, g, kk, q.sega, tid);
-            lb1.load(B, g, kk, q.segb, tid);
+        const int last = kdepth - (nks - 1) * BK;        // inner indices of a segment's last stage
+        // the stage being loaded: number, segment, stage within it (stops at
+        // the last one)
+        int ls = 0, lg = 0, lr = 0;
+        auto next = [&]() {
+            if (ls + 1 < nk) {
+                ls++;
+                lr++;
+                if (lr == nks) {
+                    lr = 0;
+                    lg++;
+                }
+            }
+        };
+        LA la;
+        LB lb;
+        la.init(A, m0, k_begin, tid);
+        lb.init(B, n0, k_begin, tid);
+        {
+            // both of the first two stages' loads before the first wait
+            LA la0 = la;
+            LB lb0 = lb;
+            la0.load(A, 0, 0, sega, tid);
+            lb0.load(B, 0, 0, segb, tid);
+            next();
+            la.load(A, lg, lr * BK, sega, tid);
+            lb.load(B, lg, lr * BK, segb, tid);
+            la0.store(lds, tid);
+            lb0.store(lds + TL::A_DOUBLES, tid);
+            if (MASK && nks == 1) {
+                la0.zero_tail(lds, tid, last);
+                lb0.zero_tail(lds + TL::A_DOUBLES, tid, last);
+            }
         }
-        la0.template store<MASK>(lds, tid, kdepth);
-        lb0.template store<MASK>(lds + TL::A_DOUBLES, tid, kdepth);
-        __syncthreads();
-        const int fa = wr * TL::MA * NSUB * 68 + lane;
-        const int fb = TL::A_DOUBLES + wc * TL::NB * NSUB * 68 + lane;
-        // register set of stage s: s & 1 (set 0 holds stages 0, 2, 4, ...)
-        int kt = 0;
-        for (; kt + 1 < nk; kt += 2) {
-            stage(A, B, q, kt, nk, lds, fa, fb, tid, la0, lb0, la1, lb1, acc);
-            stage(A, B, q, kt + 1, nk, lds, fa, fb, tid, la1, lb1, la0, lb0, acc);
+        lds_barrier();
+        const double *pa = lds + wr * TL::MA * NSUB * TL::BLK + lane;
+        const double *pb = lds + TL::A_DOUBLES + wc * TL::NB * NSUB * TL::BLK + lane;
+        Half f0, f1;
+        read(pa, pb, 0, f0);
+        int cur = 0;
+        int r = 0;                                       // stage within its segment
+        for (int kt = 0; kt < nk; kt++) {
+            const int nxt = TL::STAGE - cur;
+            read(pa + cur, pb + cur, 1, f1);
+            la.store(lds + nxt, tid);
+            lb.store(lds + nxt + TL::A_DOUBLES, tid);
+            next();
+            la.load(A, lg, lr * BK, sega, tid);
+            lb.load(B, lg, lr * BK, segb, tid);
+            multiply(f0, acc);
+            order_reads();
+            order_moves();
+            __builtin_amdgcn_sched_barrier(0);
+            const bool end = r == nks - 1;               // a segment's last stage
+            r = end ? 0 : r + 1;
+            if (MASK && r == nks - 1) {                  // of stage kt + 1
+                la.zero_tail(lds + nxt, tid, last);
+                lb.zero_tail(lds + nxt + TL::A_DOUBLES, tid, last);
+            }
+            lds_barrier();
+            if (end && last <= BK / 2) {
+                read(pa + nxt, pb + nxt, 0, f0);
+            } else {
+                read(pa + nxt, pb + nxt, 0, f0);
+                multiply(f1, acc);
+                order_reads();
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            cur = nxt;
         }
-        if (kt < nk)
-            products(lds, kt & 1, fa, fb, acc);
     }
 };
 

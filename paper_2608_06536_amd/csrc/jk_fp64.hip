@@ -100,10 +100,10 @@ __global__ void __launch_bounds__(512, 2) k_half_transform_w8(const double *__re
 }
 
 // The half-transform on the 16 x 16 x 4 engine, over the chunk's stacked
-// slabs: 128 x 128 tiles of four 64 x 64 wave tiles in stages of 8 inner
-// indices (two workgroups per CU), or 128 x 64 tiles of four 64 x 32 wave
-// tiles in stages of 16 (three workgroups per CU).  Dynamic LDS: 35 and 52 KB.
-typedef Tile16<128, 128, 64, 64, 8> TileH16a;
+// slabs: 128 x 128 tiles of four 64 x 64 wave tiles (two workgroups per CU),
+// or 128 x 64 tiles of four 64 x 32 wave tiles (three workgroups per CU), in
+// stages of 16 inner indices.  Dynamic LDS: 70 and 52 KB.
+typedef Tile16<128, 128, 64, 64, 16> TileH16a;
 typedef TileHalf16 TileH16c;
 __global__ void __launch_bounds__(256, 2) k_half_transform16a(const double *__restrict__ B,
                                                               const double *__restrict__ Cc,
