@@ -75,9 +75,10 @@ struct BufIC {
 };
 __host__ __device__ inline bool buf_extent_ok(i64 elements) { return elements * 8 < (1LL << 32); }
 
-template <int BM_, int BN_, int WM_, int WN_, int BK_>
+template <int BM_, int BN_, int WM_, int WN_, int BK_, int NSET_ = 1>
 struct Tile16 {
     static constexpr bool kMfma16 = true;
+    static constexpr int NSET = NSET_;                      // register sets of loads
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = BK_;
     static constexpr int WROWS = BM / WM, WCOLS = BN / WN;
     static constexpr int NWAVE = WROWS * WCOLS;
@@ -90,6 +91,72 @@ struct Tile16 {
     static_assert(BM % WM == 0 && BN % WN == 0 && WM % 16 == 0 && WN % 16 == 0, "tile16");
     static_assert(BK % 4 == 0, "tile16");
 };
+
+// Workgroup tile shapes of four waves.  Products of padded rows and columns
+// cost as much as real ones, and random operands hold the clock at the power
+// limit (2.2-2.33 GHz; the matrix cores are busy 85% of the cycles with any of
+// these), so a product takes the shape that covers its output with the least
+// padding, weighted by the rate the shape sustains on a full output: wider
+// wave tiles read less LDS and memory per product.
+enum Shape16 { kS128x128 = 0, kS128x64, kS96x64, kS80x64, kS64x64, kNumShapes };
+template <int S>
+struct ShapeTile;
+template <>
+struct ShapeTile<kS128x128> {
+    typedef Tile16<128, 128, 64, 64, 16> type;
+};
+template <>
+struct ShapeTile<kS128x64> {
+    typedef Tile16<128, 64, 64, 32, 16> type;
+};
+template <>
+struct ShapeTile<kS96x64> {
+    typedef Tile16<96, 64, 48, 32, 16> type;
+};
+template <>
+struct ShapeTile<kS80x64> {
+    typedef Tile16<80, 64, 80, 16, 16> type;
+};
+template <>
+struct ShapeTile<kS64x64> {
+    typedef Tile16<64, 64, 32, 32, 16, 2> type;
+};
+// Rows and columns of a shape's tile, and the workgroups of it a CU holds
+// (registers and LDS; the kernels' launch bounds say the same).
+__host__ __device__ constexpr int shape_bm(int shape)
+{
+    return shape <= kS128x64 ? 128 : shape == kS96x64 ? 96 : shape == kS80x64 ? 80 : 64;
+}
+__host__ __device__ constexpr int shape_bn(int shape) { return shape == kS128x128 ? 128 : 64; }
+__host__ __device__ constexpr int shape_wgs(int shape)
+{
+    return shape == kS128x128 ? 2 : shape == kS64x64 ? 4 : 3;
+}
+// Sustained TF of a shape (exchange-shaped products of 960 rows, depth 12000,
+// random operands; 96 x 64 on 288 rows of 257).
+inline double shape_rate(int shape)
+{
+    const double rate[kNumShapes] = {69.7, 66.5, 61.0, 59.3, 61.4};
+    return rate[shape];
+}
+// Output area, padding included, over the shape's rate.  E.g. 257 x 257: 384 x
+// 320 / 66.5, 288 x 320 / 61, 320 x 320 / 59.3 or 61.4 -> 96 x 64, 448 us
+// against 555 (128 x 64) and 492 (64 x 64) for six densities of depth 25700;
+// 150 x 150: 80 x 64, 62 us against 84 and 67 (depth 9000).
+inline double shape_cost(int shape, int64_t rows, int64_t cols)
+{
+    const int64_t bm = shape_bm(shape), bn = shape_bn(shape);
+    return (double)((rows + bm - 1) / bm * bm) * (double)((cols + bn - 1) / bn * bn) /
+           shape_rate(shape);
+}
+inline int pick_shape(int64_t rows, int64_t cols, int first = kS128x128)
+{
+    int best = first;
+    for (int s = first + 1; s < kNumShapes; s++)
+        if (shape_cost(s, rows, cols) < shape_cost(best, rows, cols))
+            best = s;
+    return best;
+}
 
 template <class TL>
 struct Acc16 {
@@ -420,7 +487,7 @@ __device__ __forceinline__ void lds_barrier()
 // second half.
 template <class TL, class OA, class OB, bool MASK>
 struct Gemm16 {
-    static constexpr int BK = TL::BK, NSUB = TL::NSUB, NH = TL::NSUB / 2;
+    static constexpr int BK = TL::BK, NSUB = TL::NSUB, NH = TL::NSUB / 2, NSET = TL::NSET;
     static_assert(NSUB % 2 == 0, "a stage has two halves");
     typedef typename LoaderOf<TL::BM, BK, TL::NTHR, OA>::type LA;
     typedef typename LoaderOf<TL::BN, BK, TL::NTHR, OB>::type LB;
@@ -501,19 +568,28 @@ struct Gemm16 {
                 }
             }
         };
-        LA la;
-        LB lb;
-        la.init(A, m0, k_begin, tid);
-        lb.init(B, n0, k_begin, tid);
+        // register sets of loads in flight: stage s is loaded into set
+        // (s - 1) % NSET, NSET stages before it is written to LDS
+        LA la[NSET];
+        LB lb[NSET];
+        la[0].init(A, m0, k_begin, tid);
+        lb[0].init(B, n0, k_begin, tid);
         {
-            // both of the first two stages' loads before the first wait
-            LA la0 = la;
-            LB lb0 = lb;
+            // the first stages' loads all issued before the first wait
+            LA la0 = la[0];
+            LB lb0 = lb[0];
+            if (NSET == 2) {
+                la[NSET - 1] = la[0];
+                lb[NSET - 1] = lb[0];
+            }
             la0.load(A, 0, 0, sega, tid);
             lb0.load(B, 0, 0, segb, tid);
-            next();
-            la.load(A, lg, lr * BK, sega, tid);
-            lb.load(B, lg, lr * BK, segb, tid);
+#pragma unroll
+            for (int u = 0; u < NSET; u++) {
+                next();
+                la[u].load(A, lg, lr * BK, sega, tid);
+                lb[u].load(B, lg, lr * BK, segb, tid);
+            }
             la0.store(lds, tid);
             lb0.store(lds + TL::A_DOUBLES, tid);
             if (MASK && nks == 1) {
@@ -528,23 +604,24 @@ struct Gemm16 {
         read(pa, pb, 0, f0);
         int cur = 0;
         int r = 0;                                       // stage within its segment
-        for (int kt = 0; kt < nk; kt++) {
+        auto stage = [&](LA &las, LB &lbs) {
             const int nxt = TL::STAGE - cur;
             read(pa + cur, pb + cur, 1, f1);
-            la.store(lds + nxt, tid);
-            lb.store(lds + nxt + TL::A_DOUBLES, tid);
+            las.store(lds + nxt, tid);
+            lbs.store(lds + nxt + TL::A_DOUBLES, tid);
+            const bool end = r == nks - 1;               // a segment's last stage
+            r = end ? 0 : r + 1;
+            const bool mask = MASK && r == nks - 1;      // of the stage just written
             next();
-            la.load(A, lg, lr * BK, sega, tid);
-            lb.load(B, lg, lr * BK, segb, tid);
+            las.load(A, lg, lr * BK, sega, tid);
+            lbs.load(B, lg, lr * BK, segb, tid);
             multiply(f0, acc);
             order_reads();
             order_moves();
             __builtin_amdgcn_sched_barrier(0);
-            const bool end = r == nks - 1;               // a segment's last stage
-            r = end ? 0 : r + 1;
-            if (MASK && r == nks - 1) {                  // of stage kt + 1
-                la.zero_tail(lds + nxt, tid, last);
-                lb.zero_tail(lds + nxt + TL::A_DOUBLES, tid, last);
+            if (mask) {
+                las.zero_tail(lds + nxt, tid, last);
+                lbs.zero_tail(lds + nxt + TL::A_DOUBLES, tid, last);
             }
             lds_barrier();
             if (end && last <= BK / 2) {
@@ -556,7 +633,15 @@ struct Gemm16 {
             }
             __builtin_amdgcn_sched_barrier(0);
             cur = nxt;
+        };
+        int kt = 0;
+        for (; kt + NSET <= nk; kt += NSET) {
+#pragma unroll
+            for (int u = 0; u < NSET; u++)
+                stage(la[u], lb[u]);
         }
+        if (NSET == 2 && kt < nk)
+            stage(la[0], lb[0]);
     }
 };
 

@@ -52,6 +52,10 @@ constexpr int kChunkChoicesMb[] = {64, 128, 256, 512, 1024, 2048, 4096};
 // The plan choices of the current build: the recorded ones, or those being
 // timed by jk_autotune on this thread.
 thread_local const jk_tuning *t_forced = nullptr;
+// Most bytes the exchange's partial sums may take: 128 MB, less where
+// jk_build_noalloc's fixed array asks for it.
+constexpr size_t kPartialCap = (size_t)128 << 20;
+thread_local size_t t_partial_cap = kPartialCap;
 jk_tuning plan_tuning(const jk_problem *p) { return t_forced ? *t_forced : jk::tuning_for(p); }
 inline size_t tuned_budget(const jk_problem *p) { return (size_t)plan_tuning(p).chunk_mb << 20; }
 
@@ -148,8 +152,8 @@ FwdPlan plan_forward(const jk_problem *p, size_t budget = kChunkBudget)
     f.o_g = c.take(sizeof(double) * nd * p->naux);
     f.o_x = c.take(sizeof(double) * nd * nao * (size_t)f.ldw);
     f.o_y = c.take(sizeof(double) * nd * nao * (size_t)f.ldw);
-    f.nsplit = jk::exchange_nsplit((int)nao, (int)nd, f.ldw);
-    f.nsplit_sym = jk::exchange_nsplit((int)nao, (int)nd, f.ldw, 1);
+    f.nsplit = jk::exchange_nsplit((int)nao, (int)nd, f.ldw, 0, t_partial_cap);
+    f.nsplit_sym = jk::exchange_nsplit((int)nao, (int)nd, f.ldw, 1, t_partial_cap);
     const int nsmax = f.nsplit > f.nsplit_sym ? f.nsplit : f.nsplit_sym;
     f.o_kp = c.take(nsmax > 1 ? sizeof(double) * (size_t)nsmax * nd * npos : 0);
     f.total = c.off;
@@ -448,10 +452,12 @@ jk_status build_fp64(const jk_problem *p, const double *B, const KSeg *seg, int 
                 first = false;
             }
         }
-        if (ns > 1)
-            JK_TRY(jk::launch_sum_splits(Kp, Kout, (i64)nd * npos, ns, s));
-        if (sym)
+        if (sym && ns > 1)
+            JK_TRY(jk::launch_sum_splits_sym(Kp, Kout, nao, nd, ns, s));
+        else if (sym)
             JK_TRY(jk::launch_mirror_upper(Kout, nao, nd, s));
+        else if (ns > 1)
+            JK_TRY(jk::launch_sum_splits(Kp, Kout, (i64)nd * npos, ns, s));
     }
     if (fused && (o.cj != 0.0 || !want_k)) {
         // F (+)= cj J (J is symmetric, so the order against the mirror does
@@ -795,10 +801,12 @@ jk_status build_mixed(const jk_problem *p, const double *B, const KSeg *seg, int
         }
     }
 #undef JK_STEP
-    if (nsplit > 1)
-        JK_TRY(jk::launch_sum_splits(Kp, K, (i64)nd * npos, nsplit, s));
-    if (sym)
+    if (sym && nsplit > 1)
+        JK_TRY(jk::launch_sum_splits_sym(Kp, K, nao, nd, nsplit, s));
+    else if (sym)
         JK_TRY(jk::launch_mirror_upper(K, nao, nd, s));
+    else if (nsplit > 1)
+        JK_TRY(jk::launch_sum_splits(Kp, K, (i64)nd * npos, nsplit, s));
     return fock_j();
 }
 
@@ -926,6 +934,11 @@ bool batched_mixed_ok(int32_t nprob, const jk_problem *p)
     return true;
 }
 
+// The exchange's tile shape in a batch: one kernel runs every member's, so the
+// 128 x 128 tile, whose registers would halve the others' residents, is left
+// out.
+int batched_ex_shape(int nao) { return jk::pick_shape(nao, nao, jk::kS128x64); }
+
 // Per-member cost of one tile of a phase (larger first in the tables).
 double tile_cost(int phase, const BPlan &b, const jk_problem &p)
 {
@@ -936,8 +949,11 @@ double tile_cost(int phase, const BPlan &b, const jk_problem &p)
     case jk::kPhaseHalf:
     case jk::kPhaseHalf64:
     case jk::kPhaseHalf16:
+    case jk::kPhaseHalf16W:
+    case jk::kPhaseHalf16S:
     case jk::kPhaseMHalf: return (double)p.nao;
     case jk::kPhaseExchange:
+        return (double)b.f.qc * p.rank / b.nsplit * jk::shape_bm(batched_ex_shape((int)p.nao));
     case jk::kPhaseMExchange: return (double)b.f.qc * p.rank / b.nsplit;
     default: return (double)p.nao;
     }
@@ -1067,13 +1083,24 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
             add(jk::kPhaseHalf64, c,
                 [&](int g) { return jk::ht64_tiles((int)p[g].nao, (int)p[g].ndens, (int)p[g].rank, nq_of(g)); },
                 [&](int g) { return in_step(g) && plans[g].tile == 1; });
-            add(jk::kPhaseHalf16, c,
-                [&](int g) {
-                    const int R = (int)(p[g].ndens * p[g].rank);
-                    return jk::ht_flat_tiles<jk::TileHalf16>((int)p[g].nao, plans[g].sym ? R : 2 * R,
-                                                           nq_of(g));
-                },
-                [&](int g) { return in_step(g) && plans[g].tile == 4 && !packed; });
+            // the 16 x 16 x 4 engine: one launch per shape of the members' chunks
+            auto ncol_of = [&](int g) {
+                const int R = (int)(p[g].ndens * p[g].rank);
+                return plans[g].sym ? R : 2 * R;
+            };
+            for (int shape : {jk::kS128x128, jk::kS128x64, jk::kS64x64})
+                add(shape == jk::kS128x128  ? jk::kPhaseHalf16W
+                    : shape == jk::kS128x64 ? jk::kPhaseHalf16
+                                            : jk::kPhaseHalf16S,
+                    c,
+                    [&](int g) {
+                        return (int)(((i64)nq_of(g) * p[g].nao + jk::shape_bm(shape) - 1) / jk::shape_bm(shape)) *
+                               ((ncol_of(g) + jk::shape_bn(shape) - 1) / jk::shape_bn(shape));
+                    },
+                    [&](int g) {
+                        return in_step(g) && plans[g].tile == 4 && !packed &&
+                               jk::ht_shape((i64)nq_of(g) * p[g].nao, ncol_of(g)) == shape;
+                    });
             add(jk::kPhaseHalf16Packed, c,
                 [&](int g) {
                     const int R = (int)(p[g].ndens * p[g].rank);
@@ -1083,9 +1110,9 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
                 [&](int g) { return in_step(g) && packed; });
             add(jk::kPhaseExchange, c,
                 [&](int g) {
-                    return plans[g].sym
-                               ? plans[g].nsplit * (int)p[g].ndens * jk::ex_tri_tiles((int)p[g].nao)
-                               : jk::ex_tiles((int)p[g].nao, (int)p[g].ndens, plans[g].nsplit);
+                    const int sh = batched_ex_shape((int)p[g].nao);
+                    return plans[g].nsplit * (int)p[g].ndens *
+                           jk::ex_tiles((int)p[g].nao, jk::shape_bm(sh), jk::shape_bn(sh), plans[g].sym);
                 },
                 in_step);
         }
@@ -1125,7 +1152,7 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
     {
         // the non-symmetric schedule's launch count, plus the mirror launch
         // (J: four phases, six with packed B)
-        const int per_step = mixed ? 5 : 4;
+        const int per_step = mixed ? 5 : 6;
         nlaunch_bound = 6 + 2 + (size_t)maxsteps * per_step + 2;
     }
     c.take(sizeof(int) * std::max(S.tabs.size(), nlaunch_bound * (2 * (size_t)G + 3)));
@@ -1146,6 +1173,7 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
         m.qc = plans[g].f.qc;
         m.ldw = plans[g].f.ldw;
         m.nsplit = plans[g].nsplit;
+        m.exs = batched_ex_shape(m.nao);
         m.npb = plans[g].f.npb;
         m.plen = plans[g].f.plen;
         m.sym = plans[g].sym;
@@ -1532,8 +1560,14 @@ hipError_t scratch_address(char **out)
     return hipSuccess;
 }
 
+// Sets the exchange's partial cap of this thread for one call.
+struct PartialCap {
+    explicit PartialCap(size_t cap) { t_partial_cap = cap; }
+    ~PartialCap() { t_partial_cap = kPartialCap; }
+};
+
 // Largest chunk budget (MiB, a power of two up to 256) whose FP64 plan fits
-// the scratch array; 0 if none does.
+// the scratch array under the current partial cap; 0 if none does.
 int noalloc_chunk_mb(const jk_problem *p)
 {
     for (int mb = 256; mb >= 1; mb /= 2)
@@ -1556,7 +1590,13 @@ jk_status jk_build_noalloc_impl(const jk_problem *p, const double *B, const doub
         return JK_EINVAL;
     if (p->precision != JK_FP64)
         return JK_EUNSUPPORTED;
-    const int mb = noalloc_chunk_mb(p);
+    // 32 MB of exchange partials, or none where they would not fit
+    PartialCap cap((size_t)32 << 20);
+    int mb = noalloc_chunk_mb(p);
+    if (mb == 0) {
+        t_partial_cap = 0;
+        mb = noalloc_chunk_mb(p);
+    }
     if (mb == 0)
         return JK_EWORKSPACE;
     char *ws = nullptr;

@@ -133,22 +133,23 @@ __global__ void __launch_bounds__(256, 4) k_b_half_transform64(const BMember *__
 
 // Stacked-slab half-transform on the 16 x 16 x 4 engine (the plan's tile 3
 // or 4; the schedule keeps members whose chunk of slabs spans 4 GiB or more
-// on the 4x4x4 tile).
+// on the 4x4x4 tile), one launch per shape.
 typedef TileHalf16 TileB16;
-__global__ void __launch_bounds__(256, 3) k_b_half_transform16(const BMember *__restrict__ M,
-                                                               const int *__restrict__ tab, int c)
+template <int SHAPE>
+__global__ void __launch_bounds__(256, shape_wgs(SHAPE))
+    k_b_half_transform16(const BMember *__restrict__ M, const int *__restrict__ tab, int c)
 {
     extern __shared__ double lds[];
     int loc;
     const BMember &m = M[find_member(tab, xcd_local(blockIdx.x, gridDim.x), loc)];
     int q0, nq;
     chunk_of(m, c, q0, nq);
-    ht_tile_flat<TileB16>(m.B, m.Cc, m.Xw, m.Yw, m.nao, m.nd, m.r, q0, nq, m.ldw, loc, lds,
-                          m.sym ? m.nd * m.r : -1);
+    ht_tile_flat<typename ShapeTile<SHAPE>::type>(m.B, m.Cc, m.Xw, m.Yw, m.nao, m.nd, m.r, q0, nq,
+                                                  m.ldw, loc, lds, m.sym ? m.nd * m.r : -1);
 }
 
-// Packed slabs on the 16 x 16 x 4 engine: 128 x 64 tiles per slab.
-__global__ void __launch_bounds__(256, 3) k_b_half_transform16_packed(const BMember *__restrict__ M,
+// Packed slabs on the 16 x 16 x 4 engine: 64 x 64 tiles per slab.
+__global__ void __launch_bounds__(256, 4) k_b_half_transform16_packed(const BMember *__restrict__ M,
                                                                       const int *__restrict__ tab,
                                                                       int c)
 {
@@ -174,8 +175,23 @@ __global__ void __launch_bounds__(256, 3) k_b_exchange(const BMember *__restrict
     const int nj = nq * m.r;
     int jlen = cdiv_i(nj, m.nsplit);
     jlen = ((jlen + 15) / 16) * 16;
-    ex_tile<TileB16>(m.Xw, m.sym ? m.Xw : m.Yw, m.nsplit > 1 ? m.Kp : m.K, m.nao, m.nd, nj, m.ldw,
-                     jlen, c > 0, loc, lds, m.sym);
+    const double *Y = m.sym ? m.Xw : m.Yw;
+    double *K = m.nsplit > 1 ? m.Kp : m.K;
+    // the member's tile shape; the workgroups of one member are consecutive,
+    // so a CU's residents mostly share one
+    switch (m.exs) {
+    case kS128x64:
+        ex_tile<ShapeTile<kS128x64>::type>(m.Xw, Y, K, m.nao, m.nd, nj, m.ldw, jlen, c > 0, loc, lds, m.sym);
+        break;
+    case kS96x64:
+        ex_tile<ShapeTile<kS96x64>::type>(m.Xw, Y, K, m.nao, m.nd, nj, m.ldw, jlen, c > 0, loc, lds, m.sym);
+        break;
+    case kS80x64:
+        ex_tile<ShapeTile<kS80x64>::type>(m.Xw, Y, K, m.nao, m.nd, nj, m.ldw, jlen, c > 0, loc, lds, m.sym);
+        break;
+    default:
+        ex_tile<ShapeTile<kS64x64>::type>(m.Xw, Y, K, m.nao, m.nd, nj, m.ldw, jlen, c > 0, loc, lds, m.sym);
+    }
 }
 
 __global__ void __launch_bounds__(256) k_b_mirror(const BMember *__restrict__ M,
@@ -198,14 +214,22 @@ __global__ void __launch_bounds__(256) k_b_sum_splits(const BMember *__restrict_
 
 // ------------------------------------------------------------------ launch
 static constexpr int kLds16 = (int)sizeof(double) * TileB16::LDS_DOUBLES;
+template <int SHAPE>
+static constexpr int shape_lds() { return (int)sizeof(double) * ShapeTile<SHAPE>::type::LDS_DOUBLES; }
+// the exchange kernel holds every shape: the largest one's LDS
+static constexpr int kLdsEx = shape_lds<kS128x64>();
 
 hipError_t prepare_batched_kernels()
 {
-    hipError_t e = set_dynamic_lds((const void *)k_b_half_transform16, kLds16);
+    hipError_t e = set_dynamic_lds((const void *)k_b_half_transform16<kS128x128>, shape_lds<kS128x128>());
+    if (e == hipSuccess)
+        e = set_dynamic_lds((const void *)k_b_half_transform16<kS128x64>, shape_lds<kS128x64>());
+    if (e == hipSuccess)
+        e = set_dynamic_lds((const void *)k_b_half_transform16<kS64x64>, shape_lds<kS64x64>());
     if (e == hipSuccess)
         e = set_dynamic_lds((const void *)k_b_half_transform16_packed, kLds16);
     if (e == hipSuccess)
-        e = set_dynamic_lds((const void *)k_b_exchange, kLds16);
+        e = set_dynamic_lds((const void *)k_b_exchange, kLdsEx);
     return e;
 }
 
@@ -260,7 +284,20 @@ hipError_t launch_batched_phase(int phase, const BMember *M, const int *tab, int
     }
     case kPhaseHalf16: {
         ProfScope ps_("b_half_transform", s);
-        hipLaunchKernelGGL(k_b_half_transform16, g, dim3(TileB16::NTHR), kLds16, s, M, tab, step);
+        hipLaunchKernelGGL(k_b_half_transform16<kS128x64>, g, dim3(256), shape_lds<kS128x64>(), s, M, tab,
+                           step);
+        break;
+    }
+    case kPhaseHalf16W: {
+        ProfScope ps_("b_half_transform", s);
+        hipLaunchKernelGGL(k_b_half_transform16<kS128x128>, g, dim3(256), shape_lds<kS128x128>(), s, M,
+                           tab, step);
+        break;
+    }
+    case kPhaseHalf16S: {
+        ProfScope ps_("b_half_transform", s);
+        hipLaunchKernelGGL(k_b_half_transform16<kS64x64>, g, dim3(256), shape_lds<kS64x64>(), s, M, tab,
+                           step);
         break;
     }
     case kPhaseHalf16Packed: {
@@ -286,7 +323,7 @@ hipError_t launch_batched_phase(int phase, const BMember *M, const int *tab, int
     }
     case kPhaseExchange: {
         ProfScope ps_("b_exchange", s);
-        hipLaunchKernelGGL(k_b_exchange, g, dim3(TileB16::NTHR), kLds16, s, M, tab, step);
+        hipLaunchKernelGGL(k_b_exchange, g, dim3(256), kLdsEx, s, M, tab, step);
         break;
     }
     case kPhaseSum: {

@@ -19,6 +19,7 @@ struct BMember {
     long long goff;
     int nao, naux, nd, r;
     int qc, ldw, nsplit, npb, plen;
+    int exs;            // FP64: the exchange's tile shape (Shape16)
     int sym;            // C_L and C_R are one buffer: X only, K on the upper triangle
     // JK_MIXED members: digit planes (single-buffered), their row exponents
     // and strides (slice_core.hpp layout), the FP64 half-transform chunk XY
@@ -64,14 +65,15 @@ __device__ __forceinline__ int find_member(const int *__restrict__ tab, int t, i
 // kXcdRun (the hardware deals workgroups round-robin over the 8 XCDs); the
 // indices of a last, partial block keep their place.
 constexpr int kXcdRun = 16;
+template <int RUN = kXcdRun>
 __device__ __forceinline__ int xcd_local(int hw, int n)
 {
-    const int blk = 8 * kXcdRun;
+    constexpr int blk = 8 * RUN;
     const int b0 = hw - hw % blk;
     if (b0 + blk > n)
         return hw;
     const int r = hw - b0;
-    return b0 + (r & 7) * kXcdRun + (r >> 3);
+    return b0 + (r & 7) * RUN + (r >> 3);
 }
 
 // Chunk of member m at step c: first slab and slab count.
@@ -91,7 +93,9 @@ enum {
     kPhaseExchange = 6,
     kPhaseSum = 7,
     kPhaseHalf64 = 8,    // the half-transform with 64 x 64 tiles (members whose plan chose them)
-    kPhaseHalf16 = 9,    // the half-transform on the 16 x 16 x 4 engine over stacked slabs
+    kPhaseHalf16 = 9,    // the half-transform on the 16 x 16 x 4 engine over stacked slabs, 128 x 64 tiles
+    kPhaseHalf16W = 15,  // the same with 128 x 128 tiles (members whose columns fill them)
+    kPhaseHalf16S = 16,  // the same with 64 x 64 tiles (members of few rows)
     kPhaseMirror = 10,   // lower triangle of K from the upper (symmetric members)
     kPhaseSymPack = 11,  // packed B: S = D + D^T on the packed positions
     kPhaseUnpackJ = 12,  // packed B: J in full from its packed form

@@ -3,6 +3,7 @@
 #include "jk_kernels.hpp"
 #include "jk_tiles.hpp"
 
+#include <cmath>
 #include <mutex>
 #include <set>
 #include <utility>
@@ -100,39 +101,35 @@ __global__ void __launch_bounds__(512, 2) k_half_transform_w8(const double *__re
 }
 
 // The half-transform on the 16 x 16 x 4 engine, over the chunk's stacked
-// slabs: 128 x 128 tiles of four 64 x 64 wave tiles (two workgroups per CU),
-// or 128 x 64 tiles of four 64 x 32 wave tiles (three workgroups per CU), in
-// stages of 16 inner indices.  Dynamic LDS: 70 and 52 KB.
-typedef Tile16<128, 128, 64, 64, 16> TileH16a;
-typedef TileHalf16 TileH16c;
-__global__ void __launch_bounds__(256, 2) k_half_transform16a(const double *__restrict__ B,
-                                                              const double *__restrict__ Cc,
-                                                              double *__restrict__ Xw,
-                                                              double *__restrict__ Yw, int nao,
-                                                              int nd, int r, int q0, int nq,
-                                                              int ldw, int ncol)
+// slabs.  The 128 x 128 tile has a kernel of its own name (plan tile 3 asks
+// for it alone; tile 4 takes ht_shape's choice).
+template <int SHAPE>
+__global__ void __launch_bounds__(256, shape_wgs(SHAPE))
+    k_half_transform16(const double *__restrict__ B, const double *__restrict__ Cc,
+                       double *__restrict__ Xw, double *__restrict__ Yw, int nao, int nd, int r,
+                       int q0, int nq, int ldw, int ncol)
 {
+    typedef typename ShapeTile<SHAPE>::type TL;
     extern __shared__ double lds_dyn[];
-    const int n = ht_flat_tiles<TileH16a>(nao, ncol, nq);
-    ht_tile_flat<TileH16a>(B, Cc, Xw, Yw, nao, nd, r, q0, nq, ldw, xcd_swizzle(blockIdx.x, n),
-                           lds_dyn, ncol);
+    const int n = ht_flat_tiles<TL>(nao, ncol, nq);
+    ht_tile_flat<TL>(B, Cc, Xw, Yw, nao, nd, r, q0, nq, ldw, xcd_swizzle(blockIdx.x, n), lds_dyn,
+                     ncol);
 }
-__global__ void __launch_bounds__(256, 3) k_half_transform16(const double *__restrict__ B,
-                                                             const double *__restrict__ Cc,
-                                                             double *__restrict__ Xw,
-                                                             double *__restrict__ Yw, int nao,
-                                                             int nd, int r, int q0, int nq, int ldw,
-                                                             int ncol)
+__global__ void __launch_bounds__(256, shape_wgs(kS128x128))
+    k_half_transform16a(const double *__restrict__ B, const double *__restrict__ Cc,
+                        double *__restrict__ Xw, double *__restrict__ Yw, int nao, int nd, int r,
+                        int q0, int nq, int ldw, int ncol)
 {
+    typedef ShapeTile<kS128x128>::type TL;
     extern __shared__ double lds_dyn[];
-    const int n = ht_flat_tiles<TileH16c>(nao, ncol, nq);
-    ht_tile_flat<TileH16c>(B, Cc, Xw, Yw, nao, nd, r, q0, nq, ldw, xcd_swizzle(blockIdx.x, n),
-                           lds_dyn, ncol);
+    const int n = ht_flat_tiles<TL>(nao, ncol, nq);
+    ht_tile_flat<TL>(B, Cc, Xw, Yw, nao, nd, r, q0, nq, ldw, xcd_swizzle(blockIdx.x, n), lds_dyn,
+                     ncol);
 }
 
 // Packed slabs on the 16 x 16 x 4 engine (plan tiles 3 and 4): 128 x 64 tiles
 // per slab, three workgroups per CU.
-__global__ void __launch_bounds__(256, 3) k_half_transform16_packed(const double *__restrict__ B,
+__global__ void __launch_bounds__(256, 4) k_half_transform16_packed(const double *__restrict__ B,
                                                                     const double *__restrict__ Cc,
                                                                     double *__restrict__ Xw,
                                                                     double *__restrict__ Yw,
@@ -184,20 +181,19 @@ __global__ void __launch_bounds__(256) k_unpack_sym(const double *__restrict__ P
     }
 }
 
-// The exchange product on the 16 x 16 x 4 engine: the same 128 x 64 tiles,
-// four 64 x 32 wave tiles, three workgroups per CU (52 KB of dynamic LDS).
-typedef TileH16c TileEx16;
-template <bool MASK>
-__global__ void __launch_bounds__(256, 3) k_exchange16(const double *__restrict__ Xw,
-                                                       const double *__restrict__ Yw,
-                                                       double *__restrict__ Kp, int nao, int nd,
-                                                       int nj, int ldw, int nsplit, int jlen,
-                                                       int accumulate, int sym, double scale)
+// The exchange product on the 16 x 16 x 4 engine, tile shape by pick_shape:
+// two to four workgroups per CU, 35 to 70 KB of dynamic LDS.
+template <int SHAPE, bool MASK>
+__global__ void __launch_bounds__(256, shape_wgs(SHAPE))
+    k_exchange16(const double *__restrict__ Xw, const double *__restrict__ Yw,
+                 double *__restrict__ Kp, int nao, int nd, int nj, int ldw, int nsplit, int jlen,
+                 int accumulate, int sym, double scale)
 {
+    typedef typename ShapeTile<SHAPE>::type TL;
     extern __shared__ double lds_dyn[];
-    const int n = nsplit * nd * (sym ? ex_tri_tiles(nao) : cdiv_i(nao, kExM) * cdiv_i(nao, kExN));
-    ex_tile<TileEx16, MASK>(Xw, Yw, Kp, nao, nd, nj, ldw, jlen, accumulate,
-                            xcd_swizzle(blockIdx.x, n), lds_dyn, sym, scale);
+    const int n = nsplit * nd * ex_tiles(nao, TL::BM, TL::BN, sym);
+    ex_tile<TL, MASK>(Xw, Yw, Kp, nao, nd, nj, ldw, jlen, accumulate, xcd_swizzle(blockIdx.x, n),
+                      lds_dyn, sym, scale);
 }
 
 __global__ void __launch_bounds__(512, 4) k_exchange(const double *__restrict__ Xw,
@@ -207,7 +203,7 @@ __global__ void __launch_bounds__(512, 4) k_exchange(const double *__restrict__ 
                                                      int sym, double scale)
 {
     __shared__ double lds[TileExch::LDS_DOUBLES];
-    const int n = nsplit * nd * (sym ? ex_tri_tiles(nao) : cdiv_i(nao, kExM) * cdiv_i(nao, kExN));
+    const int n = nsplit * nd * ex_tiles(nao, kExM, kExN, sym);
     ex_tile(Xw, Yw, Kp, nao, nd, nj, ldw, jlen, accumulate, xcd_swizzle(blockIdx.x, n), lds, sym,
             scale);
 }
@@ -224,6 +220,18 @@ __global__ void __launch_bounds__(256) k_sum_splits(const double *__restrict__ p
                                                     double *__restrict__ out, i64 n, int nsplit)
 {
     sum_tile(part, out, n, nsplit, blockIdx.x);
+}
+
+__global__ void __launch_bounds__(256) k_sum_splits_sym(const double *__restrict__ part,
+                                                        double *__restrict__ K, int nao, int nd,
+                                                        int nsplit)
+{
+    const i64 npos = (i64)nao * nao;
+    // densities k = blockIdx.y, + gridDim.y, ... (grid y is capped at 65535)
+    for (int k = blockIdx.y; k < nd; k += gridDim.y) {
+        sum_sym_tile(part + k * npos, K + k * npos, nao, nd * npos, nsplit, blockIdx.x);
+        __syncthreads();
+    }
 }
 
 // ------------------------------------------------------------------ launchers
@@ -378,6 +386,25 @@ hipError_t set_dynamic_lds(const void *fn, int bytes)
     return e;
 }
 
+namespace {
+typedef void (*HtKernel)(const double *, const double *, double *, double *, int, int, int, int, int,
+                         int, int);
+template <class TL>
+hipError_t launch_ht16(const void *fn, HtKernel k, const double *B, const double *Cc, double *Xw,
+                       double *Yw, int nao, int nd, int r, int q0, int nq, int ldw, int ncol,
+                       hipStream_t s, const char *prof)
+{
+    const int lds = (int)sizeof(double) * TL::LDS_DOUBLES;
+    hipError_t e = set_dynamic_lds(fn, lds);
+    if (e != hipSuccess)
+        return e;
+    ProfScope ps_(prof, s);
+    hipLaunchKernelGGL(k, dim3(ht_flat_tiles<TL>(nao, ncol, nq)), dim3(TL::NTHR), lds, s, B, Cc, Xw, Yw,
+                       nao, nd, r, q0, nq, ldw, ncol);
+    return hipSuccess;
+}
+} // namespace
+
 hipError_t launch_half_transform(const double *B, const double *Cc, double *Xw, double *Yw,
                                  int nao, int nd, int r, int q0, int nq, int ldw, hipStream_t s,
                                  int ncol, int packed, int tile, const char *prof)
@@ -402,18 +429,27 @@ hipError_t launch_half_transform(const double *B, const double *Cc, double *Xw, 
         hipLaunchKernelGGL(k_half_transform_packed, dim3(ht_tiles_cols(nao, ncol, nq)), dim3(256), 0,
                            s, B, Cc, Xw, Yw, nao, nd, r, q0, nq, ldw, ncol);
     } else if (tile == 3 || tile == 4) {
-        const void *fn = tile == 3 ? (const void *)k_half_transform16a : (const void *)k_half_transform16;
-        const int lds = (int)sizeof(double) * (tile == 3 ? TileH16a::LDS_DOUBLES : TileH16c::LDS_DOUBLES);
-        hipError_t e = set_dynamic_lds(fn, lds);
+        const int shape = tile == 3 ? kS128x128 : ht_shape((i64)nq * nao, ncol);
+        hipError_t e = hipErrorInvalidValue;
+        switch (shape) {
+        case kS128x128:
+            e = launch_ht16<ShapeTile<kS128x128>::type>((const void *)k_half_transform16a,
+                                                        k_half_transform16a, B, Cc, Xw, Yw, nao, nd, r,
+                                                        q0, nq, ldw, ncol, s, prof);
+            break;
+        case kS128x64:
+            e = launch_ht16<ShapeTile<kS128x64>::type>((const void *)k_half_transform16<kS128x64>,
+                                                       k_half_transform16<kS128x64>, B, Cc, Xw, Yw, nao,
+                                                       nd, r, q0, nq, ldw, ncol, s, prof);
+            break;
+        case kS64x64:
+            e = launch_ht16<ShapeTile<kS64x64>::type>((const void *)k_half_transform16<kS64x64>,
+                                                      k_half_transform16<kS64x64>, B, Cc, Xw, Yw, nao,
+                                                      nd, r, q0, nq, ldw, ncol, s, prof);
+            break;
+        }
         if (e != hipSuccess)
             return e;
-        ProfScope ps_(prof, s);
-        if (tile == 3)
-            hipLaunchKernelGGL(k_half_transform16a, dim3(ht_flat_tiles<TileH16a>(nao, ncol, nq)),
-                               dim3(256), lds, s, B, Cc, Xw, Yw, nao, nd, r, q0, nq, ldw, ncol);
-        else
-            hipLaunchKernelGGL(k_half_transform16, dim3(ht_flat_tiles<TileH16c>(nao, ncol, nq)),
-                               dim3(256), lds, s, B, Cc, Xw, Yw, nao, nd, r, q0, nq, ldw, ncol);
     } else if (tile == 2) {
         ProfScope ps_(prof, s);
         hipLaunchKernelGGL(k_half_transform_w8, dim3(ht_tiles_cols(nao, ncol, nq)), dim3(512), 0, s, B,
@@ -461,43 +497,120 @@ hipError_t launch_mirror_upper(double *K, int nao, int nd, hipStream_t s)
     return hipGetLastError();
 }
 
-int exchange_nsplit(int nao, int nd, int nj, int sym)
+int exchange_shape(int nao) { return pick_shape(nao, nao); }
+
+// Splits of the exchange's inner range: the count with the least estimated
+// time.  A CU runs ceil(workgroups / CUs) workgroups one after the other at
+// the rate of the matrix cores; with one or two of them resident the stage
+// barriers cost 14% and 4% (60.5 and 62.4 against 62.9 TF and 70 sustained);
+// every round of residents pays about 3 us of first loads and output; and the
+// partial sums are written and read back (nao^2 per density and split) at
+// about 4 TB/s.  Each split keeps at least 32 inner indices, and the partials
+// stay within kp_cap bytes.  Before, at most 16 splits of at least 256 indices
+// left a single density of nao 236 and rank 48 (depth 45312, symmetric: 6
+// tiles) on 96 workgroups: 220 us; 42 splits run it in 75.
+int exchange_nsplit(int nao, int nd, int nj, int sym, size_t kp_cap)
 {
-    // Full rounds of workgroups; each split keeps >= 256 inner indices.
-    const int tiles = nd * (sym ? ex_tri_tiles(nao) : cdiv(nao, kExM) * cdiv(nao, kExN));
-    int maxs = nj / 256 > 1 ? nj / 256 : 1;
-    if (maxs > 16)
-        maxs = 16;
-    // k_exchange16 holds three workgroups per CU
-    return pick_split_slots(tiles, maxs, device_slots() / 2 * 3);
+    const int shape = exchange_shape(nao);
+    const double tiles = (double)nd * ex_tiles(nao, shape_bm(shape), shape_bn(shape), sym);
+    const double kbytes = 8.0 * nd * nao * (double)nao;
+    const int ncu = device_slots() / 2, occ = shape_wgs(shape);
+    int smax = nj / 32;
+    if (smax > 512)
+        smax = 512;
+    if (smax * kbytes > (double)kp_cap)
+        smax = (int)(kp_cap / kbytes);
+    auto cost = [&](int s) {
+        const double n = ceil(tiles * s / ncu);                   // workgroups of a CU
+        const double depth = 16.0 * cdiv(cdiv(nj, s), 16);
+        const double per = 2.0 * shape_bm(shape) * shape_bn(shape) * depth / (77e12 / 256);
+        const double eff = n >= 3 ? 0.9 : n == 2 ? 0.86 : 0.77;
+        double t = n * per / eff + 3e-6 * ceil(n / occ);
+        if (s > 1)
+            t += 3e-6 + 2.0 * s * kbytes / 4e12;
+        return t;
+    };
+    // candidates: one split, and the most splits that give a CU n workgroups
+    int best = 1;
+    double tbest = cost(1);
+    for (int n = 1; n <= 4 * occ; n++) {
+        const double sn = floor(n * ncu / tiles);
+        const int s = sn < smax ? (int)sn : smax;
+        if (s <= 1)
+            continue;
+        const double t = cost(s);
+        if (t < tbest) {
+            best = s;
+            tbest = t;
+        }
+        if (s == smax)
+            break;
+    }
+    return best;
 }
+
+namespace {
+struct ExArgs {
+    const double *Xw, *Yw;
+    double *Kp;
+    int nao, nd, nj, ldw, nsplit, jlen, accumulate, sym;
+    double scale;
+};
+template <int SHAPE, bool MASK>
+hipError_t launch_exchange16(const ExArgs &a, hipStream_t s)
+{
+    typedef typename ShapeTile<SHAPE>::type TL;
+    const int lds = (int)sizeof(double) * TL::LDS_DOUBLES;
+    hipError_t e = set_dynamic_lds((const void *)k_exchange16<SHAPE, MASK>, lds);
+    if (e != hipSuccess)
+        return e;
+    ProfScope ps_("exchange", s);
+    hipLaunchKernelGGL((k_exchange16<SHAPE, MASK>), dim3(a.nsplit * a.nd * ex_tiles(a.nao, TL::BM, TL::BN, a.sym)),
+                       dim3(TL::NTHR), lds, s, a.Xw, a.Yw, a.Kp, a.nao, a.nd, a.nj, a.ldw, a.nsplit,
+                       a.jlen, a.accumulate, a.sym, a.scale);
+    return hipSuccess;
+}
+template <int SHAPE>
+hipError_t launch_exchange16_m(const ExArgs &a, hipStream_t s)
+{
+    // splits end on 16-deep stage boundaries (jlen is a multiple of 16), so
+    // only a depth nj off that grid leaves a stage to mask
+    return a.nj % 16 != 0 ? launch_exchange16<SHAPE, true>(a, s) : launch_exchange16<SHAPE, false>(a, s);
+}
+} // namespace
 
 hipError_t launch_exchange(const double *Xw, const double *Yw, double *Kp, int nao, int nd, int nj,
                            int ldw, int nsplit, int accumulate, hipStream_t s, int sym, double scale)
 {
     int jlen = cdiv(nj, nsplit);
     jlen = ((jlen + 15) / 16) * 16;
-    const int per = sym ? ex_tri_tiles(nao) : cdiv(nao, kExM) * cdiv(nao, kExN);
     if (buf_extent_ok((i64)nao * ldw)) {
-        // splits end on 16-deep stage boundaries (jlen is a multiple of 16), so
-        // only a depth nj off that grid leaves a stage to mask
-        const bool mask = nj % 16 != 0;
-        const int lds = (int)sizeof(double) * TileEx16::LDS_DOUBLES;
-        hipError_t e = set_dynamic_lds(mask ? (const void *)k_exchange16<true>
-                                            : (const void *)k_exchange16<false>, lds);
+        const ExArgs a{Xw, Yw, Kp, nao, nd, nj, ldw, nsplit, jlen, accumulate, sym, scale};
+        hipError_t e = hipErrorInvalidValue;
+        switch (exchange_shape(nao)) {
+        case kS128x128: e = launch_exchange16_m<kS128x128>(a, s); break;
+        case kS128x64: e = launch_exchange16_m<kS128x64>(a, s); break;
+        case kS96x64: e = launch_exchange16_m<kS96x64>(a, s); break;
+        case kS80x64: e = launch_exchange16_m<kS80x64>(a, s); break;
+        case kS64x64: e = launch_exchange16_m<kS64x64>(a, s); break;
+        }
         if (e != hipSuccess)
             return e;
-        ProfScope ps_("exchange", s);
-        if (mask)
-            hipLaunchKernelGGL(k_exchange16<true>, dim3(nsplit * nd * per), dim3(TileEx16::NTHR), lds,
-                               s, Xw, Yw, Kp, nao, nd, nj, ldw, nsplit, jlen, accumulate, sym, scale);
-        else
-            hipLaunchKernelGGL(k_exchange16<false>, dim3(nsplit * nd * per), dim3(TileEx16::NTHR), lds,
-                               s, Xw, Yw, Kp, nao, nd, nj, ldw, nsplit, jlen, accumulate, sym, scale);
     } else {
         ProfScope ps_("exchange", s);
-        hipLaunchKernelGGL(k_exchange, dim3(nsplit * nd * per), dim3(TileExch::NTHR), 0, s, Xw, Yw, Kp,
-                           nao, nd, nj, ldw, nsplit, jlen, accumulate, sym, scale);
+        hipLaunchKernelGGL(k_exchange, dim3(nsplit * nd * ex_tiles(nao, kExM, kExN, sym)), dim3(TileExch::NTHR),
+                           0, s, Xw, Yw, Kp, nao, nd, nj, ldw, nsplit, jlen, accumulate, sym, scale);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_sum_splits_sym(const double *part, double *K, int nao, int nd, int nsplit,
+                                 hipStream_t s)
+{
+    {
+        ProfScope ps_("sum_splits", s);
+        hipLaunchKernelGGL(k_sum_splits_sym, dim3(sum_sym_blocks(nao), nd < 65535 ? nd : 65535),
+                           dim3(256), 0, s, part, K, nao, nd, nsplit);
     }
     return hipGetLastError();
 }

@@ -78,13 +78,20 @@ hipError_t launch_unpack_sym(const double *P, double *out, int nao, int nd, doub
                              int accumulate, hipStream_t s);
 // Lower triangle of every K_k from its upper triangle.
 hipError_t launch_mirror_upper(double *K, int nao, int nd, hipStream_t s);
-int exchange_nsplit(int nao, int nd, int nj, int sym = 0);
+// Tile shape (Shape16) and splits of the exchange of one chunk; the partial
+// sums of all splits stay within kp_cap bytes.
+int exchange_shape(int nao);
+int exchange_nsplit(int nao, int nd, int nj, int sym, size_t kp_cap);
 // Every chunk's contribution is multiplied by scale before it is stored or
 // added (scale 1 leaves it unchanged bit for bit).
 hipError_t launch_exchange(const double *Xw, const double *Yw, double *Kp, int nao, int nd, int nj,
                            int ldw, int nsplit, int accumulate, hipStream_t s, int sym = 0,
                            double scale = 1.0);
 hipError_t launch_sum_splits(const double *part, double *out, i64 n, int nsplit, hipStream_t s);
+// The same for symmetric K_k whose partials hold the upper triangle (both
+// triangles of K are written).
+hipError_t launch_sum_splits_sym(const double *part, double *K, int nao, int nd, int nsplit,
+                                 hipStream_t s);
 
 // derivative (jk_vjp.hip)
 hipError_t launch_omega_expand(const double *om, double *omx, int naux, int nd, int r,

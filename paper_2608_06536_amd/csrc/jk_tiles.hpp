@@ -40,9 +40,22 @@ typedef Tile<64, 64, 32, 32, 16> TileDensity;
 // The half-transform's second tile shape (a plan choice, jk_tune.h): 64 x 64,
 // four workgroups per CU; wins at small nao where 128-row tiles waste rows.
 typedef Tile<64, 64, 32, 32, 16> TileHalf64;
-// The default half-transform tile (jk_tune.h tile 4): 128 x 64 on the 16 x 16 x 4
-// engine, four 64 x 32 wave tiles, over stacked slabs.
-typedef Tile16<128, 64, 64, 32, 16> TileHalf16;
+// The half-transform on the 16 x 16 x 4 engine (jk_tune.h tile 4): shapes over
+// stacked slabs by ht_shape; packed slabs take 64 x 64 tiles per slab.
+typedef ShapeTile<kS64x64>::type TileHalf16;
+
+// Shape of the half-transform of `rows` stacked rows and ncol columns: the
+// rows are never padded (one matrix), so the columns decide between 128 and
+// 64 (500 rows a slab, 640 columns: 65.8 TF with 128 x 128, 64.3 with 128 x 64
+// and 63.7 with 64 x 64); 64 x 64 where the wider tiles would leave the chip
+// short of workgroups.
+inline int ht_shape(int64_t rows, int ncol)
+{
+    const int64_t r128 = (rows + 127) / 128;
+    const int s = shape_cost(kS128x128, 128, ncol) <= shape_cost(kS128x64, 128, ncol) ? kS128x128 : kS128x64;
+    const int64_t tiles = r128 * ((ncol + shape_bn(s) - 1) / shape_bn(s));
+    return tiles < (s == kS128x128 ? 1024 : 1536) ? kS64x64 : s;
+}
 
 __host__ __device__ inline int cdiv_i(i64 a, i64 b) { return (int)((a + b - 1) / b); }
 
@@ -109,29 +122,30 @@ __host__ __device__ inline int ht_tiles_cols(int nao, int ncol, int nq)
 {
     return nq * cdiv_i(nao, kHtM) * cdiv_i(ncol, kHtN);
 }
-__host__ __device__ inline int ex_tiles(int nao, int nd, int nsplit)
+// Symmetric exchange (C_L = C_R, K = sum X X^T): only the tiles of bm x bn
+// that reach the upper triangle n >= m, row tile mb from column tile
+// (mb bm) / bn on.
+__host__ __device__ inline int ex_tri_first(int mb, int bm, int bn) { return (mb * bm) / bn; }
+__host__ __device__ inline int ex_tri_tiles(int nao, int bm, int bn)
 {
-    return nsplit * nd * cdiv_i(nao, kExM) * cdiv_i(nao, kExN);
-}
-
-// Symmetric exchange (C_L = C_R, K = sum X X^T): only the tiles that reach
-// the upper triangle n >= m, row tile mb from column tile (mb kExM) / kExN on.
-__host__ __device__ inline int ex_tri_first(int mb) { return (mb * kExM) / kExN; }
-__host__ __device__ inline int ex_tri_tiles(int nao)
-{
-    const int nmt = cdiv_i(nao, kExM), nnt = cdiv_i(nao, kExN);
+    const int nmt = cdiv_i(nao, bm), nnt = cdiv_i(nao, bn);
     int n = 0;
     for (int mb = 0; mb < nmt; mb++) {
-        const int f = ex_tri_first(mb);
+        const int f = ex_tri_first(mb, bm, bn);
         n += f < nnt ? nnt - f : 0;
     }
     return n;
 }
-__host__ __device__ inline void ex_tri_coords(int t, int nao, int &mb, int &nb)
+// tiles of one density's K
+__host__ __device__ inline int ex_tiles(int nao, int bm, int bn, int sym)
 {
-    const int nmt = cdiv_i(nao, kExM), nnt = cdiv_i(nao, kExN);
+    return sym ? ex_tri_tiles(nao, bm, bn) : cdiv_i(nao, bm) * cdiv_i(nao, bn);
+}
+__host__ __device__ inline void ex_tri_coords(int t, int nao, int bm, int bn, int &mb, int &nb)
+{
+    const int nmt = cdiv_i(nao, bm), nnt = cdiv_i(nao, bn);
     for (mb = 0; mb < nmt; mb++) {
-        const int f = ex_tri_first(mb);
+        const int f = ex_tri_first(mb, bm, bn);
         const int cnt = f < nnt ? nnt - f : 0;
         if (t < cnt) {
             nb = f + t;
@@ -142,7 +156,10 @@ __host__ __device__ inline void ex_tri_coords(int t, int nao, int &mb, int &nb)
     mb = nmt - 1;
     nb = nnt - 1;
 }
-__host__ __device__ inline int sum_tiles(i64 n) { return cdiv_i(n, kElemTile); }
+// Elements per workgroup of the split sums: 64, one per lane of each of four
+// waves.
+constexpr int kSumTile = 64;
+__host__ __device__ inline int sum_tiles(i64 n) { return cdiv_i(n, kSumTile); }
 
 // Kk[m][n] = Kk[n][m] for m > n in lower-triangle block b of 32 x 32 (blocks
 // (bi, bj), bi >= bj, numbered row by row): fills the lower triangle from the
@@ -549,16 +566,16 @@ __device__ inline void ex_tile(const double *__restrict__ Xw, const double *__re
                                int accumulate, int tile, double *lds, int sym = 0,
                                double scale = 1.0)
 {
-    static_assert(TL::BM == kExM && TL::BN == kExN, "exchange tile shape");
-    const int nmt = cdiv_i(nao, kExM), nnt = cdiv_i(nao, kExN);
-    const int pk = sym ? ex_tri_tiles(nao) : nmt * nnt;
+    constexpr int BM = TL::BM, BN = TL::BN;
+    const int nnt = cdiv_i(nao, BN);
+    const int pk = ex_tiles(nao, BM, BN, sym);
     const int per = nd * pk;
     const int sp = tile / per;
     const int t = tile % per;
     const int k = t / pk, rem = t % pk;
     int mb, nb;
     if (sym) {
-        ex_tri_coords(rem, nao, mb, nb);
+        ex_tri_coords(rem, nao, BM, BN, mb, nb);
     } else {
         mb = rem / nnt;
         nb = rem % nnt;
@@ -579,31 +596,88 @@ __device__ inline void ex_tile(const double *__restrict__ Xw, const double *__re
         BufKC b{Yw + (i64)k * nao * ldw, ldw, nao, j1};
         Acc16<TL> acc;
         acc.zero();
-        tile_gemm16<TL, MASK>(a, b, mb * kExM, nb * kExN, j0, j1, lds, acc);
-        tile_update16(acc, mb * kExM, nb * kExN, Kk, nao, nao, nao, accumulate, scale);
+        tile_gemm16<TL, MASK>(a, b, mb * BM, nb * BN, j0, j1, lds, acc);
+        tile_update16(acc, mb * BM, nb * BN, Kk, nao, nao, nao, accumulate, scale);
     } else {
         OpKC a{Xw + (i64)k * nao * ldw, ldw, nao, j1};
         OpKC b{Yw + (i64)k * nao * ldw, ldw, nao, j1};
         Acc<TL> acc;
         acc.zero();
-        tile_gemm<TL>(a, b, mb * kExM, nb * kExN, j0, j1, lds, acc);
-        tile_foreach(acc, mb * kExM, nb * kExN, out);
+        tile_gemm<TL>(a, b, mb * BM, nb * BN, j0, j1, lds, acc);
+        tile_foreach(acc, mb * BM, nb * BN, out);
     }
 }
 
-// out[e] = sum_{s < nsplit} part[s * n + e] (fixed order).
+// The sum over the splits of one element, in four interleaved partial sums
+// (splits w, w + 4, ... for w < 4) added in order: the same arithmetic whether
+// one thread or four form them.
+__device__ __forceinline__ double sum_part(const double *__restrict__ p, i64 n, int nsplit, int w)
+{
+    double s = 0.0;
+    int sp = w;
+    for (; sp + 12 < nsplit; sp += 16) {
+        const double v0 = p[(i64)sp * n], v1 = p[(i64)(sp + 4) * n];
+        const double v2 = p[(i64)(sp + 8) * n], v3 = p[(i64)(sp + 12) * n];
+        s += v0;
+        s += v1;
+        s += v2;
+        s += v3;
+    }
+    for (; sp < nsplit; sp += 4)
+        s += p[(i64)sp * n];
+    return s;
+}
+
+// out[e] = sum_{s < nsplit} part[s * n + e] for the 64 elements of one tile,
+// wave w of the four taking the splits w, w + 4, ...
 __device__ inline void sum_tile(const double *__restrict__ part, double *__restrict__ out, i64 n,
                                 int nsplit, int tile)
 {
-    for (int u = 0; u < kElemTile / 256; u++) {
-        const i64 e = (i64)tile * kElemTile + u * 256 + threadIdx.x;
-        if (e < n) {
-            double s = 0.0;
-            for (int sp = 0; sp < nsplit; sp++)
-                s += part[(i64)sp * n + e];
-            out[e] = s;
-        }
+    __shared__ double red[4][kSumTile];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const i64 e = (i64)tile * kSumTile + lane;
+    red[w][lane] = e < n ? sum_part(part + e, n, nsplit, w) : 0.0;
+    __syncthreads();
+    if (w == 0 && e < n)
+        out[e] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+}
+
+// The same for symmetric K_k whose partials hold the upper triangle only:
+// block b of 16 x 16 (blocks (bi, bj), bi <= bj, numbered row by row from the
+// diagonal) is summed and written at (m, n) and (n, m).
+constexpr int kSymBlk = 16;
+__host__ __device__ inline int sum_sym_blocks(int nao)
+{
+    const int nb = cdiv_i(nao, kSymBlk);
+    return nb * (nb + 1) / 2;
+}
+__device__ inline void sum_sym_tile(const double *__restrict__ part, double *__restrict__ out,
+                                    int nao, i64 n, int nsplit, int b)
+{
+    __shared__ double T[kSymBlk][kSymBlk + 1];
+    const int nb = cdiv_i(nao, kSymBlk);
+    int bi = 0;
+    while (b >= nb - bi) {
+        b -= nb - bi;
+        bi++;
     }
+    const int bj = bi + b;
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    const int m = bi * kSymBlk + ty, c = bj * kSymBlk + tx;
+    if (m < nao && c < nao && m <= c) {
+        const double *p = part + (i64)m * nao + c;
+        double s[4];
+#pragma unroll
+        for (int w = 0; w < 4; w++)
+            s[w] = sum_part(p, n, nsplit, w);
+        const double v = ((s[0] + s[1]) + s[2]) + s[3];
+        out[(i64)m * nao + c] = v;
+        T[ty][tx] = v;
+    }
+    __syncthreads();
+    const int r = bj * kSymBlk + ty, q = bi * kSymBlk + tx;      // (r, q) = the mirror of (q, r)
+    if (r < nao && q < nao && r > q)
+        out[(i64)r * nao + q] = T[tx][ty];
 }
 
 } // namespace jk
