@@ -33,8 +33,9 @@ typedef struct {
                            0 = 128 x 64 of four 64 x 32 wave tiles, 1 = 64 x 64, 2 = 128 x 64
                            of eight 64 x 16 wave tiles.  On the 16x16x4 instruction, over
                            the chunk's slabs stacked as one matrix: 3 = 128 x 128, 4 =
-                           128 x 64.  Packed B and JK_MIXED use their own kernels;
-                           jk_build_batched runs 2 as 0 and 3 as 4 */
+                           128 x 64, or 64 x 64 up to nao 256.  Packed B and JK_MIXED
+                           use their own kernels; jk_build_batched runs 2 as 0 and 3
+                           as 4 */
     int32_t chunk_mb;   /* Q-chunk budget in MiB, 64 .. 4096 (jk_build_batched caps its
                            members at 256)                                             */
 } jk_tuning;

@@ -949,7 +949,6 @@ double tile_cost(int phase, const BPlan &b, const jk_problem &p)
     case jk::kPhaseHalf:
     case jk::kPhaseHalf64:
     case jk::kPhaseHalf16:
-    case jk::kPhaseHalf16W:
     case jk::kPhaseHalf16S:
     case jk::kPhaseMHalf: return (double)p.nao;
     case jk::kPhaseExchange:
@@ -1088,10 +1087,8 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
                 const int R = (int)(p[g].ndens * p[g].rank);
                 return plans[g].sym ? R : 2 * R;
             };
-            for (int shape : {jk::kS128x128, jk::kS128x64, jk::kS64x64})
-                add(shape == jk::kS128x128  ? jk::kPhaseHalf16W
-                    : shape == jk::kS128x64 ? jk::kPhaseHalf16
-                                            : jk::kPhaseHalf16S,
+            for (int shape : {jk::kS128x64, jk::kS64x64})
+                add(shape == jk::kS128x64 ? jk::kPhaseHalf16 : jk::kPhaseHalf16S,
                     c,
                     [&](int g) {
                         return (int)(((i64)nq_of(g) * p[g].nao + jk::shape_bm(shape) - 1) / jk::shape_bm(shape)) *
@@ -1099,7 +1096,7 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
                     },
                     [&](int g) {
                         return in_step(g) && plans[g].tile == 4 && !packed &&
-                               jk::ht_shape((i64)nq_of(g) * p[g].nao, ncol_of(g)) == shape;
+                               jk::ht_shape((int)p[g].nao) == shape;
                     });
             add(jk::kPhaseHalf16Packed, c,
                 [&](int g) {
@@ -1152,7 +1149,7 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
     {
         // the non-symmetric schedule's launch count, plus the mirror launch
         // (J: four phases, six with packed B)
-        const int per_step = mixed ? 5 : 6;
+        const int per_step = 5;
         nlaunch_bound = 6 + 2 + (size_t)maxsteps * per_step + 2;
     }
     c.take(sizeof(int) * std::max(S.tabs.size(), nlaunch_bound * (2 * (size_t)G + 3)));

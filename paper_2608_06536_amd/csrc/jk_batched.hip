@@ -221,9 +221,7 @@ static constexpr int kLdsEx = shape_lds<kS128x64>();
 
 hipError_t prepare_batched_kernels()
 {
-    hipError_t e = set_dynamic_lds((const void *)k_b_half_transform16<kS128x128>, shape_lds<kS128x128>());
-    if (e == hipSuccess)
-        e = set_dynamic_lds((const void *)k_b_half_transform16<kS128x64>, shape_lds<kS128x64>());
+    hipError_t e = set_dynamic_lds((const void *)k_b_half_transform16<kS128x64>, shape_lds<kS128x64>());
     if (e == hipSuccess)
         e = set_dynamic_lds((const void *)k_b_half_transform16<kS64x64>, shape_lds<kS64x64>());
     if (e == hipSuccess)
@@ -286,12 +284,6 @@ hipError_t launch_batched_phase(int phase, const BMember *M, const int *tab, int
         ProfScope ps_("b_half_transform", s);
         hipLaunchKernelGGL(k_b_half_transform16<kS128x64>, g, dim3(256), shape_lds<kS128x64>(), s, M, tab,
                            step);
-        break;
-    }
-    case kPhaseHalf16W: {
-        ProfScope ps_("b_half_transform", s);
-        hipLaunchKernelGGL(k_b_half_transform16<kS128x128>, g, dim3(256), shape_lds<kS128x128>(), s, M,
-                           tab, step);
         break;
     }
     case kPhaseHalf16S: {

@@ -94,8 +94,7 @@ enum {
     kPhaseSum = 7,
     kPhaseHalf64 = 8,    // the half-transform with 64 x 64 tiles (members whose plan chose them)
     kPhaseHalf16 = 9,    // the half-transform on the 16 x 16 x 4 engine over stacked slabs, 128 x 64 tiles
-    kPhaseHalf16W = 15,  // the same with 128 x 128 tiles (members whose columns fill them)
-    kPhaseHalf16S = 16,  // the same with 64 x 64 tiles (members of few rows)
+    kPhaseHalf16S = 15,  // the same with 64 x 64 tiles (ht_shape)
     kPhaseMirror = 10,   // lower triangle of K from the upper (symmetric members)
     kPhaseSymPack = 11,  // packed B: S = D + D^T on the packed positions
     kPhaseUnpackJ = 12,  // packed B: J in full from its packed form

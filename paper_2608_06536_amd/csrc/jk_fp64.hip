@@ -429,7 +429,7 @@ hipError_t launch_half_transform(const double *B, const double *Cc, double *Xw, 
         hipLaunchKernelGGL(k_half_transform_packed, dim3(ht_tiles_cols(nao, ncol, nq)), dim3(256), 0,
                            s, B, Cc, Xw, Yw, nao, nd, r, q0, nq, ldw, ncol);
     } else if (tile == 3 || tile == 4) {
-        const int shape = tile == 3 ? kS128x128 : ht_shape((i64)nq * nao, ncol);
+        const int shape = tile == 3 ? kS128x128 : ht_shape(nao);
         hipError_t e = hipErrorInvalidValue;
         switch (shape) {
         case kS128x128:
@@ -497,18 +497,21 @@ hipError_t launch_mirror_upper(double *K, int nao, int nd, hipStream_t s)
     return hipGetLastError();
 }
 
-int exchange_shape(int nao) { return pick_shape(nao, nao); }
+// One or two 128 x 128 tiles a side leave few workgroups per split (nao 100:
+// 30 us against 24 with 128 x 64; 208: 204 against 198), four or more keep the
+// power down (500: 904 us a chunk against 930).
+int exchange_shape(int nao) { return pick_shape(nao, nao, nao <= 256 ? kS128x64 : kS128x128); }
 
 // Splits of the exchange's inner range: the count with the least estimated
 // time.  A CU runs ceil(workgroups / CUs) workgroups one after the other at
-// the rate of the matrix cores; with one or two of them resident the stage
-// barriers cost 14% and 4% (60.5 and 62.4 against 62.9 TF and 70 sustained);
-// every round of residents pays about 3 us of first loads and output; and the
-// partial sums are written and read back (nao^2 per density and split) at
-// about 4 TB/s.  Each split keeps at least 32 inner indices, and the partials
-// stay within kp_cap bytes.  Before, at most 16 splits of at least 256 indices
-// left a single density of nao 236 and rank 48 (depth 45312, symmetric: 6
-// tiles) on 96 workgroups: 220 us; 42 splits run it in 75.
+// the rate of the matrix cores (fewer residents cover fewer of the stage
+// barriers: 0.77, 0.86 and 0.9 of the peak with one, two and three); every
+// round of residents pays about 3 us of first loads and output; the partial
+// sums are written and read back (nao^2 per density and split) at about 4
+// TB/s.  Each split keeps at least 32 inner indices, and the partials stay
+// within kp_cap bytes.  At most 16 splits of at least 256 indices, the rule
+// before, left one symmetric density of nao 236 and rank 48 (depth 45312, 6
+// tiles) on 96 workgroups: 220 us, now 83; nao 48, depth 1536: 25 us, now 8.
 int exchange_nsplit(int nao, int nd, int nj, int sym, size_t kp_cap)
 {
     const int shape = exchange_shape(nao);

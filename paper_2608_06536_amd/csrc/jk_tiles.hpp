@@ -40,22 +40,17 @@ typedef Tile<64, 64, 32, 32, 16> TileDensity;
 // The half-transform's second tile shape (a plan choice, jk_tune.h): 64 x 64,
 // four workgroups per CU; wins at small nao where 128-row tiles waste rows.
 typedef Tile<64, 64, 32, 32, 16> TileHalf64;
-// The half-transform on the 16 x 16 x 4 engine (jk_tune.h tile 4): shapes over
-// stacked slabs by ht_shape; packed slabs take 64 x 64 tiles per slab.
+// The half-transform on the 16 x 16 x 4 engine (jk_tune.h tile 4): shape by
+// ht_shape over stacked slabs; packed slabs take 64 x 64 tiles per slab.
 typedef ShapeTile<kS64x64>::type TileHalf16;
 
-// Shape of the half-transform of `rows` stacked rows and ncol columns: the
-// rows are never padded (one matrix), so the columns decide between 128 and
-// 64 (500 rows a slab, 640 columns: 65.8 TF with 128 x 128, 64.3 with 128 x 64
-// and 63.7 with 64 x 64); 64 x 64 where the wider tiles would leave the chip
-// short of workgroups.
-inline int ht_shape(int64_t rows, int ncol)
-{
-    const int64_t r128 = (rows + 127) / 128;
-    const int s = shape_cost(kS128x128, 128, ncol) <= shape_cost(kS128x64, 128, ncol) ? kS128x128 : kS128x64;
-    const int64_t tiles = r128 * ((ncol + shape_bn(s) - 1) / shape_bn(s));
-    return tiles < (s == kS128x128 ? 1024 : 1536) ? kS64x64 : s;
-}
+// Shape of the half-transform over stacked slabs (the rows are one matrix, so
+// neither shape pads them): 64 x 64, four workgroups per CU, where the inner
+// loop of nao indices is too short to cover a workgroup's first loads and
+// output with two others (nao 150: 119 us against 132, 208: 313 against 319),
+// 128 x 64 beyond, whose wave tiles read less per product (374: 3.08 ms against
+// 3.13, 500: 10.1 against 10.3).
+inline int ht_shape(int nao) { return nao <= 256 ? kS64x64 : kS128x64; }
 
 __host__ __device__ inline int cdiv_i(i64 a, i64 b) { return (int)((a + b - 1) / b); }
 
@@ -483,7 +478,10 @@ __device__ inline void ht_tile_flat(const double *__restrict__ B, const double *
     acc.zero();
     // No inner-index masking: past row nao - 1, Cc reads zero (the end of its
     // resource), and the slab rows read there are finite data of the next row.
-    tile_gemm16<TL, false>(a, b, mb * BM, cb * BN, 0, nao, lds, acc);
+    if constexpr (TL::BN == 128)
+        tile_gemm16<TL, false>(a, b, mb * BM, cb * BN, 0, nao, lds, acc);
+    else
+        Gemm16Stream<TL, BufKC, BufIC>::run(a, b, mb * BM, cb * BN, nao, lds, acc);
     // Output (t, c) goes to col(c)[row(t)]: col(c) = X_ws or Y_ws at density
     // k = c' / r, column i = c' % r (c' = c or c - R), and row(t) = m ldw +
     // ql r for t = ql nao + m.  A lane holds NB columns and 4 MA rows
@@ -543,7 +541,7 @@ __device__ inline void ht_tile16_packed(const double *__restrict__ B, const doub
     BufIC b{Cc, R2, nc, nao};
     Acc16<TL> acc;
     acc.zero();
-    tile_gemm16<TL, false>(a, b, mb * BM, cb * BN, 0, nao, lds, acc);
+    Gemm16Stream<TL, BufPackedSym, BufIC>::run(a, b, mb * BM, cb * BN, nao, lds, acc);
     tile_foreach16(acc, mb * BM, cb * BN, [&](int m, int c, double v) {
         if (m < nao && c < nc) {
             double *dst = c < R ? Xw : Yw;
