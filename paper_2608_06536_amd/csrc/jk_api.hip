@@ -119,11 +119,11 @@ int chunk_slabs(const jk_problem *p, size_t budget)
 }
 
 struct FwdPlan {
-    int qc, ldw, npb, plen, ndp, nsplit;
+    int qc, ldw, nsplit;
     int nsplit_sym;     // exchange splits when C_L = C_R (upper-triangle tiles)
     bool packed;        // B slabs stored as packed upper triangles
     i64 slab;           // doubles per slab of B
-    size_t o_cc, o_d, o_s, o_part, o_g, o_x, o_y, o_kp, total;
+    size_t o_cc, o_s, o_part, o_g, o_x, o_y, o_kp, total;
 };
 
 FwdPlan plan_forward(const jk_problem *p, size_t budget = kChunkBudget)
@@ -133,22 +133,13 @@ FwdPlan plan_forward(const jk_problem *p, size_t budget = kChunkBudget)
     const i64 npos = nao * nao;
     f.qc = chunk_slabs(p, budget);
     f.ldw = (int)(f.qc * r);
-    f.ndp = (int)(((nd + 7) / 8) * 8);
     f.packed = packed_b(p);
     f.slab = f.packed ? jk::pk_size((int)nao) : npos;
-    // gamma runs over the stored positions of a slab
-    // gamma: packed slabs stream their positions in blocks of plen; full
-    // squares read their upper triangles in row groups of plen rows, npb
-    // pairs of groups (coulomb_upper.hpp)
-    if (f.packed)
-        f.npb = jk::project_nblocks(f.slab, (int)p->naux, (int)nd, &f.plen);
-    else
-        f.npb = jk::project_upper_blocks((int)nao, (int)p->naux, (int)((nd + 7) / 8), &f.plen);
     Carve c;
     f.o_cc = c.take(sizeof(double) * nao * 2 * R);
-    f.o_d = c.take(sizeof(double) * nd * npos);
-    f.o_s = c.take(f.packed ? sizeof(double) * nd * f.slab : 0);
-    f.o_part = c.take(sizeof(double) * (size_t)f.npb * p->naux * f.ndp);
+    // gamma: the folded densities and the partial sums over blocks of positions
+    f.o_s = c.take(sizeof(double) * nd * jk::pk_size((int)nao));
+    f.o_part = c.take(sizeof(double) * jk::project_part_doubles((int)nao, (int)p->naux, (int)nd));
     f.o_g = c.take(sizeof(double) * nd * p->naux);
     f.o_x = c.take(sizeof(double) * nd * nao * (size_t)f.ldw);
     f.o_y = c.take(sizeof(double) * nd * nao * (size_t)f.ldw);
@@ -182,11 +173,10 @@ int chunk_slabs_vjp(const jk_problem *p)
 }
 
 struct VjpPlan {
-    int qc, ldw, npb, plen, ndp, nsplit_c;
-    bool paired;        // omega and gamma in one pass over B (2 nd <= 16)
-    bool packed;        // JK_B_PACKED: chunks unpacked into o_bu, packed W, D, E
-    size_t o_cc, o_d, o_e, o_part, o_g, o_om, o_omx, o_x, o_y, o_pr, o_dcp;
-    size_t o_bu, o_wdp, o_ep, total;
+    int qc, ldw, nsplit_c;
+    bool packed;        // JK_B_PACKED: chunks unpacked into o_bu
+    size_t o_cc, o_wdp, o_e, o_part, o_om, o_omx, o_x, o_y, o_pr, o_dcp;
+    size_t o_bu, total;
 };
 
 VjpPlan plan_vjp(const jk_problem *p)
@@ -194,62 +184,27 @@ VjpPlan plan_vjp(const jk_problem *p)
     VjpPlan f;
     const i64 nao = p->nao, nd = p->ndens, r = p->rank, R = nd * r, naux = p->naux;
     f.packed = packed_b(p);
-    // positions per slab of B as stored (the projections stream them)
-    const i64 npos = f.packed ? nao * (nao + 1) / 2 : nao * nao;
     f.qc = chunk_slabs_vjp(p);
     f.ldw = (int)(f.qc * r);
-    f.ndp = (int)(((nd + 7) / 8) * 8);
-    f.npb = jk::project_nblocks(npos, (int)naux, (int)nd, &f.plen);
     f.nsplit_c = jk::vjp_stage_c_nsplit((int)nao, (int)R, f.qc);
-    f.paired = 2 * nd <= 16;
-    size_t part = (size_t)f.npb * naux * f.ndp;
-    if (f.paired) {
-        // 2 nd <= 8: one group of the 8-wide projection; else the 16-wide one
-        int plen2;
-        const size_t p2 = 2 * nd <= 8
-                              ? (size_t)jk::project_nblocks(npos, (int)naux, (int)(2 * nd), &plen2) * naux * 8
-                              : (size_t)jk::project16_nblocks(npos, (int)naux, &plen2) * naux * 16;
-        part = part > p2 ? part : p2;
-        if (!f.packed) {
-            // full squares: [W | D] folded onto the upper triangles
-            int G;
-            const size_t p3 = (size_t)jk::project_upper_blocks((int)nao, (int)naux, 1, &G) * naux *
-                              (2 * nd <= 8 ? 8 : 16);
-            part = part > p3 ? part : p3;
-        }
-    }
-    if (!f.packed) {
-        // full squares, W and D projected on their own (groups of 8)
-        int G;
-        const size_t p4 = (size_t)jk::project_upper_blocks((int)nao, (int)naux, (int)((nd + 7) / 8), &G) *
-                          naux * f.ndp;
-        part = part > p4 ? part : p4;
-    }
     Carve c;
-    const i64 nsq = nao * nao;
+    const i64 nsq = nao * nao, npk = jk::pk_size((int)nao);
     f.o_cc = c.take(sizeof(double) * nao * 2 * R);
-    // [W | D]: the cotangent copied in front of the densities (folded in
-    // place for full squares; paired, the two in one pass over B)
-    f.o_d = c.take(sizeof(double) * (f.paired || !f.packed ? 2 : 1) * nd * nsq);
-    f.o_e = c.take(sizeof(double) * nd * nsq);
-    f.o_part = c.take(sizeof(double) * part);
-    f.o_g = c.take(sizeof(double) * nd * naux);
-    f.o_om = c.take(sizeof(double) * (f.paired ? 2 : 1) * nd * naux);   // paired: [omega | gamma]
+    // [W | D] folded onto the packed positions: one pass over B gives
+    // [omega | gamma]
+    f.o_wdp = c.take(sizeof(double) * 2 * nd * npk);
+    f.o_e = c.take(f.packed ? 0 : sizeof(double) * nd * nsq);
+    f.o_part = c.take(sizeof(double) * std::max(jk::project_part_doubles((int)nao, (int)naux, (int)(2 * nd)),
+                                                jk::project_part_doubles((int)nao, (int)naux, (int)nd)));
+    f.o_om = c.take(sizeof(double) * 2 * nd * naux);
     f.o_omx = c.take(sizeof(double) * naux * R);
     f.o_x = c.take(sizeof(double) * nd * nao * (size_t)f.ldw);
     f.o_y = c.take(sizeof(double) * nd * nao * (size_t)f.ldw);
     f.o_pr = c.take(sizeof(double) * (size_t)f.qc * nao * 2 * R);
     f.o_dcp = c.take(sizeof(double) * (size_t)f.nsplit_c * nao * 2 * R);
-    if (f.packed) {
-        // the chunk's slabs as full squares (stage C, their last reader, runs
-        // on the stream that unpacks the next chunk); W, D and E as packed
-        // sums over each symmetric pair of positions
-        f.o_bu = c.take(sizeof(double) * (size_t)f.qc * nsq);
-        f.o_wdp = c.take(sizeof(double) * 2 * nd * npos);
-        f.o_ep = c.take(sizeof(double) * nd * npos);
-    } else {
-        f.o_bu = f.o_wdp = f.o_ep = 0;
-    }
+    // the chunk's slabs as full squares (stage C, their last reader, runs on
+    // the stream that unpacks the next chunk)
+    f.o_bu = f.packed ? c.take(sizeof(double) * (size_t)f.qc * nsq) : 0;
     f.total = c.off;
     return f;
 }
@@ -380,30 +335,17 @@ struct BuildOut {
     double cj = 0.0;
 };
 
-// The Coulomb part: gamma_kQ = <D_k, B^Q> in FP64, then
-// out (+)= scale sum_Q gamma_kQ B^Q.  Packed slabs: gamma pairs B^Q with the
-// packed S_k = D_k + D_k^T (diagonal once), J runs over the packed positions
-// into the D buffer and is written out in full by the unpack pass.
+// The Coulomb part: gamma_kQ = <D_k, B^Q> in FP64 (D folded onto the upper
+// triangle), then out (+)= scale sum_Q gamma_kQ B^Q.
 jk_status coulomb_part(const FwdPlan &f, int nao, int naux, int nd, int r, const double *B,
                        const double *CL, const double *CR, double *out, double scale,
                        int accumulate, char *ws, hipStream_t s)
 {
-    double *D = (double *)(ws + f.o_d);
-    double *part = (double *)(ws + f.o_part);
-    double *g = (double *)(ws + f.o_g);
-    JK_TRY(jk::launch_density(CL, CR, D, nao, nd, r, s));
-    if (!f.packed) {
-        // the upper triangles of the symmetric slabs: D folded onto its own
-        JK_TRY(jk::launch_fold_upper(D, nao, nd, s));
-        JK_TRY(jk::launch_project_upper(B, D, part, g, nao, naux, nd, s));
-        JK_TRY(jk::launch_coulomb_upper(B, g, out, nao, naux, nd, s, scale, accumulate));
-        return JK_OK;
-    }
     double *S = (double *)(ws + f.o_s);
-    JK_TRY(jk::launch_sym_pack(D, S, nao, nd, s));
-    JK_TRY(jk::launch_project(B, S, part, g, naux, nd, f.slab, s));
-    JK_TRY(jk::launch_coulomb(B, g, D, naux, nd, f.slab, s));
-    JK_TRY(jk::launch_unpack_sym(D, out, nao, nd, scale, accumulate, s));
+    double *g = (double *)(ws + f.o_g);
+    JK_TRY(jk::launch_fold_density(CL, CR, S, nao, nd, r, s));
+    JK_TRY(jk::launch_project(B, S, (double *)(ws + f.o_part), g, nao, naux, nd, f.packed, s));
+    JK_TRY(jk::launch_coulomb(B, g, out, nao, naux, nd, f.packed, s, scale, accumulate));
     return JK_OK;
 }
 
@@ -478,23 +420,17 @@ jk_status vjp_fp64(const jk_problem *p, const double *B, const double *CL, const
     const int nao = (int)p->nao, naux = (int)p->naux, nd = (int)p->ndens, r = (int)p->rank;
     const int R = nd * r;
     const i64 npos = (i64)nao * nao;
-    // Packed B: the projections and the affine term run over the packed
-    // positions, with W, D and E folded onto them (each symmetric pair of
-    // positions summed: <W, B^Q> over the square is the packed dot product);
-    // every chunk is unpacked to full squares for the half-transform and
-    // stage C, and stage D writes the packed gradient.
+    // Packed B: every chunk is unpacked to full squares for the half-transform
+    // and stage C, and stage D and the affine term write the packed gradient.
     const bool pk = f.packed;
-    const i64 npk = pk ? (i64)nao * (nao + 1) / 2 : npos;
-    double *WDp = pk ? (double *)(ws + f.o_wdp) : nullptr;
-    double *Ep = pk ? (double *)(ws + f.o_ep) : nullptr;
+    const i64 npk = (i64)nao * (nao + 1) / 2;
+    double *WDp = (double *)(ws + f.o_wdp);
     const int has_w = W != nullptr, has_v = V != nullptr;
     const bool want_db = dB != nullptr, want_dc = dCL != nullptr;
     double *Cc = (double *)(ws + f.o_cc);
-    double *D = (double *)(ws + f.o_d);
     double *E = (double *)(ws + f.o_e);
     double *part = (double *)(ws + f.o_part);
-    double *g = (double *)(ws + f.o_g);
-    double *om = (double *)(ws + f.o_om);
+    double *om = (double *)(ws + f.o_om), *g = om + (i64)nd * naux;     // [omega | gamma]
     double *omx = (double *)(ws + f.o_omx);
     double *Xw = (double *)(ws + f.o_x);
     double *Yw = (double *)(ws + f.o_y);
@@ -506,61 +442,24 @@ jk_status vjp_fp64(const jk_problem *p, const double *B, const double *CL, const
     double *Yx = sym ? Xw : Yw;
 
     JK_TRY(jk::launch_pack_c(CL, CR, Cc, nao, nd, r, s));
-    if (has_w && want_db && f.paired) {
-        // omega_kQ = <W_k, B^Q> and gamma_kQ = <D_k, B^Q> in one pass over B:
-        // the 2 nd matrices [W | D] against each slab; E = D - 2 D^T.
-        double *WD = D;
-        D = WD + (i64)nd * npos;
-        g = om + (i64)nd * naux;
-        JK_TRY(hipMemcpyAsync(WD, W, sizeof(double) * (size_t)nd * npos, hipMemcpyDeviceToDevice, s));
-        JK_TRY(jk::launch_density(CL, CR, D, nao, nd, r, s));
-        JK_TRY(jk::launch_vjp_e_matrix(D, E, nao, nd, s));
-        if (pk) {
-            JK_TRY(jk::launch_sym_pack(WD, WDp, nao, 2 * nd, s));
-            if (2 * nd <= 8)
-                JK_TRY(jk::launch_project(B, WDp, part, om, naux, 2 * nd, npk, s));
-            else
-                JK_TRY(jk::launch_project16(B, WDp, part, om, naux, 2 * nd, npk, s));
-        } else {
-            // the upper triangles of the symmetric slabs: [W | D] folded onto
-            // their own (E is formed from D above, before the fold)
-            JK_TRY(jk::launch_fold_upper(WD, nao, 2 * nd, s));
-            JK_TRY(jk::launch_project_upper(B, WD, part, om, nao, naux, 2 * nd, s, 2 * nd > 8));
-        }
-        JK_TRY(jk::launch_omega_expand(om, omx, naux, nd, r, s));
-    } else if (has_w && pk) {
-        // omega_kQ = <W_k, B^Q>; for dB also gamma_kQ = <D_k, B^Q> and E = D - 2 D^T.
-        JK_TRY(jk::launch_sym_pack(W, WDp, nao, nd, s));
-        JK_TRY(jk::launch_project(B, WDp, part, om, naux, nd, npk, s));
-        JK_TRY(jk::launch_omega_expand(om, omx, naux, nd, r, s));
-        if (want_db) {
-            JK_TRY(jk::launch_density(CL, CR, D, nao, nd, r, s));
-            JK_TRY(jk::launch_sym_pack(D, WDp + (i64)nd * npk, nao, nd, s));
-            JK_TRY(jk::launch_project(B, WDp + (i64)nd * npk, part, g, naux, nd, npk, s));
-            JK_TRY(jk::launch_vjp_e_matrix(D, E, nao, nd, s));
-        }
-    } else if (has_w) {
-        // The same from a folded copy of W (then D), in the row groups of the
-        // paired pass: omega comes out bit for bit as there.
-        double *Wc = D;
-        D = Wc + (i64)nd * npos;
-        JK_TRY(hipMemcpyAsync(Wc, W, sizeof(double) * (size_t)nd * npos, hipMemcpyDeviceToDevice, s));
-        JK_TRY(jk::launch_fold_upper(Wc, nao, nd, s));
-        JK_TRY(jk::launch_project_upper(B, Wc, part, om, nao, naux, nd, s));
-        JK_TRY(jk::launch_omega_expand(om, omx, naux, nd, r, s));
-        if (want_db) {
-            JK_TRY(jk::launch_density(CL, CR, D, nao, nd, r, s));
-            JK_TRY(jk::launch_vjp_e_matrix(D, E, nao, nd, s));
-            JK_TRY(jk::launch_fold_upper(D, nao, nd, s));
-            JK_TRY(jk::launch_project_upper(B, D, part, g, nao, naux, nd, s));
-        }
-    }
-    // the affine term's matrices as the positions of dB are stored
+    // omega_kQ = <W_k, B^Q>; for dB also gamma_kQ = <D_k, B^Q>, in one pass over
+    // B, and E_k = D_k - 2 D_k^T.  On the packed positions E folds to -(D_k +
+    // D_k^T), the folded density itself with its sign changed.
     const double *Wa = W, *Ea = E;
-    if (pk && has_w && want_db) {
-        JK_TRY(jk::launch_sym_pack(E, Ep, nao, nd, s));
-        Wa = WDp;                                 // [W | D] packed, W first
-        Ea = Ep;
+    double esign = 1.0;
+    if (has_w) {
+        JK_TRY(jk::launch_sym_pack(W, WDp, nao, nd, s));
+        if (want_db)
+            JK_TRY(jk::launch_fold_density(CL, CR, WDp + (i64)nd * npk, nao, nd, r, s));
+        JK_TRY(jk::launch_project(B, WDp, part, om, nao, naux, want_db ? 2 * nd : nd, pk, s));
+        JK_TRY(jk::launch_omega_expand(om, omx, naux, nd, r, s));
+        if (want_db && pk) {
+            Wa = WDp;
+            Ea = WDp + (i64)nd * npk;
+            esign = -1.0;
+        } else if (want_db) {
+            JK_TRY(jk::launch_vjp_e_matrix(CL, CR, E, nao, nd, r, s));
+        }
     }
     // Stage B's two products run side by side on two streams:
     //   main: HT(c), B[P'](c), C(c), D(c), affine(c)
@@ -606,7 +505,8 @@ jk_status vjp_fp64(const jk_problem *p, const double *B, const double *CL, const
             else
                 JK_TRY(jk::launch_vjp_stage_d(L, Cc, dB, nao, R, q0, nq, s));
             if (has_w)
-                JK_TRY(jk::launch_vjp_db_affine(g, om, Wa, Ea, dB, nd, naux, npk, q0, nq, s));
+                JK_TRY(jk::launch_vjp_db_affine(g, om, Wa, Ea, esign, dB, nd, naux, pk ? npk : npos, q0,
+                                                nq, s));
         }
     }
     if (want_dc)
@@ -880,6 +780,7 @@ struct BPlan {
     int tile = 0;        // FP64 half-transform: 0, 1 (4x4x4) or 4 (16x16x4, stacked slabs)
     int sym = 0;         // symmetric densities routed to the X-only path
     int nsplit = 1;      // exchange splits of the path taken
+    jk::PjGeom pj = {};  // gamma's split
     size_t total = 0;
 };
 
@@ -943,8 +844,9 @@ int batched_ex_shape(int nao) { return jk::pick_shape(nao, nao, jk::kS128x64); }
 double tile_cost(int phase, const BPlan &b, const jk_problem &p)
 {
     switch (phase) {
-    case jk::kPhaseProject: return (double)b.f.plen * (b.f.packed ? 1 : p.nao);
-    case jk::kPhaseReduce: return (double)b.f.npb;
+    case jk::kPhaseProject:
+        return (double)b.pj.qlen * b.pj.per;
+    case jk::kPhaseReduce: return (double)b.pj.nbg;
     case jk::kPhaseCoulomb: return (double)p.naux;
     case jk::kPhaseHalf:
     case jk::kPhaseHalf64:
@@ -973,6 +875,13 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
         maxsteps = std::max(maxsteps, st);
     }
     const int w = want(&p[0]);
+    int width = 1;      // of gamma's and J's widest member
+    for (int g = 0; g < G; g++) {
+        width = std::max(width, jk::pj_width((int)p[g].ndens));
+        // the batch's workgroups together, but at least 256 per member
+        plans[g].pj = jk::pj_geom((int)p[g].nao, (int)p[g].naux, (int)p[g].ndens,
+                                  std::max(jk::kPjWgs / G, 256));
+    }
     struct Pending {
         int phase, step, arg;
         std::vector<int> members;
@@ -1004,22 +913,22 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
     };
     auto all = [](int) { return true; };
     const bool packed = packed_b(&p[0]);
-    auto rows = [&](int g) { return (int)(p[g].ndens * p[g].nao); };
     if (w & JK_WANT_J) {
-        add(jk::kPhaseDensity, 0, [&](int g) { return jk::density_tiles((int)p[g].nao, (int)p[g].ndens); }, all);
-        add(packed ? jk::kPhaseSymPack : jk::kPhaseFoldUpper, 0, rows, all);
-        add(jk::kPhaseProject, 0,
-            [&](int g) { return jk::project_tiles((int)p[g].naux, (int)p[g].ndens, plans[g].f.npb); }, all);
-        add(jk::kPhaseReduce, 0, [&](int g) { return jk::reduce_tiles((int)p[g].naux, (int)p[g].ndens); },
+        add(jk::kPhaseDensity, 0, [&](int g) { return jk::fold_tiles((int)p[g].nao, (int)p[g].ndens); }, all);
+        add(jk::kPhaseProject, 0, [&](int g) { return jk::pj_tiles(plans[g].pj, (int)p[g].naux); }, all,
+            width);
+        add(jk::kPhaseReduce, 0,
+            [&](int g) {
+                const int nd = (int)p[g].ndens;
+                return jk::reduce_tiles((int)p[g].naux, jk::pj_groups(nd) * jk::pj_width(nd));
+            },
             all);
         add(jk::kPhaseCoulomb, 0,
             [&](int g) {
-                return packed ? jk::coulomb_tiles((int)p[g].ndens, plans[g].f.slab)
-                              : jk::cu_tiles((int)p[g].nao, (int)p[g].ndens);
+                return jk::cu_tiles((int)p[g].nao, (int)p[g].ndens, jk::pj_width((int)p[g].ndens),
+                                    jk::kBatchRuns);
             },
-            all);
-        if (packed)
-            add(jk::kPhaseUnpackJ, 0, rows, all);
+            all, width);
     }
     if (w & JK_WANT_K) {
         add(jk::kPhasePack, 0,
@@ -1148,7 +1057,7 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
     size_t nlaunch_bound = 0;
     {
         // the non-symmetric schedule's launch count, plus the mirror launch
-        // (J: four phases, six with packed B)
+        // (J: four phases)
         const int per_step = 5;
         nlaunch_bound = 6 + 2 + (size_t)maxsteps * per_step + 2;
     }
@@ -1171,8 +1080,7 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
         m.ldw = plans[g].f.ldw;
         m.nsplit = plans[g].nsplit;
         m.exs = batched_ex_shape(m.nao);
-        m.npb = plans[g].f.npb;
-        m.plen = plans[g].f.plen;
+        m.pj = plans[g].pj;
         m.sym = plans[g].sym;
         if (mixed) {
             const MixPlan &x = plans[g].x;
@@ -1337,8 +1245,7 @@ jk_status build_batched(int32_t nprob, const jk_problem *p, const double *const 
         m.J = J[g];
         m.K = K[g];
         m.Cc = (double *)(base + f.o_cc);
-        m.D = (double *)(base + f.o_d);
-        m.S = f.packed ? (double *)(base + f.o_s) : nullptr;
+        m.S = (double *)(base + f.o_s);
         m.part = (double *)(base + f.o_part);
         m.g = (double *)(base + f.o_g);
         m.goff = (long long)((S.region[g] + f.o_g) / sizeof(double));

@@ -34,57 +34,23 @@ __global__ void __launch_bounds__(256) k_b_density(const BMember *__restrict__ M
     __shared__ double lds[TileDensity::LDS_DOUBLES];
     int loc;
     const BMember &m = M[find_member(tab, blockIdx.x, loc)];
-    density_tile(m.CL, m.CR, m.D, m.nao, m.r, loc, lds);
+    fold_density_tile(m.CL, m.CR, m.S, m.nao, m.r, loc, lds);
 }
 
-// S_k = D_k + D_k^T on the packed positions (D_k[m][m] on the diagonal):
-// one row m of one k per workgroup.
-__global__ void __launch_bounds__(256) k_b_sym_pack(const BMember *__restrict__ M,
-                                                    const int *__restrict__ tab)
+// Group widths up to MAX: 16 takes all; batches of at most 8 densities run with
+// the registers of the narrower passes (8).
+template <int MAX>
+__global__ void __launch_bounds__(256, MAX == 16 ? 2 : 3)
+    k_b_project(const BMember *__restrict__ M, const int *__restrict__ tab)
 {
+    __shared__ double lds[(2 * 4 * kPjQ + kPjMaxQ) * MAX];
     int loc;
     const BMember &m = M[find_member(tab, blockIdx.x, loc)];
-    const int k = loc / m.nao, a = loc % m.nao;
-    const double *Dk = m.D + (i64)k * m.npos;
-    double *row = m.S + (i64)k * m.bslab + pk_row(a, m.nao) - a;
-    for (int b = a + threadIdx.x; b < m.nao; b += 256)
-        row[b] = b == a ? Dk[(i64)a * m.nao + a] : Dk[(i64)a * m.nao + b] + Dk[(i64)b * m.nao + a];
-}
-
-// D_k folded onto its upper triangle in place (coulomb_upper.hpp): one row
-// per workgroup.
-__global__ void __launch_bounds__(256) k_b_fold_upper(const BMember *__restrict__ M,
-                                                      const int *__restrict__ tab)
-{
-    int loc;
-    const BMember &m = M[find_member(tab, blockIdx.x, loc)];
-    fold_upper_row(m.D, m.nao, loc / m.nao, loc % m.nao);
-}
-
-// J_k[a][b] from the packed J_k the Coulomb phase left in D: one row per
-// workgroup.
-__global__ void __launch_bounds__(256) k_b_unpack_j(const BMember *__restrict__ M,
-                                                    const int *__restrict__ tab)
-{
-    int loc;
-    const BMember &m = M[find_member(tab, blockIdx.x, loc)];
-    const int k = loc / m.nao, a = loc % m.nao;
-    const double *Pk = m.D + (i64)k * m.bslab;
-    double *o = m.J + ((i64)k * m.nao + a) * m.nao;
-    for (int b = threadIdx.x; b < m.nao; b += 256)
-        o[b] = Pk[pk_index(a, b, m.nao)];
-}
-
-__global__ void __launch_bounds__(256) k_b_project(const BMember *__restrict__ M,
-                                                   const int *__restrict__ tab)
-{
-    __shared__ double lds[TileProject::LDS_DOUBLES];
-    int loc;
-    const BMember &m = M[find_member(tab, blockIdx.x, loc)];
-    if (m.packed)
-        project_tile(m.B, m.S, m.part, m.naux, m.nd, m.bslab, m.plen, loc, lds);
-    else
-        project_upper_tile<TileProject, 8>(m.B, m.D, m.part, m.naux, m.nd, m.nao, m.plen, loc, lds);
+    width_dispatch<MAX>(pj_width(m.nd), [&](auto nk) {
+        constexpr int NK = decltype(nk)::value;
+        project_tile<NK>(m.B, m.S, m.part, m.nao, m.naux, m.nd, m.packed, m.pj, loc,
+                         (double (*)[4][kPjQ][NK])lds, (double (*)[NK])(lds + 2 * 4 * kPjQ * NK));
+    });
 }
 
 __global__ void __launch_bounds__(256) k_b_reduce(const BMember *__restrict__ M,
@@ -92,21 +58,24 @@ __global__ void __launch_bounds__(256) k_b_reduce(const BMember *__restrict__ M,
 {
     int loc;
     const BMember &m = M[find_member(tab, blockIdx.x, loc)];
-    reduce_tile(m.part, m.g, m.naux, m.nd, m.npb, loc);
+    reduce_tile(m.part, m.g, m.naux, m.nd, m.pj.nkg * pj_width(m.nd), m.pj.nbg, loc);
 }
 
 // ws: the workspace start (where M lies), as doubles; g is read at ws + goff.
-__global__ void __launch_bounds__(256) k_b_coulomb(const BMember *__restrict__ M,
+// kBatchRuns runs of positions per wave for every member: the same sums (the
+// slices are the member's own).
+template <int MAX>
+__global__ void __launch_bounds__(512) k_b_coulomb(const BMember *__restrict__ M,
                                                    const int *__restrict__ tab,
                                                    const double *__restrict__ ws)
 {
+    __shared__ double red[8 * MAX * 64];
     int loc;
     const BMember &m = M[find_member(tab, blockIdx.x, loc)];
     const double *g = ws + m.goff;
-    if (m.packed)
-        coulomb_tile(m.B, g, m.D, m.naux, m.nd, m.bslab, loc);
-    else
-        coulomb_upper_tile(m.B, g, m.J, m.nao, m.naux, m.nd, loc);
+    width_dispatch<MAX>(pj_width(m.nd), [&](auto nk) {
+        coulomb_tile<decltype(nk)::value, kBatchRuns>(m.B, g, m.J, m.nao, m.naux, m.nd, m.packed, loc, red);
+    });
 }
 
 __global__ void __launch_bounds__(256, 3) k_b_half_transform(const BMember *__restrict__ M,
@@ -257,7 +226,7 @@ hipError_t launch_batched_phase(int phase, const BMember *M, const int *tab, int
     }
     case kPhaseProject: {
         ProfScope ps_("b_project", s);
-        hipLaunchKernelGGL(k_b_project, g, dim3(256), 0, s, M, tab);
+        hipLaunchKernelGGL(arg > 8 ? k_b_project<16> : k_b_project<8>, g, dim3(256), 0, s, M, tab);
         break;
     }
     case kPhaseReduce: {
@@ -267,7 +236,8 @@ hipError_t launch_batched_phase(int phase, const BMember *M, const int *tab, int
     }
     case kPhaseCoulomb: {
         ProfScope ps_("b_coulomb", s);
-        hipLaunchKernelGGL(k_b_coulomb, g, dim3(256), 0, s, M, tab, (const double *)M);
+        hipLaunchKernelGGL(arg > 8 ? k_b_coulomb<16> : k_b_coulomb<8>, g, dim3(512), 0, s, M, tab,
+                           (const double *)M);
         break;
     }
     case kPhaseHalf: {
@@ -296,21 +266,6 @@ hipError_t launch_batched_phase(int phase, const BMember *M, const int *tab, int
         ProfScope ps_("b_half_transform", s);
         hipLaunchKernelGGL(k_b_half_transform16_packed, g, dim3(TileB16::NTHR), kLds16, s, M, tab,
                            step);
-        break;
-    }
-    case kPhaseFoldUpper: {
-        ProfScope ps_("b_fold_upper", s);
-        hipLaunchKernelGGL(k_b_fold_upper, g, dim3(256), 0, s, M, tab);
-        break;
-    }
-    case kPhaseSymPack: {
-        ProfScope ps_("b_sym_pack", s);
-        hipLaunchKernelGGL(k_b_sym_pack, g, dim3(256), 0, s, M, tab);
-        break;
-    }
-    case kPhaseUnpackJ: {
-        ProfScope ps_("b_unpack_j", s);
-        hipLaunchKernelGGL(k_b_unpack_j, g, dim3(256), 0, s, M, tab);
         break;
     }
     case kPhaseExchange: {

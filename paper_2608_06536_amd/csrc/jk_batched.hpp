@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "coulomb_upper.hpp"
+
 namespace jk {
 
 // One problem of a batch: its inputs, outputs, the workspace pointers of its
@@ -10,7 +12,7 @@ namespace jk {
 struct BMember {
     const double *B, *CL, *CR;
     double *J, *K;
-    double *Cc, *D, *part, *g, *Xw, *Yw, *Kp;
+    double *Cc, *S, *part, *g, *Xw, *Yw, *Kp;   // S: densities folded onto the packed positions
     long long npos;
     // g as an offset in doubles from the start of the workspace (the batch's
     // descriptors): the Coulomb pass reads g through a kernel argument, whose
@@ -18,7 +20,8 @@ struct BMember {
     // wave, not per lane)
     long long goff;
     int nao, naux, nd, r;
-    int qc, ldw, nsplit, npb, plen;
+    int qc, ldw, nsplit;
+    PjGeom pj;          // gamma's split
     int exs;            // FP64: the exchange's tile shape (Shape16)
     int sym;            // C_L and C_R are one buffer: X only, K on the upper triangle
     // JK_MIXED members: digit planes (single-buffered), their row exponents
@@ -30,13 +33,16 @@ struct BMember {
     long long bkb, bps, ckb, cps, xkb, xps;
     int mp, kp, cp, cpx;    // padded rows / inner bytes; cpx: [C_L | C_R] rows the products use
     int mpb;                // rows per slab of B's planes (the half-transform's row tiles)
-    // Packed-triangular B (jk.h JK_B_PACKED): bslab doubles per slab of B
-    // (npos for full squares); gamma pairs B with S = D + D^T folded onto the
-    // packed positions, and J is formed packed in D, then written out in full.
-    double *S;
+    // doubles per slab of B: npos for full squares, packed-triangular slabs
+    // (jk.h JK_B_PACKED) otherwise
     long long bslab;
     int packed;
 };
+
+// Runs of 64 positions per wave of the Coulomb pass (coulomb_upper.hpp): four
+// whatever the size, as the members together fill the chip (24 members of nao
+// 100-250: 544 us, 604 with one run; 12 of 100-500: 1.50 ms, 1.72).
+constexpr int kBatchRuns = 4;
 
 // Table layout: tab[0] = n entries, tab[1 .. n+1] = start offsets (n+1
 // values), tab[n+2 .. 2n+2) = member indices.  Returns the member of tile t
@@ -85,7 +91,7 @@ __device__ __forceinline__ void chunk_of(const BMember &m, int c, int &q0, int &
 
 enum {
     kPhasePack = 0,
-    kPhaseDensity = 1,
+    kPhaseDensity = 1,   // the folded densities
     kPhaseProject = 2,
     kPhaseReduce = 3,
     kPhaseCoulomb = 4,
@@ -96,10 +102,7 @@ enum {
     kPhaseHalf16 = 9,    // the half-transform on the 16 x 16 x 4 engine over stacked slabs, 128 x 64 tiles
     kPhaseHalf16S = 15,  // the same with 64 x 64 tiles (ht_shape)
     kPhaseMirror = 10,   // lower triangle of K from the upper (symmetric members)
-    kPhaseSymPack = 11,  // packed B: S = D + D^T on the packed positions
-    kPhaseUnpackJ = 12,  // packed B: J in full from its packed form
     kPhaseHalf16Packed = 13,  // packed B: the 16 x 16 x 4 half-transform, tiles per slab
-    kPhaseFoldUpper = 14,     // full squares: D folded onto its upper triangle (gamma)
     // JK_MIXED phases (jk_mixed.hip)
     kPhaseMSliceC = 20,  // digit planes of [C_L | C_R]
     kPhaseMSliceB = 21,  // digit planes of the chunk's slabs of B

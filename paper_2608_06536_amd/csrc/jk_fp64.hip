@@ -17,46 +17,6 @@ __global__ void __launch_bounds__(256) k_pack_c(const double *__restrict__ CL,
     pack_tile(CL, CR, Cc, nao, nd, r, blockIdx.x);
 }
 
-__global__ void __launch_bounds__(256) k_density(const double *__restrict__ CL,
-                                                 const double *__restrict__ CR, double *__restrict__ D,
-                                                 int nao, int r)
-{
-    __shared__ double lds[TileDensity::LDS_DOUBLES];
-    density_tile(CL, CR, D, nao, r, blockIdx.x, lds);
-}
-
-__global__ void __launch_bounds__(256) k_project(const double *__restrict__ B,
-                                                 const double *__restrict__ A, double *__restrict__ part,
-                                                 int naux, int nd, i64 npos, int plen)
-{
-    __shared__ double lds[TileProject::LDS_DOUBLES];
-    project_tile(B, A, part, naux, nd, npos, plen, blockIdx.x, lds);
-}
-
-__global__ void __launch_bounds__(256) k_project16(const double *__restrict__ B,
-                                                   const double *__restrict__ A,
-                                                   double *__restrict__ part, int naux, int nd,
-                                                   i64 npos, int plen)
-{
-    __shared__ double lds[TileProject16::LDS_DOUBLES];
-    project16_tile(B, A, part, naux, nd, npos, plen, blockIdx.x, lds);
-}
-
-__global__ void __launch_bounds__(256) k_project_reduce(const double *__restrict__ part,
-                                                        double *__restrict__ g, int naux, int nd,
-                                                        int npb)
-{
-    reduce_tile(part, g, naux, nd, npb, blockIdx.x);
-}
-
-__global__ void __launch_bounds__(256) k_coulomb(const double *__restrict__ B,
-                                                 const double *__restrict__ g, double *__restrict__ J,
-                                                 int naux, int nd, i64 npos, double scale,
-                                                 int accumulate)
-{
-    coulomb_tile(B, g, J, naux, nd, npos, blockIdx.x, scale, accumulate);
-}
-
 __global__ void __launch_bounds__(256, 3) k_half_transform(const double *__restrict__ B,
                                                            const double *__restrict__ Cc,
                                                            double *__restrict__ Xw,
@@ -153,32 +113,6 @@ __global__ void __launch_bounds__(256, 3) k_half_transform_packed(const double *
     __shared__ double lds[TileHalf::LDS_DOUBLES];
     const int n = ht_tiles_cols(nao, ncol, nq);
     ht_tile<true>(B, Cc, Xw, Yw, nao, nd, r, q0, ldw, xcd_swizzle(blockIdx.x, n), lds, ncol);
-}
-
-// S_k packed from D_k: S[m <= n] = D[m][n] + D[n][m] (m < n), D[m][m], so
-// that <B^Q, D_k> = sum over the packed positions of B^Q S_k.  Block (k, m).
-__global__ void __launch_bounds__(256) k_sym_pack(const double *__restrict__ D,
-                                                  double *__restrict__ S, int nao)
-{
-    const int k = blockIdx.x, m = blockIdx.y;
-    const double *Dk = D + (i64)k * nao * nao;
-    double *Sk = S + (i64)k * pk_size(nao) + pk_row(m, nao) - m;
-    for (int n = m + threadIdx.x; n < nao; n += 256)
-        Sk[n] = n == m ? Dk[(i64)m * nao + m] : Dk[(i64)m * nao + n] + Dk[(i64)n * nao + m];
-}
-
-// out[k][m][n] (+)= scale * P[k][(m, n)] for packed symmetric P.  Block (k, m).
-__global__ void __launch_bounds__(256) k_unpack_sym(const double *__restrict__ P,
-                                                    double *__restrict__ out, int nao, double scale,
-                                                    int accumulate)
-{
-    const int k = blockIdx.x, m = blockIdx.y;
-    const double *Pk = P + (i64)k * pk_size(nao);
-    double *o = out + ((i64)k * nao + m) * nao;
-    for (int n = threadIdx.x; n < nao; n += 256) {
-        const double v = scale * Pk[pk_index(m, n, nao)];
-        o[n] = accumulate ? o[n] + v : v;
-    }
 }
 
 // The exchange product on the 16 x 16 x 4 engine, tile shape by pick_shape:
@@ -285,88 +219,6 @@ hipError_t launch_pack_c(const double *CL, const double *CR, double *Cc, int nao
     return hipGetLastError();
 }
 
-hipError_t launch_density(const double *CL, const double *CR, double *D, int nao, int nd, int r,
-                          hipStream_t s)
-{
-    {
-        ProfScope ps_("density", s);
-        hipLaunchKernelGGL(k_density, dim3(density_tiles(nao, nd)), dim3(256), 0, s, CL, CR, D, nao, r);
-    }
-    return hipGetLastError();
-}
-
-int project_nblocks(i64 npos, int naux, int nd, int *plen)
-{
-    // Aim for >= 2048 workgroups in total; position blocks are multiples of 16.
-    int nqt = cdiv(naux, kProjRows), nkg = cdiv(nd, 8);
-    i64 want = 2048 / (nqt * nkg);
-    if (want < 1)
-        want = 1;
-    i64 len = (npos + want - 1) / want;
-    len = ((len + 15) / 16) * 16;
-    if (len < 256)
-        len = 256;
-    *plen = (int)len;
-    return cdiv(npos, len);
-}
-
-hipError_t launch_project(const double *B, const double *A, double *part, double *g, int naux,
-                          int nd, i64 npos, hipStream_t s)
-{
-    int plen;
-    int npb = project_nblocks(npos, naux, nd, &plen);
-    {
-        ProfScope ps_("project", s);
-        hipLaunchKernelGGL(k_project, dim3(project_tiles(naux, nd, npb)), dim3(256), 0, s, B, A, part,
-                           naux, nd, npos, plen);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    {
-        ProfScope ps_("project_reduce", s);
-        hipLaunchKernelGGL(k_project_reduce, dim3(reduce_tiles(naux, nd)), dim3(256), 0, s, part, g,
-                           naux, nd, npb);
-    }
-    return hipGetLastError();
-}
-
-int project16_nblocks(i64 npos, int naux, int *plen) { return project_nblocks(npos, naux, 8, plen); }
-
-hipError_t launch_project16(const double *B, const double *A, double *part, double *g, int naux,
-                            int nd, i64 npos, hipStream_t s)
-{
-    if (nd <= 8 || nd > 16)
-        return hipErrorInvalidValue;
-    int plen;
-    const int npb = project16_nblocks(npos, naux, &plen);
-    {
-        ProfScope ps_("project16", s);
-        hipLaunchKernelGGL(k_project16, dim3(project16_tiles(naux, npb)), dim3(256), 0, s, B, A,
-                           part, naux, nd, npos, plen);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    {
-        ProfScope ps_("project_reduce", s);
-        hipLaunchKernelGGL(k_project_reduce, dim3(reduce_tiles(naux, nd)), dim3(256), 0, s, part, g,
-                           naux, nd, npb);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_coulomb(const double *B, const double *g, double *J, int naux, int nd, i64 npos,
-                          hipStream_t s, double scale, int accumulate)
-{
-    {
-        ProfScope ps_("coulomb", s);
-        hipLaunchKernelGGL(k_coulomb, dim3(coulomb_tiles(nd, npos)), dim3(256), 0, s, B, g, J, naux, nd,
-                           npos, scale, accumulate);
-    }
-    return hipGetLastError();
-}
-
 // Dynamic LDS above 64 KB needs a per-kernel attribute, set once per
 // (kernel, device).
 hipError_t set_dynamic_lds(const void *fn, int bytes)
@@ -462,26 +314,6 @@ hipError_t launch_half_transform(const double *B, const double *Cc, double *Xw, 
         ProfScope ps_(prof, s);
         hipLaunchKernelGGL(k_half_transform, dim3(ht_tiles_cols(nao, ncol, nq)), dim3(256), 0, s, B, Cc,
                            Xw, Yw, nao, nd, r, q0, nq, ldw, ncol);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_sym_pack(const double *D, double *S, int nao, int nd, hipStream_t s)
-{
-    {
-        ProfScope ps_("sym_pack", s);
-        hipLaunchKernelGGL(k_sym_pack, dim3(nd, nao), dim3(256), 0, s, D, S, nao);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_unpack_sym(const double *P, double *out, int nao, int nd, double scale,
-                             int accumulate, hipStream_t s)
-{
-    {
-        ProfScope ps_("unpack_sym", s);
-        hipLaunchKernelGGL(k_unpack_sym, dim3(nd, nao), dim3(256), 0, s, P, out, nao, scale,
-                           accumulate);
     }
     return hipGetLastError();
 }

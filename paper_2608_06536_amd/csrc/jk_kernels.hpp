@@ -37,31 +37,20 @@ int pick_split_slots(int tiles, int smax, int slots);
 
 hipError_t launch_pack_c(const double *CL, const double *CR, double *Cc, int nao, int nd, int r,
                          hipStream_t s);
-hipError_t launch_density(const double *CL, const double *CR, double *D, int nao, int nd, int r,
-                          hipStream_t s);
-int project_nblocks(int64_t npos, int naux, int nd, int *plen);
-// 9 to 16 matrices A_k (contiguous, npos apart) projected in one pass over B
-// into g[k][Q]; part holds project16_nblocks x naux x 16 doubles.
-int project16_nblocks(int64_t npos, int naux, int *plen);
-hipError_t launch_project16(const double *B, const double *A, double *part, double *g, int naux,
-                            int nd, int64_t npos, hipStream_t s);
-hipError_t launch_project(const double *B, const double *A, double *part, double *g, int naux,
-                          int nd, int64_t npos, hipStream_t s);
-// J (+)= scale * sum_Q g B^Q; accumulate adds to what J holds.
-hipError_t launch_coulomb(const double *B, const double *g, double *J, int naux, int nd,
-                          int64_t npos, hipStream_t s, double scale = 1.0, int accumulate = 0);
-// Full-square symmetric slabs read on their upper triangles (half the bytes
-// of B).  fold_upper: A_k[m][n] += A_k[n][m], A_k[n][m] = 0 for n > m, in
-// place (nmat matrices).  project_upper: g[k][Q] = <B^Q, A_k> from the folded
-// A; part holds project_upper_blocks pairs x naux x (8 groups, or 16) doubles;
-// sixteen: 9 to 16 matrices in one pass (else groups of 8).
-hipError_t launch_fold_upper(double *A, int nao, int nmat, hipStream_t s);
-int project_upper_blocks(int nao, int naux, int nkg, int *G);
-hipError_t launch_project_upper(const double *B, const double *S, double *part, double *g, int nao,
-                                int naux, int nd, hipStream_t s, bool sixteen = false);
-// J (bit-identical to launch_coulomb's for symmetric slabs).
-hipError_t launch_coulomb_upper(const double *B, const double *g, double *J, int nao, int naux,
-                                int nd, hipStream_t s, double scale = 1.0, int accumulate = 0);
+// gamma and J on the upper triangles of the slabs (coulomb_upper.hpp), full
+// squares or packed slabs.  S_k: matrices folded onto the packed positions
+// (A[m][n] + A[n][m] above the diagonal), from the factors or from given
+// matrices (nmat of them).  project: g[k][Q] = sum_p B^Q[p] S_k[p], all nd
+// matrices; part holds project_part_doubles doubles.  coulomb: J (+)= scale *
+// sum_Q g B^Q in full; accumulate adds to what J holds.
+hipError_t launch_fold_density(const double *CL, const double *CR, double *S, int nao, int nd, int r,
+                               hipStream_t s);
+hipError_t launch_sym_pack(const double *A, double *S, int nao, int nmat, hipStream_t s);
+size_t project_part_doubles(int nao, int naux, int nd);
+hipError_t launch_project(const double *B, const double *S, double *part, double *g, int nao, int naux,
+                          int nd, int packed, hipStream_t s);
+hipError_t launch_coulomb(const double *B, const double *g, double *J, int nao, int naux, int nd,
+                          int packed, hipStream_t s, double scale = 1.0, int accumulate = 0);
 // packed: B holds packed upper-triangle slabs (nao (nao + 1) / 2 doubles).
 // tile (full slabs only; jk_tune.h): 0 = 128 x 64 workgroup tiles of four
 // waves, 1 = 64 x 64, 2 = 128 x 64 of eight waves (4x4x4 engine); 3 = 128 x 128,
@@ -71,11 +60,6 @@ hipError_t launch_half_transform(const double *B, const double *Cc, double *Xw, 
                                  int nao, int nd, int r, int q0, int nq, int ldw, hipStream_t s,
                                  int ncol = -1, int packed = 0, int tile = 0,
                                  const char *prof = "half_transform");
-// S_k = D_k + D_k^T off the diagonal, D_k on it, as packed upper triangles.
-hipError_t launch_sym_pack(const double *D, double *S, int nao, int nd, hipStream_t s);
-// out_k (+)= scale * P_k, P_k a packed symmetric matrix, written in full.
-hipError_t launch_unpack_sym(const double *P, double *out, int nao, int nd, double scale,
-                             int accumulate, hipStream_t s);
 // Lower triangle of every K_k from its upper triangle.
 hipError_t launch_mirror_upper(double *K, int nao, int nd, hipStream_t s);
 // Tile shape (Shape16) and splits of the exchange of one chunk; the partial
@@ -108,7 +92,9 @@ hipError_t launch_vjp_stage_c(const double *B, const double *L, double *dCp, int
                               int q0, int nq, int nsplit, int accumulate, hipStream_t s);
 hipError_t launch_vjp_dc_finish(const double *dCp, double *dCL, double *dCR, int nao, int nd,
                                 int r, int nsplit, hipStream_t s);
-hipError_t launch_vjp_e_matrix(const double *D, double *E, int nao, int nd, hipStream_t s);
+// E_k = D_k - 2 D_k^T from the factors
+hipError_t launch_vjp_e_matrix(const double *CL, const double *CR, double *E, int nao, int nd, int r,
+                               hipStream_t s);
 hipError_t launch_vjp_stage_d(const double *L, const double *Cc, double *dB, int nao, int R,
                               int q0, int nq, hipStream_t s);
 // Packed B (jk.h JK_B_PACKED): full squares of slabs q0 .. q0 + nq - 1 into
@@ -118,9 +104,10 @@ hipError_t launch_unpack_slabs(const double *Bp, double *out, int nao, int q0, i
                                hipStream_t s);
 hipError_t launch_vjp_stage_d_packed(const double *L, const double *Cc, double *dB, int nao, int R,
                                      int q0, int nq, hipStream_t s);
+// dB^Q += sum_k gam W + esign om E
 hipError_t launch_vjp_db_affine(const double *gam, const double *om, const double *W,
-                                const double *E, double *dB, int nd, int naux, i64 npos, int q0,
-                                int nq, hipStream_t s);
+                                const double *E, double esign, double *dB, int nd, int naux,
+                                i64 npos, int q0, int nq, hipStream_t s);
 
 // mixed precision (jk_mixed.hip)
 int mixed_nslice();

@@ -8,10 +8,8 @@
 //
 // Phases (Sec. 2.3, Eq. (4), half-transform form K = B_V^T B_U):
 //   pack          Cc[n][c]       = [C_L | C_R] as one nao x 2R matrix
-//   density       D_k            = C_Lk C_Rk^T
-//   project       part[p][Q][k]  = sum over a block of positions of B^Q . A_k
-//   reduce        g[k][Q]        = sum of the partials in fixed order
-//   coulomb       J_k            = sum_Q gamma_kQ B^Q
+//   gamma, J      coulomb_upper.hpp
+//   reduce        g[k][Q]        = sum of gamma's partials in fixed order
 //   half-transform X^Q, Y^Q      = B^Q [C_L | C_R]            (per Q-chunk)
 //   exchange      K_k           += sum_{Q in chunk} X^Q_k (Y^Q_k)^T
 //   sum splits    K              = sum of the split partials in fixed order
@@ -23,19 +21,15 @@
 
 namespace jk {
 
-// Tile shapes (chosen by measurement on MI355X): the half-transform uses
-// 128 x 64 workgroup tiles of four 64 x 32 wave tiles (two workgroups per
-// CU); the exchange product 128 x 64 tiles of eight 64 x 16 wave tiles (four
-// waves per SIMD); the projection 256 Q-rows x 8 densities; the density
-// 64 x 64.  Element-wise phases take 1024 elements per tile.
+// Tile shapes of the 4x4x4 engine: the half-transform uses 128 x 64 workgroup
+// tiles of four 64 x 32 wave tiles (two workgroups per CU); the exchange
+// product 128 x 64 tiles of eight 64 x 16 wave tiles (four waves per SIMD);
+// the density 64 x 64.  Element-wise phases take 1024 elements per tile.
 constexpr int kHtM = 128, kHtN = 64;
 constexpr int kExM = 128, kExN = 64;
-constexpr int kProjRows = 256;
 constexpr int kElemTile = 1024;
 typedef Tile<kHtM, kHtN, 64, 32, 16> TileHalf;
 typedef Tile<kExM, kExN, 64, 16, 16> TileExch;
-typedef Tile<kProjRows, 8, 64, 8, 16> TileProject;
-typedef Tile<kProjRows, 16, 64, 16, 16> TileProject16;
 typedef Tile<64, 64, 32, 32, 16> TileDensity;
 // The half-transform's second tile shape (a plan choice, jk_tune.h): 64 x 64,
 // four workgroups per CU; wins at small nao where 128-row tiles waste rows.
@@ -93,17 +87,7 @@ __host__ __device__ inline int pack_tiles(int nao, int nd, int r)
 {
     return cdiv_i((i64)nao * 2 * nd * r, kElemTile);
 }
-__host__ __device__ inline int density_tiles(int nao, int nd)
-{
-    const int nt = cdiv_i(nao, 64);
-    return nd * nt * nt;
-}
-__host__ __device__ inline int project_tiles(int naux, int nd, int npb)
-{
-    return cdiv_i(naux, kProjRows) * cdiv_i(nd, 8) * npb;
-}
-__host__ __device__ inline int reduce_tiles(int naux, int nd) { return cdiv_i((i64)naux * (cdiv_i(nd, 8) * 8), 64); }
-__host__ __device__ inline int coulomb_tiles(int nd, i64 npos) { return cdiv_i(nd, 8) * cdiv_i(npos, 512); }
+__host__ __device__ inline int reduce_tiles(int naux, int ndp) { return cdiv_i((i64)naux * ndp, 64); }
 __host__ __device__ inline int ht_tiles(int nao, int nd, int r, int nq)
 {
     return nq * cdiv_i(nao, kHtM) * cdiv_i(2 * (i64)nd * r, kHtN);
@@ -207,89 +191,15 @@ __device__ inline void pack_tile(const double *__restrict__ CL, const double *__
     }
 }
 
-// ------------------------------------------------------------------ density
-// D_k[m][n] = sum_i CL[k][m][i] CR[k][n][i]
-__device__ inline void density_tile(const double *__restrict__ CL, const double *__restrict__ CR,
-                                    double *__restrict__ D, int nao, int r, int tile, double *lds)
-{
-    typedef TileDensity TL;
-    const int nt = cdiv_i(nao, 64);
-    const int k = tile / (nt * nt), rem = tile % (nt * nt);
-    const int mb = rem / nt, nb = rem % nt;
-    OpKC a{CL + (i64)k * nao * r, r, nao, r};
-    OpKC b{CR + (i64)k * nao * r, r, nao, r};
-    Acc<TL> acc;
-    acc.zero();
-    tile_gemm<TL>(a, b, mb * 64, nb * 64, 0, r, lds, acc);
-    double *Dk = D + (i64)k * nao * nao;
-    tile_foreach(acc, mb * 64, nb * 64, [&](int m, int n, double v) {
-        if (m < nao && n < nao)
-            Dk[(i64)m * nao + n] = v;
-    });
-}
-
-// ------------------------------------------------------------------ project
-// part[pb][Q][kg*8 + kk] = sum_{p in block pb} B[Q][p] * A[kg*8 + kk][p]:
-// a product with M = naux, N = nd (groups of 8), inner = nao^2 cut into
-// blocks of plen positions.
-__device__ inline void project_tile(const double *__restrict__ B, const double *__restrict__ A,
-                                    double *__restrict__ part, int naux, int nd, i64 npos, int plen,
-                                    int tile, double *lds)
-{
-    typedef TileProject TL;
-    const int nqt = cdiv_i(naux, kProjRows), nkg = cdiv_i(nd, 8);
-    const int pb = tile / (nqt * nkg), rem = tile % (nqt * nkg);
-    const int kg = rem / nqt, qt = rem % nqt;
-    const i64 p0 = (i64)pb * plen;
-    const int len = (int)((npos - p0) < plen ? (npos - p0) : plen);
-    const int ndg = (nd - kg * 8) < 8 ? (nd - kg * 8) : 8;
-    OpKC a{B + p0, npos, naux, len};
-    OpKC b{A + (i64)kg * 8 * npos + p0, npos, ndg, len};
-    Acc<TL> acc;
-    acc.zero();
-    tile_gemm<TL>(a, b, qt * kProjRows, 0, 0, len, lds, acc);
-    const int ndp = nkg * 8;
-    double *out = part + (i64)pb * naux * ndp;
-    tile_foreach(acc, qt * kProjRows, 0, [&](int q, int kk, double v) {
-        if (q < naux && kk < 8)
-            out[(i64)q * ndp + kg * 8 + kk] = v;
-    });
-}
-
-// The same product for 9 to 16 matrices A_k in one group (two sets of
-// projections paired in one pass over B): part[pb][Q][k], k < 16, one tile per
-// (position block, Q-tile).
-__host__ __device__ inline int project16_tiles(int naux, int npb) { return cdiv_i(naux, kProjRows) * npb; }
-__device__ inline void project16_tile(const double *__restrict__ B, const double *__restrict__ A,
-                                      double *__restrict__ part, int naux, int nd, i64 npos,
-                                      int plen, int tile, double *lds)
-{
-    typedef TileProject16 TL;
-    const int nqt = cdiv_i(naux, kProjRows);
-    const int pb = tile / nqt, qt = tile % nqt;
-    const i64 p0 = (i64)pb * plen;
-    const int len = (int)((npos - p0) < plen ? (npos - p0) : plen);
-    OpKC a{B + p0, npos, naux, len};
-    OpKC b{A + p0, npos, nd, len};
-    Acc<TL> acc;
-    acc.zero();
-    tile_gemm<TL>(a, b, qt * kProjRows, 0, 0, len, lds, acc);
-    double *out = part + (i64)pb * naux * 16;
-    tile_foreach(acc, qt * kProjRows, 0, [&](int q, int kk, double v) {
-        if (q < naux && kk < 16)
-            out[(i64)q * 16 + kk] = v;
-    });
-}
-
+// ------------------------------------------------------------------ reduce
 // g[k][Q] = sum_{pb} part[pb][Q][k] in a fixed order.  A tile covers 64
 // consecutive entries (Q, k) of one partial block; wave w of the four sums
 // the blocks pb = w, w + 4, ... (coalesced 512-byte reads), and the four wave
 // sums are added in wave order.
 __device__ inline void reduce_tile(const double *__restrict__ part, double *__restrict__ g, int naux,
-                                   int nd, int npb, int tile)
+                                   int nd, int ndp, int npb, int tile)
 {
     __shared__ double red[4][64];
-    const int ndp = cdiv_i(nd, 8) * 8;
     const i64 total = (i64)naux * ndp;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const i64 e = (i64)tile * 64 + lane;
@@ -315,72 +225,6 @@ __device__ inline void reduce_tile(const double *__restrict__ part, double *__re
         if (k < nd)
             g[(i64)k * naux + q] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
     }
-}
-
-// ------------------------------------------------------------------ coulomb
-// J[k][p] = sum_Q g[k][Q] B[Q][p] for the 8 densities of group kg and the 512
-// positions of block pb: thread t takes positions pb*512 + t and + 256 (each
-// load instruction reads 512 contiguous bytes), Q unrolled by 8, so 16 loads
-// per thread are in flight.  The inner loop has no branches: positions past
-// the end read a valid clamped address and densities past nd repeat the last
-// one; neither is stored.  HBM-bound stream over B.
-// J_k (+)= scale * sum_Q g[k][Q] B^Q (accumulate: add to what J holds).
-__device__ inline void coulomb_tile(const double *__restrict__ B, const double *__restrict__ g,
-                                    double *__restrict__ J, int naux, int nd, i64 npos, int tile,
-                                    double scale = 1.0, int accumulate = 0)
-{
-    const int npb = cdiv_i(npos, 512);
-    const int kg = tile / npb, pb = tile % npb;
-    const int k0 = kg * 8;
-    const int nk = (nd - k0) < 8 ? (nd - k0) : 8;
-    const i64 p0 = (i64)pb * 512 + threadIdx.x, p1 = p0 + 256;
-    const double *b0 = B + (p0 < npos ? p0 : npos - 1);
-    const double *b1 = B + (p1 < npos ? p1 : npos - 1);
-    const double *gk[8];
-#pragma unroll
-    for (int k = 0; k < 8; k++)
-        gk[k] = g + (i64)(k0 + (k < nk ? k : nk - 1)) * naux;
-    double a0[8], a1[8];
-#pragma unroll
-    for (int k = 0; k < 8; k++) {
-        a0[k] = 0.0;
-        a1[k] = 0.0;
-    }
-    int q = 0;
-    for (; q + 8 <= naux; q += 8) {
-        double v0[8], v1[8];
-#pragma unroll
-        for (int u = 0; u < 8; u++) {
-            v0[u] = __builtin_nontemporal_load(b0 + (i64)(q + u) * npos);
-            v1[u] = __builtin_nontemporal_load(b1 + (i64)(q + u) * npos);
-        }
-#pragma unroll
-        for (int u = 0; u < 8; u++)
-#pragma unroll
-            for (int k = 0; k < 8; k++) {
-                const double gv = gk[k][q + u];
-                a0[k] = fma(gv, v0[u], a0[k]);
-                a1[k] = fma(gv, v1[u], a1[k]);
-            }
-    }
-    for (; q < naux; q++) {
-        const double v0 = b0[(i64)q * npos], v1 = b1[(i64)q * npos];
-#pragma unroll
-        for (int k = 0; k < 8; k++) {
-            const double gv = gk[k][q];
-            a0[k] = fma(gv, v0, a0[k]);
-            a1[k] = fma(gv, v1, a1[k]);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < 8; k++)
-        if (k < nk) {
-            double *Jk = J + (i64)(k0 + k) * npos;
-            if (p0 < npos)
-                Jk[p0] = accumulate ? Jk[p0] + scale * a0[k] : scale * a0[k];
-            if (p1 < npos)
-                Jk[p1] = accumulate ? Jk[p1] + scale * a1[k] : scale * a1[k];
-        }
 }
 
 // ------------------------------------------------------------------ half-transform

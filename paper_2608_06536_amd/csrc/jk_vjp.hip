@@ -24,6 +24,7 @@
 #include "f64_core.hpp"
 #include "f64_mfma16.hpp"
 #include "jk_kernels.hpp"
+#include "jk_tiles.hpp"
 
 namespace jk {
 
@@ -172,16 +173,34 @@ __global__ void __launch_bounds__(256) k_vjp_dc_finish(const double *__restrict_
     }
 }
 
-// E[k][a][b] = D[k][a][b] - 2 D[k][b][a]
-__global__ void __launch_bounds__(256) k_vjp_e_matrix(const double *__restrict__ D,
-                                                      double *__restrict__ E, int nao, int nd)
+// E[k][a][b] = D_k[a][b] - 2 D_k[b][a], D_k = CL_k CR_k^T: two products per
+// 64 x 64 tile, sum_i CL[a][i] CR[b][i] - 2 sum_i CR[a][i] CL[b][i].
+__global__ void __launch_bounds__(256) k_vjp_e_matrix(const double *__restrict__ CL,
+                                                      const double *__restrict__ CR,
+                                                      double *__restrict__ E, int nao, int r)
 {
-    const i64 n2 = (i64)nao * nao, total = n2 * nd;
-    for (i64 e = (i64)blockIdx.x * 256 + threadIdx.x; e < total; e += (i64)gridDim.x * 256) {
-        const i64 k = e / n2, ab = e % n2;
-        const int a = (int)(ab / nao), b = (int)(ab % nao);
-        E[e] = D[e] - 2.0 * D[k * n2 + (i64)b * nao + a];
-    }
+    typedef TileDensity TL;
+    __shared__ double lds[TL::LDS_DOUBLES];
+    const int nt = cdiv_i(nao, 64);
+    const int k = blockIdx.x / (nt * nt), rem = blockIdx.x % (nt * nt);
+    const int mb = rem / nt, nb = rem % nt;
+    OpKC l{CL + (i64)k * nao * r, r, nao, r};
+    OpKC q{CR + (i64)k * nao * r, r, nao, r};
+    Acc<TL> d, dt;
+    d.zero();
+    dt.zero();
+    tile_gemm<TL>(l, q, mb * 64, nb * 64, 0, r, lds, d);
+    tile_gemm<TL>(q, l, mb * 64, nb * 64, 0, r, lds, dt);
+#pragma unroll
+    for (int i = 0; i < TL::MA; i++)
+#pragma unroll
+        for (int j = 0; j < TL::NB; j++)
+            d.c[i][j] -= 2.0 * dt.c[i][j];
+    double *Ek = E + (i64)k * nao * nao;
+    tile_foreach(d, mb * 64, nb * 64, [&](int m, int n, double v) {
+        if (m < nao && n < nao)
+            Ek[(i64)m * nao + n] = v;
+    });
 }
 
 // ------------------------------------------------------------------ stage D
@@ -330,7 +349,7 @@ __global__ void __launch_bounds__(256, 2) k_vjp_stage_d_packed(const double *__r
     });
 }
 
-// dB[Q][p] += sum_k gamma[k][Q] W[k][p] + omega[k][Q] E[k][p] for Q in
+// dB[Q][p] += sum_k gamma[k][Q] W[k][p] + esign omega[k][Q] E[k][p] for Q in
 // [q0, q0 + nq): each thread keeps the W and E values of its two positions in
 // registers across its slabs (densities in groups of 8) and updates four
 // slabs at a time, so eight loads are in flight; blockIdx.y splits the
@@ -340,7 +359,7 @@ __global__ void __launch_bounds__(256, 2) k_vjp_stage_d_packed(const double *__r
 __global__ void __launch_bounds__(256) k_vjp_db_affine(const double *__restrict__ gam,
                                                        const double *__restrict__ om,
                                                        const double *__restrict__ W,
-                                                       const double *__restrict__ E,
+                                                       const double *__restrict__ E, double esign,
                                                        double *__restrict__ dB, int nd, int naux,
                                                        i64 npos, int q0, int nq_all, int qlen)
 {
@@ -361,9 +380,9 @@ __global__ void __launch_bounds__(256) k_vjp_db_affine(const double *__restrict_
             const int kk = k0 + (k < nk ? k : 0);
             const i64 base = (i64)kk * npos;
             w[k][0] = W[base + p0];
-            e[k][0] = E[base + p0];
+            e[k][0] = esign * E[base + p0];
             w[k][1] = W[base + p1];
-            e[k][1] = E[base + p1];
+            e[k][1] = esign * E[base + p1];
             gk[k] = gam + (i64)kk * naux;
             ok[k] = om + (i64)kk * naux;
         }
@@ -518,12 +537,13 @@ hipError_t launch_vjp_dc_finish(const double *dCp, double *dCL, double *dCR, int
     return hipGetLastError();
 }
 
-hipError_t launch_vjp_e_matrix(const double *D, double *E, int nao, int nd, hipStream_t s)
+hipError_t launch_vjp_e_matrix(const double *CL, const double *CR, double *E, int nao, int nd, int r,
+                               hipStream_t s)
 {
     {
         ProfScope ps_("vjp_e_matrix", s);
-        hipLaunchKernelGGL(k_vjp_e_matrix, dim3(grid_1d((i64)nao * nao * nd)), dim3(256), 0, s, D, E,
-                           nao, nd);
+        const int nt = cdiv(nao, 64);
+        hipLaunchKernelGGL(k_vjp_e_matrix, dim3(nd * nt * nt), dim3(256), 0, s, CL, CR, E, nao, r);
     }
     return hipGetLastError();
 }
@@ -571,8 +591,8 @@ hipError_t launch_vjp_stage_d_packed(const double *L, const double *Cc, double *
 }
 
 hipError_t launch_vjp_db_affine(const double *gam, const double *om, const double *W,
-                                const double *E, double *dB, int nd, int naux, i64 npos, int q0,
-                                int nq, hipStream_t s)
+                                const double *E, double esign, double *dB, int nd, int naux,
+                                i64 npos, int q0, int nq, hipStream_t s)
 {
     {
         ProfScope ps_("vjp_db_affine", s);
@@ -585,7 +605,7 @@ hipError_t launch_vjp_db_affine(const double *gam, const double *om, const doubl
             ny = 1;
         const int qlen = cdiv(nq, ny);
         hipLaunchKernelGGL(k_vjp_db_affine, dim3(nx, cdiv(nq, qlen)), dim3(256), 0, s, gam, om, W, E,
-                           dB, nd, naux, npos, q0, nq, qlen);
+                           esign, dB, nd, naux, npos, q0, nq, qlen);
     }
     return hipGetLastError();
 }
