@@ -223,11 +223,12 @@ VjpPlan plan_vjp(const jk_problem *p)
 struct MixPlan {
     FwdPlan f;
     int ns, mp, kp, cp, jp, nsplit;
-    int mpb;                  // rows per slab of B's planes (X/Y planes: mp)
+    i64 rows;                 // rows of a chunk's B planes (X/Y planes: mp per key)
+    int nsp;                  // partial row maxima per row of X/Y
     int cp_sym, nsplit_sym;   // X-only columns and triangle splits (C_L = C_R)
     size_t bp_bytes, xy_bytes, xyp_bytes;
     size_t o_bp[2], o_eb[2], o_xy[2], o_xyp[2], o_exy[2], o_cp, o_ec, o_kp, total;
-    size_t o_pm[2];           // the half-transform's row maxima per tile (single builds)
+    size_t o_pm[2], o_mx[2];  // the half-transform's row maxima per tile, and their maxima
 };
 
 inline i64 pad_to(i64 x, i64 m) { return ((x + m - 1) / m) * m; }
@@ -239,15 +240,16 @@ MixPlan plan_mixed(const jk_problem *p, size_t budget = kChunkBudget)
     const i64 nao = p->nao, nd = p->ndens, r = p->rank, R = nd * r;
     x.ns = jk::mixed_nslice();
     x.mp = (int)pad_to(nao, jk::mixed_row_pad());
-    x.mpb = (int)pad_to(nao, jk::mixed_b_row_pad());
+    x.rows = jk::mixed_b_rows((i64)x.f.qc * nao);
     x.kp = (int)pad_to(nao, jk::mixed_k_pad());
-    x.cp = (int)pad_to(2 * R, jk::mixed_row_pad());
+    x.cp = (int)pad_to(2 * R, jk::mixed_col_pad());
     x.jp = (int)pad_to((i64)x.f.qc * r, jk::mixed_k_pad());
     x.nsplit = jk::ex_mixed_nsplit(x.mp, (int)nd, x.jp / jk::mixed_k_block());
-    x.cp_sym = (int)pad_to(R, jk::mixed_row_pad());
+    x.cp_sym = (int)pad_to(R, jk::mixed_col_pad());
     x.nsplit_sym = jk::ex_mixed_nsplit(x.mp, (int)nd, x.jp / jk::mixed_k_block(), 1);
     const int nsmax = x.nsplit > x.nsplit_sym ? x.nsplit : x.nsplit_sym;
-    x.bp_bytes = (size_t)x.ns * x.f.qc * x.mpb * x.kp;
+    x.bp_bytes = (size_t)x.ns * x.rows * x.kp;
+    x.nsp = jk::xy_rowmax_splits((int)nao, (int)(2 * nd), x.f.qc);
     x.xy_bytes = sizeof(double) * (size_t)x.f.qc * nao * 2 * R;
     x.xyp_bytes = (size_t)x.ns * 2 * nd * x.mp * x.jp;
     Carve c;
@@ -258,7 +260,7 @@ MixPlan plan_mixed(const jk_problem *p, size_t budget = kChunkBudget)
     x.o_xy[1] = c.take(x.xy_bytes);
     for (int b = 0; b < 2; b++) {
         x.o_bp[b] = c.take(x.bp_bytes);
-        x.o_eb[b] = c.take(sizeof(int) * (size_t)x.f.qc * x.mpb);
+        x.o_eb[b] = c.take(sizeof(int) * (size_t)x.rows);
         x.o_xyp[b] = c.take(x.xyp_bytes);
         x.o_exy[b] = c.take(sizeof(int) * (size_t)2 * nd * x.mp);
     }
@@ -266,9 +268,11 @@ MixPlan plan_mixed(const jk_problem *p, size_t budget = kChunkBudget)
     x.o_ec = c.take(sizeof(int) * (size_t)x.cp);
     x.o_kp = c.take(sizeof(double) * (size_t)nsmax * nd * nao * nao);
     // sized for both sides (the X-only case has fewer column tiles and keys)
-    const size_t pm = jk::xy_rowmax_pm_doubles(x.f.qc, x.mpb, x.cp, (int)r, (int)(2 * nd));
-    for (int b = 0; b < 2; b++)
-        x.o_pm[b] = c.take(sizeof(double) * pm);
+    const size_t pm = jk::xy_rowmax_pm_words(x.rows, x.cp, (int)r, (int)(2 * nd));
+    for (int b = 0; b < 2; b++) {
+        x.o_pm[b] = c.take(sizeof(uint32_t) * pm);
+        x.o_mx[b] = c.take(sizeof(uint32_t) * (size_t)x.nsp * 2 * nd * x.mp);
+    }
     x.total = c.off;
     return x;
 }
@@ -515,9 +519,10 @@ jk_status vjp_fp64(const jk_problem *p, const double *B, const double *CL, const
 }
 
 // Digit planes of a whole B made once by jk_slice_b (jk.h): row exponents of
-// the naux * mp plane rows, then the planes, K-blocked over all slabs.
+// the naux * nao plane rows, then the planes, K-blocked over all slabs.
 struct SliceLayout {
-    int mp, kp;
+    int kp;
+    i64 rows;
     size_t o_exp, o_planes, total;
     i64 kbstride, pstride;
 };
@@ -525,13 +530,13 @@ struct SliceLayout {
 SliceLayout slice_layout(const jk_problem *p)
 {
     SliceLayout L;
-    L.mp = (int)pad_to(p->nao, jk::mixed_b_row_pad());
+    L.rows = jk::mixed_b_rows((i64)p->naux * p->nao);
     L.kp = (int)pad_to(p->nao, jk::mixed_k_pad());
     const int KB = jk::mixed_k_block();
-    L.kbstride = (i64)p->naux * L.mp * KB;
+    L.kbstride = L.rows * KB;
     L.pstride = L.kbstride * (L.kp / KB);
     Carve c;
-    L.o_exp = c.take(sizeof(int) * (size_t)p->naux * L.mp);
+    L.o_exp = c.take(sizeof(int) * (size_t)L.rows);
     L.o_planes = c.take((size_t)jk::mixed_nslice() * L.pstride);
     L.total = c.off;
     return L;
@@ -596,7 +601,7 @@ jk_status build_mixed(const jk_problem *p, const double *B, const KSeg *seg, int
     double *Kp = nsplit > 1 ? (double *)(ws + x.o_kp) : K;
     const int KB = jk::mixed_k_block();
     // K-blocked plane strides (slice_core.hpp): kbstride = rows * 32 bytes
-    const i64 bkb = pre ? SL.kbstride : (i64)f.qc * x.mpb * KB;
+    const i64 bkb = pre ? SL.kbstride : x.rows * KB;
     const i64 bps = pre ? SL.pstride : bkb * (x.kp / KB);
     const i64 ckb = (i64)x.cp * KB, cps = ckb * (x.kp / KB);
     const i64 xkb = (i64)2 * nd * x.mp * KB, xps = xkb * (x.jp / KB);
@@ -604,16 +609,17 @@ jk_status build_mixed(const jk_problem *p, const double *B, const KSeg *seg, int
     auto nq_of = [&](int c) { return chunks[c].nq; };
     auto nkb_of = [&](int c) { return (int)(pad_to((i64)nq_of(c) * r, jk::mixed_k_pad()) / KB); };
     auto Bp = [&](int c) {
-        return pre ? (int8_t *)(pre + SL.o_planes) + (i64)chunks[c].q0 * x.mpb * KB
+        return pre ? (int8_t *)(pre + SL.o_planes) + (i64)chunks[c].q0 * nao * KB
                    : (int8_t *)(ws + x.o_bp[c & 1]);
     };
     auto eB = [&](int c) {
-        return pre ? (int *)(pre + SL.o_exp) + (i64)chunks[c].q0 * x.mpb : (int *)(ws + x.o_eb[c & 1]);
+        return pre ? (int *)(pre + SL.o_exp) + (i64)chunks[c].q0 * nao : (int *)(ws + x.o_eb[c & 1]);
     };
     auto XY = [&](int c) { return (double *)(ws + x.o_xy[c & 1]); };
     auto XYp = [&](int c) { return (int8_t *)(ws + x.o_xyp[c & 1]); };
     auto eXY = [&](int c) { return (int *)(ws + x.o_exy[c & 1]); };
-    auto PM = [&](int c) { return (double *)(ws + x.o_pm[c & 1]); };
+    auto PM = [&](int c) { return (uint32_t *)(ws + x.o_pm[c & 1]); };
+    auto MX = [&](int c) { return (uint32_t *)(ws + x.o_mx[c & 1]); };
 
     // Two streams.  Main stream s: the MFMA-bound products, ht(c + 1) then
     // ex(c).  Auxiliary stream a: the HBM-bound slicing, slice_b(c + 2), then
@@ -634,18 +640,18 @@ jk_status build_mixed(const jk_problem *p, const double *B, const KSeg *seg, int
             return JK_OK;
         }
         if (f.packed)
-            JK_TRY(jk::launch_slice_b_packed(chunks[c].B, f.slab, nq_of(c), nao, x.mpb, x.kp / KB,
+            JK_TRY(jk::launch_slice_b_packed(chunks[c].B, f.slab, nq_of(c), nao, nao, x.kp / KB,
                                              Bp(c), bps, bkb, eB(c), a));
         else
-            JK_TRY(jk::launch_slice_b(chunks[c].B, npos, nao, nq_of(c), nao, nao, x.mpb,
+            JK_TRY(jk::launch_slice_b(chunks[c].B, npos, nao, nq_of(c), nao, nao, nao,
                                       x.kp / KB, Bp(c), bps, bkb, eB(c), a));
         JK_TRY(hipEventRecord(sb[c & 1], a));
         return JK_OK;
     };
     auto slice_xy = [&](int c) -> jk_status {
-        JK_TRY(jk::launch_xy_rowmax_pm(PM(c), nao, nq_of(c), nkey, r, x.mpb, x.mp, cpx, eXY(c), a));
+        JK_TRY(jk::launch_xy_rowmax_pm(PM(c), nao, nq_of(c), nkey, r, x.rows, x.mp, MX(c), x.nsp, a));
         JK_TRY(jk::launch_slice_xy(XY(c), nao, nkey, r, x.mp, nq_of(c) * r, nkb_of(c), XYp(c), xps, xkb,
-                                   eXY(c), a));
+                                   MX(c), x.nsp, eXY(c), a));
         JK_TRY(hipEventRecord(sx[c & 1], a));
         return JK_OK;
     };
@@ -654,7 +660,7 @@ jk_status build_mixed(const jk_problem *p, const double *B, const KSeg *seg, int
         if (c >= 2)
             JK_TRY(hipStreamWaitEvent(s, sx[c & 1], 0));    // XY[c] free
         JK_TRY(jk::launch_ht_mixed(Bp(c), bps, bkb, eB(c), Cp, cps, ckb, eC, XY(c), nao, ncol, nq_of(c),
-                                   x.mpb, cpx, x.kp / KB, s, PM(c), r));
+                                   cpx, x.kp / KB, PM(c), x.rows, r, s));
         JK_TRY(hipEventRecord(ht[c & 1], s));
         return JK_OK;
     };
@@ -949,17 +955,16 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
                 }
                 if (packed)      // bands of 8 rows through LDS; arg = 16 x LDS bytes + blocks
                     add(jk::kPhaseMSliceBPacked, c,
-                        [&](int g) { return nq_of(g) * ((plans[g].x.mpb + 7) / 8); }, in_step,
+                        [&](int g) { return nq_of(g) * (int)((p[g].nao + 7) / 8); }, in_step,
                         16 * (int)sizeof(double) * 8 * maxnao + nj);
                 else
                     add(jk::kPhaseMSliceB, c,
-                        [&](int g) { return (int)(((i64)nq_of(g) * plans[g].x.mpb + 3) / 4); }, in_step,
+                        [&](int g) { return (int)((nq_of(g) * p[g].nao + 3) / 4); }, in_step,
                         nj);
                 add(jk::kPhaseMHalf, c,
                     [&](int g) {
-                        return jk::mixed_ht_tiles(plans[g].x.mpb,
-                                                  plans[g].sym ? plans[g].x.cp_sym : plans[g].x.cp,
-                                                  nq_of(g));
+                        return jk::mixed_ht_tiles(nq_of(g) * (int)p[g].nao,
+                                                  plans[g].sym ? plans[g].x.cp_sym : plans[g].x.cp);
                     },
                     in_step);
                 // one tile per (64-row block, key) of X/Y
@@ -1086,11 +1091,11 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
             const MixPlan &x = plans[g].x;
             const int KB = jk::mixed_k_block();
             m.mp = x.mp;
-            m.mpb = x.mpb;
+            m.rows = (int)x.rows;
             m.kp = x.kp;
             m.cp = x.cp;
             m.cpx = m.sym ? x.cp_sym : x.cp;
-            m.bkb = (i64)x.f.qc * x.mpb * KB;
+            m.bkb = x.rows * KB;
             m.bps = m.bkb * (x.kp / KB);
             m.ckb = (i64)x.cp * KB;
             m.cps = m.ckb * (x.kp / KB);
@@ -1260,7 +1265,8 @@ jk_status build_batched(int32_t nprob, const jk_problem *p, const double *const 
             m.XY = (double *)(base + b.x.o_xy[0]);
             m.XYp = (int8_t *)(base + b.x.o_xyp[0]);
             m.eXY = (int *)(base + b.x.o_exy[0]);
-            m.pm = (double *)(base + b.x.o_pm[0]);
+            m.pm = (uint32_t *)(base + b.x.o_pm[0]);
+            m.mx = (uint32_t *)(base + b.x.o_mx[0]);
         }
     }
     if (copy_header(S.mem.data(), nprob, S.tabs, S.header_bytes, ws, s) != hipSuccess)
@@ -1379,10 +1385,10 @@ static jk_status jk_slice_b_impl(const jk_problem *p, const double *B, void *sli
     int *exps = (int *)(base + L.o_exp);
     hipStream_t s = (hipStream_t)stream;
     if (packed_b(p))
-        JK_TRY(jk::launch_slice_b_packed(B, jk::pk_size(nao), naux, nao, L.mp, L.kp / KB, planes,
+        JK_TRY(jk::launch_slice_b_packed(B, jk::pk_size(nao), naux, nao, nao, L.kp / KB, planes,
                                          L.pstride, L.kbstride, exps, s));
     else
-        JK_TRY(jk::launch_slice_b(B, (i64)nao * nao, nao, naux, nao, nao, L.mp, L.kp / KB, planes,
+        JK_TRY(jk::launch_slice_b(B, (i64)nao * nao, nao, naux, nao, nao, nao, L.kp / KB, planes,
                                   L.pstride, L.kbstride, exps, s));
     return JK_OK;
 }

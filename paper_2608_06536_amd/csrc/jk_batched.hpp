@@ -29,10 +29,10 @@ struct BMember {
     int8_t *Bp, *Cp, *XYp;
     int *eB, *eC, *eXY;
     double *XY;
-    double *pm;         // the half-transform's partial row maxima of X/Y
+    uint32_t *pm, *mx;  // the half-transform's partial row maxima of X/Y, and their maxima
     long long bkb, bps, ckb, cps, xkb, xps;
     int mp, kp, cp, cpx;    // padded rows / inner bytes; cpx: [C_L | C_R] rows the products use
-    int mpb;                // rows per slab of B's planes (the half-transform's row tiles)
+    int rows;               // rows of B's planes (slabs x nao and spare)
     // doubles per slab of B: npos for full squares, packed-triangular slabs
     // (jk.h JK_B_PACKED) otherwise
     long long bslab;

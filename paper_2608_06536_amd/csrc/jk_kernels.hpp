@@ -112,9 +112,10 @@ hipError_t launch_vjp_db_affine(const double *gam, const double *om, const doubl
 // mixed precision (jk_mixed.hip)
 int mixed_nslice();
 int mixed_row_pad();
-// rows per slab of B's digit planes (a multiple of the INT8 half-transform's
-// row tile; X/Y planes keep mixed_row_pad)
-int mixed_b_row_pad();
+// rows of B's digit planes for nrow = slabs x nao stacked rows (with the rows a
+// half-transform tile may read past them), and the padding of [C_L | C_R]'s
+i64 mixed_b_rows(i64 nrow);
+int mixed_col_pad();
 int mixed_k_pad();
 int mixed_k_block();
 hipError_t launch_slice_rows(const double *src, i64 bs, i64 rs, i64 ks, int nb, int nr, int nk,
@@ -124,27 +125,29 @@ hipError_t launch_slice_b(const double *src, i64 bs, i64 rs, int nb, int nr, int
                           int8_t *out, i64 pstride, i64 kbstride, int *exps, hipStream_t s);
 // widths 2 nd r of X/Y the mixed path takes
 int mixed_rowmax_ok(int R2);
+// XY's digit planes; the row exponents (left in exps) from nsp partial maxima.
 hipError_t launch_slice_xy(const double *XY, int nao, int nkey, int r, int mp, int nj, int nkb,
-                           int8_t *out, i64 pstride, i64 kbstride, const int *exps, hipStream_t s);
-// pm (optional): the row maxima of the chunk's X and Y per tile
-// (xy_rowmax_pm_doubles doubles), reduced into exponents by launch_xy_rowmax_pm.
+                           int8_t *out, i64 pstride, i64 kbstride, const uint32_t *mx, int nsp,
+                           int *exps, hipStream_t s);
+// pm: the row maxima of the chunk's X and Y per tile, pitch rows
+// (xy_rowmax_pm_words words), reduced to nsp partial maxima per row of the X/Y
+// planes, mx[sp nkey mpe + key mpe + m], by launch_xy_rowmax_pm.
 hipError_t launch_ht_mixed(const int8_t *Bp, i64 bpstride, i64 bkbstride, const int *eB,
                            const int8_t *Cp, i64 cpstride, i64 ckbstride, const int *eC, double *XY,
-                           int nao, int R2, int nq, int mp, int cp, int nkb, hipStream_t s,
-                           double *pm = nullptr, int r = 1);
-int xy_rowmax_slots(int r, int nkey);
-size_t xy_rowmax_pm_doubles(int nq, int mp, int cp, int r, int nkey);
-// pm rows mp per slab (the half-transform's row pitch); exps[key mpe + m]
-hipError_t launch_xy_rowmax_pm(const double *pm, int nao, int nq, int nkey, int r, int mp, int mpe,
-                               int cp, int *exps, hipStream_t s);
+                           int nao, int R2, int nq, int cp, int nkb, uint32_t *pm, i64 rows, int r,
+                           hipStream_t s);
+size_t xy_rowmax_pm_words(i64 rows, int cp, int r, int nkey);
+int xy_rowmax_splits(int nao, int nkey, int nq);
+hipError_t launch_xy_rowmax_pm(const uint32_t *pm, int nao, int nq, int nkey, int r, i64 rows, int mpe,
+                               uint32_t *mx, int nsp, hipStream_t s);
 // Exchange splits of a chunk of nkb inner blocks: chosen for occupancy, and
 // never fewer than keep each split's int32 sums exact (mixed_max_depth()
 // inner indices at most).
 int ex_mixed_nsplit(int mp, int nd, int nkb, int sym = 0);
 int mixed_max_depth();
-// Workgroups of the mixed half-transform of nq slabs (cpx padded factor
-// columns) and of the mixed exchange with nsplit splits.
-int mixed_ht_tiles(int mp, int cpx, int nq);
+// Workgroups of the mixed half-transform of nrow stacked rows (cpx padded
+// factor columns) and of the mixed exchange with nsplit splits.
+int mixed_ht_tiles(int nrow, int cpx);
 int mixed_ex_tiles(int mp, int nd, int nsplit, int sym);
 // B digit planes from packed slabs (slab stride bs = nao (nao + 1) / 2);
 // mixed_packed_ok tells whether the packed slicer covers rows of kp inner

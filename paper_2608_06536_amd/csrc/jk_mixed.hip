@@ -8,6 +8,7 @@
 //   ht      [X^Q | Y^Q] = slices(B^Q) x slices([C_L | C_R]), recombined in FP64
 //   rowmax  exponent of every row (side, k, m) of X/Y over the chunk
 //   ex      K_k (+)= slices(X_k) x slices(Y_k) over the chunk, recombined in FP64
+#include <algorithm>
 #include <mutex>
 #include <set>
 #include <utility>
@@ -21,16 +22,17 @@ namespace jk {
 
 namespace {
 constexpr int kNS = kSliceDigits;       // digits per operand (31 bits)
-constexpr int kMT = 128, kNT = 128;     // workgroup tile: eight waves of 32 x 64
-constexpr int kWTN = 2;                 // MFMA tiles per wave, side by side
-constexpr int kRowPad = 128;            // plane rows are padded to this
+constexpr int kRowPad = 64;             // X/Y planes' rows are padded to this
 constexpr int kKPad = kSliceKB;         // plane inner bytes are padded to this
-typedef STileW<kMT, kNT, kNS, kWTN> TileS;   // exchange: eight waves, one workgroup per CU
-constexpr int kHtMT = 64;                     // half-transform: 64 x 128, four waves,
-typedef STileW<kHtMT, kNT, kNS, kWTN> TileH;  // two workgroups per CU
-constexpr int kNbHt = 3, kNbEx = 3;           // LDS stage buffers
-typedef SPipe<TileH, kNbHt> PipeHt;
-typedef SPipe<TileS, kNbEx> PipeEx;
+// Workgroup tiles of four 32 x 64 waves, 73.5 KB of LDS, two workgroups per CU
+// (the sums of a wave's 32 x 64 outputs take 160 registers).  The
+// half-transform and the exchange's vertical tiles are 128 x 64, the
+// exchange's horizontal ones 64 x 128.
+typedef STileW<128, 64, kNS, 2> TileV;
+typedef STileW<64, 128, kNS, 2> TileZ;
+constexpr int kLdsBytes = 3 * TileV::STAGE_BYTES;
+static_assert(TileV::STAGE_BYTES == TileZ::STAGE_BYTES, "one LDS size");
+constexpr int kMhM = 128, kMhN = 64;
 
 inline int cdiv(i64 a, i64 b) { return (int)((a + b - 1) / b); }
 
@@ -259,19 +261,27 @@ __global__ void __launch_bounds__(256) k_slice_band_packed(const double *__restr
 
 // Elementwise slicer of the half-transformed factors.  Source XY[ql][m][c]
 // (c < nkey r; X_k = columns k*r.., Y_k = columns R + k*r..; nkey = 2 nd, or
-// nd when only X is formed), plane row (side * nd + k) * mp + m, inner index j = ql * r + i (j < nj), row
-// exponents exps[plane row] known.  32 plane rows x one 32-byte inner block
-// per workgroup (grid: row groups x nkb); each plane write of a workgroup is
-// one contiguous kilobyte.
+// nd when only X is formed), plane row (side * nd + k) * mp + m, inner index
+// j = ql * r + i (j < nj).  The row's exponent comes from its nsp partial
+// maxima (rowmax below) and is left in exps for the exchange by the threads of
+// inner block 0.  32 plane rows x one 32-byte inner block per workgroup (grid:
+// row groups x nkb); each plane write of a workgroup is one contiguous
+// kilobyte.
 __device__ __forceinline__ void slice_xy_block(const double *__restrict__ XY, int nao, int nkey,
                                                int r, int mp, int nj, int8_t *__restrict__ out,
                                                i64 pstride, i64 kbstride,
-                                               const int *__restrict__ exps, int row, int sub,
-                                               int kb)
+                                               const uint32_t *__restrict__ mx, int nsp,
+                                               int *__restrict__ exps, int row, int sub, int kb)
 {
     const int key = row / mp, m = row % mp;
     const bool live = m < nao;
-    const int e = exps[row];
+    uint32_t hi = 0;
+    if (live)
+        for (int u = 0; u < nsp; u++)
+            hi = max(hi, mx[(i64)u * nkey * mp + row]);
+    const int e = row_exponent_hi(hi);
+    if (kb == 0 && sub == 0)
+        exps[row] = e;
     const i64 R2 = (i64)nkey * r;     // row length of XY
     // loads are unconditional (clamped addresses), masked afterwards
     const double *s = XY + (i64)(live ? m : nao - 1) * R2 + (i64)key * r;
@@ -303,7 +313,8 @@ __device__ __forceinline__ void slice_xy_block(const double *__restrict__ XY, in
 __global__ void __launch_bounds__(256) k_slice_xy(const double *__restrict__ XY, int nao, int nkey,
                                                   int r, int mp, int nj, int8_t *__restrict__ out,
                                                   i64 pstride, i64 kbstride,
-                                                  const int *__restrict__ exps, int nkb)
+                                                  const uint32_t *__restrict__ mx, int nsp,
+                                                  int *__restrict__ exps, int nkb)
 {
     const int t = threadIdx.x, sub = t & 7;
     const int row = blockIdx.x * 32 + (t >> 3);
@@ -311,92 +322,97 @@ __global__ void __launch_bounds__(256) k_slice_xy(const double *__restrict__ XY,
         return;
     // inner blocks kb = blockIdx.y, + gridDim.y, ... (grid y is capped at 65535)
     for (int kb = blockIdx.y; kb < nkb; kb += gridDim.y)
-        slice_xy_block(XY, nao, nkey, r, mp, nj, out, pstride, kbstride, exps, row, sub, kb);
+        slice_xy_block(XY, nao, nkey, r, mp, nj, out, pstride, kbstride, mx, nsp, exps, row, sub, kb);
 }
 
 // ------------------------------------------------------------------ half-transform
-// For slab ql of the chunk: XY[ql][m][c] = 2^(eB + eC - 14) * sum_l S_l 2^(-8 (l - 2))
-// (c < R: X = B^Q C_L, c >= R: Y = B^Q C_R).  A planes: rows ql * mp + m;
-// B planes: rows c.  Each workgroup writes whole 1 KB row segments.
+// XY[g][c] = 2^(eB + eC - 14) * sum_l S_l 2^(-8 (l - 2)) over the chunk's slabs
+// stacked into rows g = ql nao + m (c < R: X = B^Q C_L, c >= R: Y = B^Q C_R),
+// so that only the chunk's last tile has rows to spare; A planes: rows g (tiles
+// may read up to 127 rows past the chunk), B planes: rows c, cp of them.
 //
-// With pm set, the tile also leaves the row maxima the exponents of X and Y
-// need: for each of its rows m and each key (c / r) its columns meet, the
-// largest |XY[ql][m][c]| over those columns, at
-//     pm[((ql nct + cb) nslot + key - key0) mp + m]
-// (cb = column tile, key0 = its first key, nslot >= the keys a tile meets).
-// The tile's |XY| values go to LDS (the pipeline's buffers, free after the
-// products), rows kPmLd doubles apart, and one thread per (row, key) takes the
-// maximum over the key's columns.  The maximum is exact, so the exponents
-// equal those of a pass over XY.
+// The tile also leaves the row maxima the exponents of X and Y need: for each
+// of its rows and each key (c / r) its columns meet, the largest |XY| over
+// those columns, as the value's high word rounded up (the exponent depends on
+// no more), at
+//     pm[(cb nslot + key - key0) rows + g]
+// (cb = column tile, key0 = its first key, nslot >= the keys a tile meets,
+// rows = pm's pitch).  The words go to LDS (the pipeline's buffers, free after
+// the products), and one thread per row takes the maxima key by key.  The
+// maximum is exact, so the exponents equal those of a pass over XY.
 //
 // The row and column exponents a lane needs (16 rows, 2 columns) are loaded
 // before the products, so that their latency is hidden behind them.
-constexpr int kPmLd = kNT + 1;      // LDS row stride of the |XY| tile (doubles)
-static_assert(kHtMT * kPmLd * 8 <= PipeHt::LDS_BYTES, "|XY| tile in the pipeline's LDS");
+constexpr int kPmLd = kMhN + 1;     // LDS row stride of the |XY| tile (words)
+static_assert(kMhM * kPmLd * 4 <= kLdsBytes, "|XY| tile in the pipeline's LDS");
 
 __device__ __forceinline__ void ht_mixed_tile(const int8_t *__restrict__ Bp, i64 bpstride,
                                               i64 bkbstride, const int *__restrict__ eB,
                                               const int8_t *__restrict__ Cp, i64 cpstride,
                                               i64 ckbstride, const int *__restrict__ eC,
-                                              double *__restrict__ XY, int nao, int R2, int mp,
-                                              int cp, int nkb, int t, char *lds,
-                                              double *__restrict__ pm = nullptr, int r = 1,
-                                              int nslot = 0)
+                                              double *__restrict__ XY, int nrow, int R2, int cp,
+                                              int nkb, int t, char *lds, uint32_t *__restrict__ pm,
+                                              int rows, int r, int nslot)
 {
-    typedef TileH TL;
-    const int nmt = mp / kHtMT, nct = cp / kNT;
-    const int ql = t / (nmt * nct), rem = t % (nmt * nct);
-    const int mb = rem / nct, cb = rem % nct;
+    typedef TileV TL;
+    const int nct = cp / kMhN;
+    const int rb = t / nct, cb = t % nct;
+    const int g0 = rb * kMhM, c0 = cb * kMhN;
     // exponents of this lane's rows (element e of either tile) and columns
-    // (rows < mp and columns < cp always have one)
-    int eb[16], ec[kWTN];
+    int eb[16], ec[TL::TN];
 #pragma unroll
     for (int e = 0; e < 16; e++) {
         int row, col;
         stile_coord_wide<TL>(0, e, row, col);
-        eb[e] = eB[(i64)ql * mp + mb * kHtMT + row];
+        eb[e] = eB[g0 + row];
     }
 #pragma unroll
-    for (int tt = 0; tt < kWTN; tt++) {
+    for (int tt = 0; tt < TL::TN; tt++) {
         int row, col;
         stile_coord_wide<TL>(tt, 0, row, col);
-        ec[tt] = eC[cb * kNT + col] + kSliceProdShift;
+        ec[tt] = eC[c0 + col] + kSliceProdShift;
     }
-    SPlanes a{Bp + (i64)ql * mp * kSliceKB, bpstride, bkbstride};
+    SPlanes a{Bp, bpstride, bkbstride};
     SPlanes b{Cp, cpstride, ckbstride};
     SAccW<TL> acc;
     acc.zero();
-    stile_gemm_w4<TL, kNS, kNbHt>(a, b, mb * kHtMT, cb * kNT, 0, nkb, lds, acc);
-    double *out = XY + (i64)ql * nao * R2;
-    double *tile = (double *)lds;
-    if (pm)
-        __syncthreads();                      // every wave past its last stage
+    stile_gemm_w4<TL, kNS>(a, b, g0, c0, 1 << 30, cp, 0, nkb, lds, acc);
+    uint32_t *tile = (uint32_t *)lds;
+    __syncthreads();                          // every wave past its last stage
 #pragma unroll
-    for (int tt = 0; tt < kWTN; tt++)
+    for (int tt = 0; tt < TL::TN; tt++)
 #pragma unroll
         for (int e = 0; e < 16; e++) {
             int row, col;
             stile_coord_wide<TL>(tt, e, row, col);
-            const int m = mb * kHtMT + row, c = cb * kNT + col;
+            const int g = g0 + row, c = c0 + col;
             const double v = ldexp(combine_levels_wide<TL>(acc, tt, e), eb[e] + ec[tt]);
-            if (m < nao && c < R2)
-                out[(i64)m * R2 + c] = v;
-            if (pm)
-                tile[row * kPmLd + col] = fabs(v);
+            if (g < nrow && c < R2)
+                XY[(i64)g * R2 + c] = v;
+            tile[row * kPmLd + col] = high_word_up(v);
         }
-    if (pm) {
-        __syncthreads();
-        const int c0 = cb * kNT, key0 = c0 / r;
-        const int cend = (c0 + kNT) < R2 ? (c0 + kNT) : R2;
-        double *dst = pm + (i64)(ql * nct + cb) * nslot * mp + mb * kHtMT;
-        for (int e = threadIdx.x; e < kHtMT * nslot; e += TL::NTHR) {
-            const int slot = e / kHtMT, row = e % kHtMT, key = key0 + slot;
-            const int ca = key * r > c0 ? key * r - c0 : 0;
-            const int cz = ((key + 1) * r < cend ? (key + 1) * r : cend) - c0;
-            double mx = 0.0;
-            for (int c = ca; c < cz; c++)
-                mx = fmax(mx, tile[row * kPmLd + c]);
-            dst[(i64)slot * mp + row] = mx;
+    __syncthreads();
+    if (threadIdx.x < kMhM) {
+        const uint32_t *x = tile + threadIdx.x * kPmLd;
+        uint32_t *dst = pm + (i64)cb * nslot * rows + g0 + threadIdx.x;
+        const int cend = (c0 + kMhN) < R2 ? kMhN : R2 - c0;
+        int left = r - c0 % r;                // columns of the first key
+        uint32_t mx = 0;
+        for (int cg = 0; cg < cend; cg += 16) {
+            uint32_t v[16];
+#pragma unroll
+            for (int u = 0; u < 16; u++)
+                v[u] = x[cg + u];
+#pragma unroll
+            for (int u = 0; u < 16; u++) {
+                mx = max(mx, v[u]);
+                if (cg + u < cend && (--left == 0 || cg + u + 1 == cend)) {
+                    *dst = mx;
+                    dst += rows;
+                    left = r;
+                    mx = 0;
+                }
+            }
         }
     }
 }
@@ -405,147 +421,153 @@ __global__ void __launch_bounds__(256, 2) k_ht_mixed(const int8_t *__restrict__ 
                                                      i64 bkbstride, const int *__restrict__ eB,
                                                      const int8_t *__restrict__ Cp, i64 cpstride,
                                                      i64 ckbstride, const int *__restrict__ eC,
-                                                     double *__restrict__ XY, int nao, int R2, int mp,
-                                                     int cp, int nkb, double *__restrict__ pm, int r,
-                                                     int nslot)
+                                                     double *__restrict__ XY, int nrow, int R2, int cp,
+                                                     int nkb, uint32_t *__restrict__ pm, int rows,
+                                                     int r, int nslot)
 {
     extern __shared__ char lds[];
     // consecutive tiles (the column tiles of a row panel) on one XCD, sharing its L2
-    ht_mixed_tile(Bp, bpstride, bkbstride, eB, Cp, cpstride, ckbstride, eC, XY, nao, R2, mp, cp, nkb,
-                  xcd_swizzle(blockIdx.x, gridDim.x), lds, pm, r, nslot);
+    ht_mixed_tile(Bp, bpstride, bkbstride, eB, Cp, cpstride, ckbstride, eC, XY, nrow, R2, cp, nkb,
+                  xcd_swizzle(blockIdx.x, gridDim.x), lds, pm, rows, r, nslot);
 }
 
 // Partial-maximum slots per (row, column tile): the keys a column tile of
-// kNT columns can meet.
+// kMhN columns can meet.
 __host__ __device__ inline int pm_slots(int r, int nkey)
 {
-    const int n = (kNT - 1) / r + 2;
+    const int n = (kMhN - 1) / r + 2;
     return n < nkey ? n : nkey;
 }
 
-// exps[key mpe + m] from the half-transform's partial maxima (rows of mp per
-// slab, the half-transform's row pitch): the largest over the chunk's slabs
-// and over the (one or two) column tiles that meet key's columns [key r,
-// key r + r), for the 64 rows of row block mblk.  NW waves; wave w takes the
-// slabs ql = w, w + NW, ... (coalesced 512-byte reads); the wave maxima meet
-// in red.
-template <int NW>
-__device__ __forceinline__ void rowmax_pm_block(const double *__restrict__ pm, int nao, int nq,
-                                                int nct, int mp, int mpe, int nslot, int r,
-                                                int *__restrict__ exps, int mblk, int key,
-                                                double (*red)[64])
+// mx[sp nkey mpe + key mpe + m]: the largest of the half-transform's partial
+// maxima (pitch rows) over the slabs of split sp of the chunk's nq, and over
+// the column tiles that meet key's columns [key r, key r + r), for the 64 rows
+// of row block mblk.  Four waves; wave w takes every fourth slab (coalesced
+// 256-byte reads); the wave maxima meet in red.
+__device__ __forceinline__ void rowmax_pm_block(const uint32_t *__restrict__ pm, int nao, int nq,
+                                                int rows, int mpe, int nslot, int nkey, int r,
+                                                uint32_t *__restrict__ out, int mblk, int key, int sp,
+                                                int nsp, uint32_t (*red)[64])
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int m = mblk * 64 + lane;
     const int mc = m < nao ? m : nao - 1;
-    const int cb0 = key * r / kNT, cb1 = (key * r + r - 1) / kNT;
-    const i64 qs = (i64)nct * nslot * mp;
-    double mx = 0.0;
+    const int cb0 = key * r / kMhN, cb1 = (key * r + r - 1) / kMhN;
+    const int len = (nq + nsp - 1) / nsp, q0 = sp * len, q1 = q0 + len < nq ? q0 + len : nq;
+    uint32_t mx = 0;
     for (int cb = cb0; cb <= cb1; cb++) {
-        const int slot = key - cb * kNT / r;
-        const double *p = pm + ((i64)cb * nslot + slot) * mp + mc;
-        int ql = w;
-        for (; ql + 3 * NW < nq; ql += 4 * NW) {
-            const double v0 = p[(i64)ql * qs], v1 = p[(i64)(ql + NW) * qs];
-            const double v2 = p[(i64)(ql + 2 * NW) * qs], v3 = p[(i64)(ql + 3 * NW) * qs];
-            mx = fmax(mx, fmax(fmax(v0, v1), fmax(v2, v3)));
+        const int slot = key - cb * kMhN / r;
+        const uint32_t *p = pm + ((i64)cb * nslot + slot) * rows + mc;
+        int ql = q0 + w;
+        for (; ql + 12 < q1; ql += 16) {
+            const uint32_t v0 = p[(i64)ql * nao], v1 = p[(i64)(ql + 4) * nao];
+            const uint32_t v2 = p[(i64)(ql + 8) * nao], v3 = p[(i64)(ql + 12) * nao];
+            mx = max(mx, max(max(v0, v1), max(v2, v3)));
         }
-        for (; ql < nq; ql += NW)
-            mx = fmax(mx, p[(i64)ql * qs]);
+        for (; ql < q1; ql += 4)
+            mx = max(mx, p[(i64)ql * nao]);
     }
     red[w][lane] = mx;
     __syncthreads();
-    if (w == 0 && m < nao) {
-        double v = red[0][lane];
-#pragma unroll
-        for (int u = 1; u < NW; u++)
-            v = fmax(v, red[u][lane]);
-        exps[(i64)key * mpe + m] = row_exponent(v);
-    }
+    if (w == 0 && m < nao)
+        out[((i64)sp * nkey + key) * mpe + m] = max(max(red[0][lane], red[1][lane]),
+                                                   max(red[2][lane], red[3][lane]));
 }
 
-// Workgroup: 64 rows of one key, 16 waves.
-constexpr int kPmWaves = 16;
-__global__ void __launch_bounds__(64 * kPmWaves) k_xy_rowmax_pm(const double *__restrict__ pm, int nao,
-                                                               int nq, int nct, int mp, int mpe,
-                                                               int nslot, int r,
-                                                               int *__restrict__ exps)
+// Workgroup: 64 rows of one key, one split of the slabs.
+__global__ void __launch_bounds__(256) k_xy_rowmax_pm(const uint32_t *__restrict__ pm, int nao, int nq,
+                                                      int rows, int mpe, int nslot, int r,
+                                                      uint32_t *__restrict__ out)
 {
-    __shared__ double red[kPmWaves][64];
-    rowmax_pm_block<kPmWaves>(pm, nao, nq, nct, mp, mpe, nslot, r, exps, blockIdx.x, blockIdx.y, red);
+    __shared__ uint32_t red[4][64];
+    rowmax_pm_block(pm, nao, nq, rows, mpe, nslot, gridDim.y, r, out, blockIdx.x, blockIdx.y, blockIdx.z,
+                    gridDim.z, red);
 }
 
 // ------------------------------------------------------------------ exchange
 // Kp[s][k][m][n] (+)= scale 2^(eX + eY - 14) * sum_l S_l 2^(-8 (l - 2)) over the inner
 // blocks [s * kbl, (s + 1) * kbl) of split s.  X/Y planes: rows k * mp + m
 // from Xp / Yp (same strides); row exponents eX[k * mp + m], eY[k * mp + n].
-__device__ __forceinline__ void ex_mixed_tile(const int8_t *__restrict__ Xp,
-                                              const int8_t *__restrict__ Yp, i64 pstride,
-                                              i64 kbstride, const int *__restrict__ eX,
-                                              const int *__restrict__ eY, double *__restrict__ Kp,
-                                              int nao, int nd, int mp, int nkb, int kbl,
-                                              int accumulate, int sym, double scale, int t,
-                                              char *lds)
+//
+// Tiles: the n x n blocks of 64 x 64 (n = mp / 64) in pairs, side by side along
+// each row of blocks, the last column of an odd n on top of each other (general
+// densities), so that the padding is that of 64 rows and columns: n = 5 (nao
+// 300) takes 13 tiles of 128 x 64 where 128 x 128 ones took 9, twice the size.
+// sym (Y = X, the upper triangle): row mb's blocks from mb on in pairs.  The
+// exchange of nao 300, naux 1200, 4 densities of rank 30: 278 -> 212 us (93 -> 123
+// TFLOP/s of FP64 equivalent); at multiples of 128 the two are even.
+__host__ __device__ inline int ex_pairs(int n, int sym)
 {
-    typedef TileS TL;
-    const int nmt = mp / kMT, nnt = mp / kNT;
-    // sym: Y = X, only the square tiles with nb >= mb (upper triangle)
-    const int pk = sym ? nmt * (nmt + 1) / 2 : nmt * nnt;
-    const int per = nd * pk;
-    const int sp = t / per, rem0 = t % per;
-    const int k = rem0 / pk, rem = rem0 % pk;
-    int mb, nb;
+    if (sym)                          // sum over mb of ceil((n - mb) / 2)
+        return ((n + 1) / 2) * ((n + 2) / 2);
+    return n * (n / 2) + (n & 1 ? (n + 1) / 2 : 0);
+}
+// Blocks (mb, nb) of pair t; true: on top of each other.
+__device__ __forceinline__ bool ex_pair(int t, int n, int sym, int &mb, int &nb)
+{
     if (sym) {
-        int q = rem;
         mb = 0;
-        while (q >= nmt - mb) {
-            q -= nmt - mb;
+        while (t >= (n - mb + 1) / 2) {
+            t -= (n - mb + 1) / 2;
             mb++;
         }
-        nb = mb + q;
-    } else {
-        mb = rem / nnt;
-        nb = rem % nnt;
+        nb = mb + 2 * t;
+        return false;
     }
-    const int kb0 = sp * kbl < nkb ? sp * kbl : nkb;
-    const int kb1 = (kb0 + kbl) < nkb ? (kb0 + kbl) : nkb;
-    SPlanes a{Xp + (i64)k * mp * kSliceKB, pstride, kbstride};
-    SPlanes b{Yp + (i64)k * mp * kSliceKB, pstride, kbstride};
+    const int h = n / 2;
+    if (t < n * h) {
+        mb = t / h;
+        nb = 2 * (t % h);
+        return false;
+    }
+    mb = 2 * (t - n * h);
+    nb = n - 1;
+    return true;
+}
+
+template <class TL>
+__device__ __forceinline__ void ex_mixed_product(const int8_t *__restrict__ Xk,
+                                                 const int8_t *__restrict__ Yk, i64 pstride,
+                                                 i64 kbstride, const int *__restrict__ eX,
+                                                 const int *__restrict__ eY, double *__restrict__ Kk,
+                                                 int nao, int mp, int m0, int n0, int kb0, int kb1,
+                                                 int accumulate, double scale, char *lds)
+{
+    SPlanes a{Xk, pstride, kbstride};
+    SPlanes b{Yk, pstride, kbstride};
     SAccW<TL> acc;
     acc.zero();
-    stile_gemm_pp<TL, kNS, kNbEx>(a, b, mb * kMT, nb * kNT, kb0, kb1, lds, acc);
-    double *Kk = Kp + ((i64)sp * nd + k) * nao * nao;
-    // The lane's row and column exponents (rows and columns < mp all have
-    // one), and per tile the partial sums it adds to, each loaded in one
-    // batch so that their latencies overlap.
-    int ex[16], ey[kWTN];
+    stile_gemm_w4<TL, kNS>(a, b, m0, n0, mp, mp, kb0, kb1, lds, acc);
+    // The lane's row and column exponents, and per tile the partial sums it
+    // adds to, each loaded in one batch so that their latencies overlap.
+    int ex[16], ey[TL::TN];
 #pragma unroll
     for (int e = 0; e < 16; e++) {
         int row, col;
         stile_coord_wide<TL>(0, e, row, col);
-        ex[e] = eX[(i64)k * mp + mb * kMT + row];
+        ex[e] = eX[min(m0 + row, mp - 1)];
     }
 #pragma unroll
-    for (int tt = 0; tt < kWTN; tt++) {
+    for (int tt = 0; tt < TL::TN; tt++) {
         int row, col;
         stile_coord_wide<TL>(tt, 0, row, col);
-        ey[tt] = eY[(i64)k * mp + nb * kNT + col] + kSliceProdShift;
+        ey[tt] = eY[min(n0 + col, mp - 1)] + kSliceProdShift;
     }
 #pragma unroll
-    for (int tt = 0; tt < kWTN; tt++) {
+    for (int tt = 0; tt < TL::TN; tt++) {
         double old[16];
 #pragma unroll
         for (int e = 0; e < 16; e++) {
             int row, col;
             stile_coord_wide<TL>(tt, e, row, col);
-            const int m = mb * kMT + row, n = nb * kNT + col;
+            const int m = m0 + row, n = n0 + col;
             old[e] = (accumulate && m < nao && n < nao) ? Kk[(i64)m * nao + n] : 0.0;
         }
 #pragma unroll
         for (int e = 0; e < 16; e++) {
             int row, col;
             stile_coord_wide<TL>(tt, e, row, col);
-            const int m = mb * kMT + row, n = nb * kNT + col;
+            const int m = m0 + row, n = n0 + col;
             if (m < nao && n < nao) {
                 const double v = scale * ldexp(combine_levels_wide<TL>(acc, tt, e), ex[e] + ey[tt]);
                 Kk[(i64)m * nao + n] = accumulate ? old[e] + v : v;
@@ -554,13 +576,39 @@ __device__ __forceinline__ void ex_mixed_tile(const int8_t *__restrict__ Xp,
     }
 }
 
-__global__ void __launch_bounds__(512) k_ex_mixed(const int8_t *__restrict__ Xp,
-                                                  const int8_t *__restrict__ Yp, i64 pstride,
-                                                  i64 kbstride, const int *__restrict__ eX,
-                                                  const int *__restrict__ eY,
-                                                  double *__restrict__ Kp, int nao, int nd, int mp,
-                                                  int nkb, int kbl, int accumulate, int sym,
-                                                  double scale)
+__device__ __forceinline__ void ex_mixed_tile(const int8_t *__restrict__ Xp,
+                                              const int8_t *__restrict__ Yp, i64 pstride,
+                                              i64 kbstride, const int *__restrict__ eX,
+                                              const int *__restrict__ eY, double *__restrict__ Kp,
+                                              int nao, int nd, int mp, int nkb, int kbl,
+                                              int accumulate, int sym, double scale, int t,
+                                              char *lds)
+{
+    const int n = mp / 64, np = ex_pairs(n, sym), per = nd * np;
+    const int sp = t / per, rem0 = t % per;
+    const int k = rem0 / np;
+    int mb, nb;
+    const bool vertical = ex_pair(rem0 % np, n, sym, mb, nb);
+    const int kb0 = sp * kbl < nkb ? sp * kbl : nkb;
+    const int kb1 = (kb0 + kbl) < nkb ? (kb0 + kbl) : nkb;
+    const int8_t *Xk = Xp + (i64)k * mp * kSliceKB, *Yk = Yp + (i64)k * mp * kSliceKB;
+    const int *eXk = eX + (i64)k * mp, *eYk = eY + (i64)k * mp;
+    double *Kk = Kp + ((i64)sp * nd + k) * nao * nao;
+    if (vertical)
+        ex_mixed_product<TileV>(Xk, Yk, pstride, kbstride, eXk, eYk, Kk, nao, mp, mb * 64, nb * 64, kb0,
+                                kb1, accumulate, scale, lds);
+    else
+        ex_mixed_product<TileZ>(Xk, Yk, pstride, kbstride, eXk, eYk, Kk, nao, mp, mb * 64, nb * 64, kb0,
+                                kb1, accumulate, scale, lds);
+}
+
+__global__ void __launch_bounds__(256, 2) k_ex_mixed(const int8_t *__restrict__ Xp,
+                                                     const int8_t *__restrict__ Yp, i64 pstride,
+                                                     i64 kbstride, const int *__restrict__ eX,
+                                                     const int *__restrict__ eY,
+                                                     double *__restrict__ Kp, int nao, int nd, int mp,
+                                                     int nkb, int kbl, int accumulate, int sym,
+                                                     double scale)
 {
     extern __shared__ char lds[];
     ex_mixed_tile(Xp, Yp, pstride, kbstride, eX, eY, Kp, nao, nd, mp, nkb, kbl, accumulate, sym,
@@ -595,9 +643,9 @@ __global__ void __launch_bounds__(256) k_bm_slice_b(const BMember *__restrict__ 
     int q0, nq;
     chunk_of(m, c, q0, nq);
     const i64 row = (i64)loc * 4 + (threadIdx.x >> 6);
-    if (row >= (i64)nq * m.mpb)      // whole waves leave together
+    if (row >= (i64)nq * m.nao)      // whole waves leave together
         return;
-    slice_row_wave<NJ>(m.B + (i64)q0 * m.npos, m.npos, m.nao, m.nao, m.nao, m.mpb, m.kp / kSliceKB,
+    slice_row_wave<NJ>(m.B + (i64)q0 * m.npos, m.npos, m.nao, m.nao, m.nao, m.nao, m.kp / kSliceKB,
                        m.Bp, m.bps, m.bkb, m.eB, row);
 }
 
@@ -612,9 +660,9 @@ __global__ void __launch_bounds__(256) k_bm_slice_b_packed(const BMember *__rest
     const BMember &m = M[find_member(tab, blockIdx.x, loc)];
     int q0, nq;
     chunk_of(m, c, q0, nq);
-    const int nband = (m.mpb + kBand - 1) / kBand;
+    const int nband = (m.nao + kBand - 1) / kBand;
     const int b = loc / nband, m0 = (loc % nband) * kBand;
-    slice_band_packed<NJ>(m.B + (i64)(q0 + b) * m.bslab, b, m0, m.nao, m.mpb, m.kp / kSliceKB, m.Bp,
+    slice_band_packed<NJ>(m.B + (i64)(q0 + b) * m.bslab, b, m0, m.nao, m.nao, m.kp / kSliceKB, m.Bp,
                           m.bps, m.bkb, m.eB, T);
 }
 
@@ -624,25 +672,26 @@ __global__ void __launch_bounds__(256, 2) k_bm_ht(const BMember *__restrict__ M,
     extern __shared__ char lds[];
     int loc;
     const BMember &m = M[find_member(tab, xcd_local(blockIdx.x, gridDim.x), loc)];
-    (void)c;
+    int q0, nq;
+    chunk_of(m, c, q0, nq);
     const int nkey = m.sym ? m.nd : 2 * m.nd;
-    ht_mixed_tile(m.Bp, m.bps, m.bkb, m.eB, m.Cp, m.cps, m.ckb, m.eC, m.XY, m.nao, nkey * m.r, m.mpb,
-                  m.cpx, m.kp / kSliceKB, loc, lds, m.pm, m.r, pm_slots(m.r, nkey));
+    ht_mixed_tile(m.Bp, m.bps, m.bkb, m.eB, m.Cp, m.cps, m.ckb, m.eC, m.XY, nq * m.nao, nkey * m.r,
+                  m.cpx, m.kp / kSliceKB, loc, lds, m.pm, m.rows, m.r, pm_slots(m.r, nkey));
 }
 
-// Row exponents from the half-transform's partial maxima: tile loc of a
+// Row maxima from the half-transform's partial ones: tile loc of a
 // member is (row block loc % nmb, key loc / nmb), 64 rows, four waves.
 __global__ void __launch_bounds__(256) k_bm_rowmax(const BMember *__restrict__ M,
                                                    const int *__restrict__ tab, int c)
 {
-    __shared__ double red[4][64];
+    __shared__ uint32_t red[4][64];
     int loc;
     const BMember &m = M[find_member(tab, blockIdx.x, loc)];
     int q0, nq;
     chunk_of(m, c, q0, nq);
     const int nkey = m.sym ? m.nd : 2 * m.nd, nmb = (m.nao + 63) / 64;
-    rowmax_pm_block<4>(m.pm, m.nao, nq, m.cpx / kNT, m.mpb, m.mp, pm_slots(m.r, nkey), m.r, m.eXY,
-                       loc % nmb, loc / nmb, red);
+    rowmax_pm_block(m.pm, m.nao, nq, m.rows, m.mp, pm_slots(m.r, nkey), nkey, m.r, m.mx, loc % nmb,
+                    loc / nmb, 0, 1, red);
 }
 
 __global__ void __launch_bounds__(256) k_bm_slice_xy(const BMember *__restrict__ M,
@@ -657,11 +706,11 @@ __global__ void __launch_bounds__(256) k_bm_slice_xy(const BMember *__restrict__
     const int row = (loc % ngroup) * 32 + (threadIdx.x >> 3);
     if (row >= nkey * m.mp)
         return;
-    slice_xy_block(m.XY, m.nao, nkey, m.r, m.mp, nq * m.r, m.XYp, m.xps, m.xkb, m.eXY, row,
+    slice_xy_block(m.XY, m.nao, nkey, m.r, m.mp, nq * m.r, m.XYp, m.xps, m.xkb, m.mx, 1, m.eXY, row,
                    threadIdx.x & 7, loc / ngroup);
 }
 
-__global__ void __launch_bounds__(512) k_bm_ex(const BMember *__restrict__ M,
+__global__ void __launch_bounds__(256, 2) k_bm_ex(const BMember *__restrict__ M,
                                                const int *__restrict__ tab, int c)
 {
     extern __shared__ char lds[];
@@ -680,7 +729,8 @@ __global__ void __launch_bounds__(512) k_bm_ex(const BMember *__restrict__ M,
 // ------------------------------------------------------------------ launchers
 int mixed_nslice() { return kNS; }
 int mixed_row_pad() { return kRowPad; }
-int mixed_b_row_pad() { return kHtMT; }
+i64 mixed_b_rows(i64 nrow) { return (nrow + kMhM - 1) / kMhM * kMhM + kMhM; }
+int mixed_col_pad() { return kMhN; }
 int mixed_k_pad() { return kKPad; }
 int mixed_k_block() { return kSliceKB; }
 
@@ -782,52 +832,55 @@ int mixed_packed_ok(int nao, int kp) { return cdiv(kp / kSliceKB, 8) <= 8 && nao
 int mixed_rowmax_ok(int R2) { return R2 <= 8192; }
 
 hipError_t launch_slice_xy(const double *XY, int nao, int nkey, int r, int mp, int nj, int nkb,
-                           int8_t *out, i64 pstride, i64 kbstride, const int *exps, hipStream_t s)
+                           int8_t *out, i64 pstride, i64 kbstride, const uint32_t *mx, int nsp,
+                           int *exps, hipStream_t s)
 {
     {
         ProfScope ps_("slice_xy", s);
         hipLaunchKernelGGL(k_slice_xy, dim3(cdiv((i64)nkey * mp, 32), nkb < 65535 ? nkb : 65535),
-                           dim3(256), 0, s, XY, nao, nkey, r, mp, nj, out, pstride, kbstride, exps,
-                           nkb);
+                           dim3(256), 0, s, XY, nao, nkey, r, mp, nj, out, pstride, kbstride, mx, nsp,
+                           exps, nkb);
     }
     return hipGetLastError();
 }
 
-
-int xy_rowmax_slots(int r, int nkey) { return pm_slots(r, nkey); }
-
-size_t xy_rowmax_pm_doubles(int nq, int mp, int cp, int r, int nkey)
+size_t xy_rowmax_pm_words(i64 rows, int cp, int r, int nkey)
 {
-    return (size_t)nq * (cp / kNT) * xy_rowmax_slots(r, nkey) * mp;
+    return (size_t)(cp / kMhN) * pm_slots(r, nkey) * rows;
 }
 
 hipError_t launch_ht_mixed(const int8_t *Bp, i64 bpstride, i64 bkbstride, const int *eB,
                            const int8_t *Cp, i64 cpstride, i64 ckbstride, const int *eC, double *XY,
-                           int nao, int R2, int nq, int mp, int cp, int nkb, hipStream_t s,
-                           double *pm, int r)
+                           int nao, int R2, int nq, int cp, int nkb, uint32_t *pm, i64 rows, int r,
+                           hipStream_t s)
 {
-    hipError_t e = set_lds((const void *)k_ht_mixed, PipeHt::LDS_BYTES);
+    hipError_t e = set_lds((const void *)k_ht_mixed, kLdsBytes);
     if (e != hipSuccess)
         return e;
-    const int nslot = pm ? xy_rowmax_slots(r, R2 / r) : 0;
-    if (pm && (size_t)kHtMT * nslot * sizeof(double) > (size_t)PipeHt::LDS_BYTES)
-        return hipErrorInvalidValue;
     {
         ProfScope ps_("ht_mixed", s);
-        hipLaunchKernelGGL(k_ht_mixed, dim3(nq * (mp / kHtMT) * (cp / kNT)), dim3(TileH::NTHR),
-                           PipeHt::LDS_BYTES, s, Bp, bpstride, bkbstride, eB, Cp, cpstride, ckbstride,
-                           eC, XY, nao, R2, mp, cp, nkb, pm, r, nslot);
+        hipLaunchKernelGGL(k_ht_mixed, dim3(mixed_ht_tiles(nq * nao, cp)), dim3(TileV::NTHR), kLdsBytes, s,
+                           Bp, bpstride, bkbstride, eB, Cp, cpstride, ckbstride, eC, XY, nq * nao, R2, cp,
+                           nkb, pm, (int)rows, r, pm_slots(r, R2 / r));
     }
     return hipGetLastError();
 }
 
-hipError_t launch_xy_rowmax_pm(const double *pm, int nao, int nq, int nkey, int r, int mp, int mpe,
-                               int cp, int *exps, hipStream_t s)
+// Splits of the row maxima's slabs: the row blocks and keys alone leave a
+// device of 256 CUs idle.
+int xy_rowmax_splits(int nao, int nkey, int nq)
+{
+    const int n = 512 / (cdiv(nao, 64) * nkey), most = nq / 16;
+    return std::max(1, std::min(std::min(n, most), 8));
+}
+
+hipError_t launch_xy_rowmax_pm(const uint32_t *pm, int nao, int nq, int nkey, int r, i64 rows, int mpe,
+                               uint32_t *mx, int nsp, hipStream_t s)
 {
     {
         ProfScope ps_("xy_rowmax_pm", s);
-        hipLaunchKernelGGL(k_xy_rowmax_pm, dim3(cdiv(nao, 64), nkey), dim3(64 * kPmWaves), 0, s, pm, nao, nq,
-                           cp / kNT, mp, mpe, xy_rowmax_slots(r, nkey), r, exps);
+        hipLaunchKernelGGL(k_xy_rowmax_pm, dim3(cdiv(nao, 64), nkey, nsp), dim3(256), 0, s, pm, nao, nq,
+                           (int)rows, mpe, pm_slots(r, nkey), r, mx);
     }
     return hipGetLastError();
 }
@@ -836,13 +889,11 @@ int mixed_max_depth() { return kSliceMaxDepth; }
 
 int ex_mixed_nsplit(int mp, int nd, int nkb, int sym)
 {
-    // one 512-thread workgroup per CU (registers), so half the usual slots
-    const int nmt = mp / kMT;
-    const int tiles = nd * (sym ? nmt * (nmt + 1) / 2 : nmt * (mp / kNT));
+    const int tiles = nd * ex_pairs(mp / 64, sym);
     int maxs = nkb / 16 > 1 ? nkb / 16 : 1;
     if (maxs > 16)
         maxs = 16;
-    const int s = pick_split_slots(tiles, maxs, device_slots() / 2);
+    const int s = pick_split_slots(tiles, maxs, device_slots());
     // exact int32 level sums: a split of cdiv(nkb, s) inner blocks may hold at
     // most kSliceMaxDepth inner indices
     const int need = cdiv(nkb, kSliceMaxDepth / kSliceKB);
@@ -853,17 +904,15 @@ hipError_t launch_ex_mixed(const int8_t *Xp, const int8_t *Yp, i64 pstride, i64 
                            const int *eX, const int *eY, double *Kp, int nao, int nd, int mp, int nkb,
                            int nsplit, int accumulate, hipStream_t s, int sym, double scale)
 {
-    hipError_t e = set_lds((const void *)k_ex_mixed, PipeEx::LDS_BYTES);
+    hipError_t e = set_lds((const void *)k_ex_mixed, kLdsBytes);
     if (e != hipSuccess)
         return e;
     const int kbl = cdiv(nkb, nsplit);
-    const int nmt = mp / kMT;
-    const int pk = sym ? nmt * (nmt + 1) / 2 : nmt * (mp / kNT);
     {
         ProfScope ps_("ex_mixed", s);
-        hipLaunchKernelGGL(k_ex_mixed, dim3(nsplit * nd * pk), dim3(TileS::NTHR), PipeEx::LDS_BYTES, s, Xp,
-                           Yp, pstride, kbstride, eX, eY, Kp, nao, nd, mp, nkb, kbl, accumulate, sym,
-                           scale);
+        hipLaunchKernelGGL(k_ex_mixed, dim3(mixed_ex_tiles(mp, nd, nsplit, sym)), dim3(TileV::NTHR),
+                           kLdsBytes, s, Xp, Yp, pstride, kbstride, eX, eY, Kp, nao, nd, mp, nkb, kbl,
+                           accumulate, sym, scale);
     }
     return hipGetLastError();
 }
@@ -872,9 +921,9 @@ hipError_t launch_ex_mixed(const int8_t *Xp, const int8_t *Yp, i64 pstride, i64 
 // before a launch sequence is captured.
 hipError_t prepare_batched_mixed_kernels()
 {
-    hipError_t e = set_lds((const void *)k_bm_ht, PipeHt::LDS_BYTES);
+    hipError_t e = set_lds((const void *)k_bm_ht, kLdsBytes);
     if (e == hipSuccess)
-        e = set_lds((const void *)k_bm_ex, PipeEx::LDS_BYTES);
+        e = set_lds((const void *)k_bm_ex, kLdsBytes);
     // the packed slicer's band of the longest rows the packed path takes
     const int band = (int)sizeof(double) * kBand * 2048;
     if (e == hipSuccess)
@@ -933,7 +982,7 @@ hipError_t launch_batched_mixed_phase(int phase, const BMember *M, const int *ta
     }
     case kPhaseMHalf: {
         ProfScope ps_("bm_ht_mixed", s);
-        hipLaunchKernelGGL(k_bm_ht, g, dim3(TileH::NTHR), PipeHt::LDS_BYTES, s, M, tab, step);
+        hipLaunchKernelGGL(k_bm_ht, g, dim3(TileV::NTHR), kLdsBytes, s, M, tab, step);
         break;
     }
     case kPhaseMRowmax: {
@@ -948,7 +997,7 @@ hipError_t launch_batched_mixed_phase(int phase, const BMember *M, const int *ta
     }
     case kPhaseMExchange: {
         ProfScope ps_("bm_ex_mixed", s);
-        hipLaunchKernelGGL(k_bm_ex, g, dim3(TileS::NTHR), PipeEx::LDS_BYTES, s, M, tab, step);
+        hipLaunchKernelGGL(k_bm_ex, g, dim3(TileV::NTHR), kLdsBytes, s, M, tab, step);
         break;
     }
     default:
@@ -958,11 +1007,7 @@ hipError_t launch_batched_mixed_phase(int phase, const BMember *M, const int *ta
 }
 
 // Tile counts of the batched mixed phases for one member (host).
-int mixed_ht_tiles(int mp, int cpx, int nq) { return nq * (mp / kHtMT) * (cpx / kNT); }
-int mixed_ex_tiles(int mp, int nd, int nsplit, int sym)
-{
-    const int nmt = mp / kMT;
-    return nsplit * nd * (sym ? nmt * (nmt + 1) / 2 : nmt * (mp / kNT));
-}
+int mixed_ht_tiles(int nrow, int cpx) { return cdiv(nrow, kMhM) * (cpx / kMhN); }
+int mixed_ex_tiles(int mp, int nd, int nsplit, int sym) { return nsplit * nd * ex_pairs(mp / 64, sym); }
 
 } // namespace jk

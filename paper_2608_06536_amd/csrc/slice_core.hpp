@@ -65,6 +65,19 @@ __device__ __forceinline__ int row_exponent(double maxabs)
     return e;
 }
 
+// The same from the high word of maxabs, rounded up if its low word is not
+// zero (high_word_up): the threshold's low word is zero, so both comparisons
+// have the same outcome.
+__device__ __forceinline__ uint32_t high_word_up(double x)
+{
+    const uint64_t v = __builtin_bit_cast(uint64_t, x);
+    return ((uint32_t)(v >> 32) & 0x7fffffffu) + ((uint32_t)v != 0);
+}
+__device__ __forceinline__ int row_exponent_hi(uint32_t hi)
+{
+    return row_exponent(__builtin_bit_cast(double, (uint64_t)hi << 32));
+}
+
 // The four digits of a, given the row exponent e (|a| <= 2^e * 127/128):
 // d[0] is the leading digit.
 __device__ __forceinline__ void slice_value(double a, int e, int8_t *d)
@@ -141,20 +154,6 @@ struct SAccW {
     }
 };
 
-// ---------------------------------------------------------------- ping-pong GEMM
-// acc_l += sum over inner blocks [kb_begin, kb_end) of the kept digit pairs of
-// level l, for the 128 x 128 tile of eight waves of 32 x 64 outputs.  The
-// waves work in two groups half a stage apart.  Group 0 (waves 0-3, rows
-// 0..63) reads a stage's fragments from LDS while group 1 (waves 4-7, rows
-// 64..127) multiplies the previous stage's, then the roles swap; every SIMD
-// holds one wave of each group, so its matrix core is fed by one group while
-// the other waits on LDS.  A workgroup barrier separates the phases.
-//
-// NBUF LDS stage buffers: the blocks of stage s are copied global -> LDS
-// (direct, 16 bytes per lane) in phase 2 (s - NBUF + 1) and must have landed
-// by the end of phase 2s - 1, before group 0 reads them in phase 2s.  Stage
-// s's buffer is refilled with stage s + NBUF in phase 2s + 2, after the
-// barrier that ends group 1's read of stage s (phase 2s + 1).
 // s_waitcnt with vmcnt <= n and the other counters unconstrained (gfx9
 // encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8).
 template <int N>
@@ -162,14 +161,6 @@ __device__ __forceinline__ void wait_vmcnt()
 {
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
-
-// LDS of a GEMM pipeline with NB stage buffers.
-template <class TL, int NB = 3>
-struct SPipe {
-    static_assert(NB >= 3 && NB <= 5, "LDS stage buffers");
-    static constexpr int NBUF = NB;
-    static constexpr int LDS_BYTES = NBUF * TL::STAGE_BYTES;
-};
 
 // s_waitcnt vmcnt(n * PER) for a run-time n in [0, NMAX].
 template <int PER, int NMAX>
@@ -211,19 +202,42 @@ __device__ __forceinline__ void wg_barrier()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <class TL, int NS, int NSTAGEBUF = 3>
-__device__ __forceinline__ void stile_gemm_pp(const SPlanes &A, const SPlanes &B, int m0, int n0,
-                                              int kb_begin, int kb_end, char *lds, SAccW<TL> &acc)
+// ---------------------------------------------------------------- GEMM
+// acc_l += sum over inner blocks [kb_begin, kb_end) of the kept digit pairs of
+// level l, for one tile of four waves of 32 x 64 outputs (two workgroups per
+// CU).  m_rows, n_rows: plane rows of the operands (multiples of 32): blocks of
+// 32 rows beyond them repeat the last one (their outputs are not stored).
+//
+// Three LDS stage buffers, one stage = one 32-byte inner block.  A stage's 26
+// products use 12 fragments (4 of A, 8 of B); a wave reads the next stage's
+// while it multiplies, each into the registers of a fragment that has had its
+// last use, in an order of the pairs in which every fragment is free at least
+// six pairs (12 products) before it is needed again, so a stage never starts
+// with a wait on LDS (A digit, B digit):
+//   (1,4) (2,4) (1,3) (2,3) (3,3)
+//   barrier: every wave holds this stage in registers, the next is in LDS;
+//            this stage's buffer takes the copies of the one three ahead
+//   reads B4 B3   (1,2) (1,1)   A1   (2,2) (2,1)   A2   (3,2) (3,1)   A3
+//                 (4,2)   B2   (4,1)   A4 B1
+// Bound by power: with the matrix cores half busy the clock falls from 2.1 to
+// 1.97 GHz, so what a tile costs beyond its products (padding, LDS reads) counts
+// more than stalls.  As the half-transform: nao 250 450 -> 386 us, nao 1000 159
+// -> 176 TFLOP/s of FP64 equivalent against reading a stage's fragments before
+// its products.
+template <class TL, int NS>
+__device__ __forceinline__ void stile_gemm_w4(const SPlanes &A, const SPlanes &B, int m0, int n0,
+                                              int m_rows, int n_rows, int kb_begin, int kb_end,
+                                              char *lds, SAccW<TL> &acc)
 {
+    static_assert(TL::NWAVE == 4 && NS == 4 && TL::TN == 2, "four waves, 13 digit pairs");
     constexpr int BM = TL::WROWS * 32, BN = TL::WCOLS * 32 * TL::TN, WTN = TL::TN;
+    constexpr int NBUF = 3;
     constexpr int NBA = NS * (BM / 32), NB = NBA + NS * (BN / 32);
     constexpr int NW = TL::NWAVE, PER = (NB + NW - 1) / NW;
-    static_assert(TL::NWAVE == 8 && TL::WROWS == 4 && TL::WCOLS == 2, "two groups of four waves");
-    constexpr int NBUF = SPipe<TL, NSTAGEBUF>::NBUF;
+    static_assert(NB % NW == 0, "whole blocks per wave");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave / TL::WCOLS, wc = wave % TL::WCOLS;
-    const int grp = wave >> 2;
     const int nst = kb_end - kb_begin;
     if (nst <= 0)
         return;
@@ -237,132 +251,13 @@ __device__ __forceinline__ void stile_gemm_pp(const SPlanes &A, const SPlanes &B
 #pragma unroll
     for (int u = 0; u < PER; u++) {
         const int b = wave + u * NW;
-        const int bb = b < NB ? b : 0;
-        const bool isA = bb < NBA;
-        const int bl = isA ? bb : bb - NBA;
-        const int T = isA ? BM : BN;
-        const int p = bl / (T / 32), rh = bl % (T / 32);
-        const SPlanes &op = isA ? A : B;
-        ub[u] = uniform_ptr(op.base + p * op.pstride + (i64)((isA ? m0 : n0) + rh * 32) * kSliceKB);
-        loff[u] = (isA ? 0 : TL::A_BYTES) + p * T * kSliceKB + rh * 32 * kSliceKB;
-    }
-    const i64 akbs = A.kbstride, bkbs = B.kbstride;
-    auto issue = [&](int kb, int buf) {
-#pragma unroll
-        for (int u = 0; u < PER; u++) {
-            const int b = wave + u * NW;
-            if (NB % NW == 0 || b < NB)
-                global_to_lds16(ub[u] + (i64)kb * (b < NBA ? akbs : bkbs) + lane_off,
-                                lds + buf * TL::STAGE_BYTES + loff[u]);
-        }
-    };
-    const int aoff = slds_off(wr * 32 + (lane & 31), lane >> 5);
-    int boff[WTN];
-#pragma unroll
-    for (int t = 0; t < WTN; t++)
-        boff[t] = slds_off((wc * WTN + t) * 32 + (lane & 31), lane >> 5);
-    v4i fa[NS], fb[WTN][NS];
-    auto read = [&](int st) {
-        const char *sa = lds + (st % NBUF) * TL::STAGE_BYTES;
-        const char *sb = sa + TL::A_BYTES;
-#pragma unroll
-        for (int p = 0; p < NS; p++) {
-            fa[p] = *(const v4i *)(sa + p * BM * kSliceKB + aoff);
-#pragma unroll
-            for (int t = 0; t < WTN; t++)
-                fb[t][p] = *(const v4i *)(sb + p * BN * kSliceKB + boff[t]);
-        }
-    };
-    // digit pairs (i + 1, j + 1) with i + j + 2 <= kSliceLevel, into level i + j
-    auto mult = [&]() {
-#pragma unroll
-        for (int i = 0; i < NS; i++)
-#pragma unroll
-            for (int t = 0; t < WTN; t++)
-#pragma unroll
-                for (int j = 0; j < NS; j++)
-                    if (i + j + 2 <= kSliceLevel)
-                        acc.c[t][i + j] = mfma_i8(fa[i], fb[t][j], acc.c[t][i + j]);
-    };
-    // Each group runs its own loop (straight-line bodies, one fragment set
-    // each); the workgroup barriers pair up phase by phase:
-    //   phase 2s      group 0 reads stage s,       group 1 multiplies stage s - 1
-    //   phase 2s + 1  group 0 multiplies stage s,  group 1 reads stage s
-    // Both groups issue their copies of stage s in phase 2 (s - NBUF + 1) and
-    // wait for them at the end of phase 2s - 1, when the copies of the
-    // NBUF - 2 later stages may still be in flight.
-    constexpr int AHEAD = NBUF - 1;
-    for (int s0 = 0; s0 < AHEAD; s0++)
-        if (s0 < nst)
-            issue(kb_begin + s0, s0);
-    wait_vm_stages<PER, NBUF - 2>(min(nst - 1, AHEAD - 1));
-    wg_barrier();
-    if (grp == 0) {
-#pragma clang loop unroll(disable)
-        for (int st = 0; st < nst; st++) {
-            if (st + AHEAD < nst)
-                issue(kb_begin + st + AHEAD, (st + AHEAD) % NBUF);
-            read(st);
-            __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): fragments in registers
-            wg_barrier();
-            mult();
-            // stage st + 1 landed; stages st + 2 .. st + AHEAD may be in flight
-            wait_vm_stages<PER, NBUF - 2>(min(nst - st - 2, AHEAD - 1));
-            wg_barrier();
-        }
-    } else {
-        if (AHEAD < nst)
-            issue(kb_begin + AHEAD, AHEAD % NBUF);
-        wg_barrier();
-#pragma clang loop unroll(disable)
-        for (int st = 0; st < nst; st++) {
-            read(st);
-            __builtin_amdgcn_s_waitcnt(0xC07F);
-            wait_vm_stages<PER, NBUF - 2>(min(nst - st - 2, AHEAD - 1));
-            wg_barrier();
-            if (st + AHEAD + 1 < nst)
-                issue(kb_begin + st + AHEAD + 1, (st + AHEAD + 1) % NBUF);
-            mult();
-            if (st + 1 < nst)
-                wg_barrier();
-        }
-    }
-}
-
-// ---------------------------------------------------------------- four-wave GEMM
-// The same product for a workgroup of (BM/32) x (BN/64) = four waves of
-// 32 x 64 outputs, small enough for two workgroups per CU: while one
-// workgroup waits on LDS, a prologue or its epilogue, the other's products
-// keep the matrix cores busy.  All waves read a stage's fragments, multiply,
-// then meet at one barrier; NBUF LDS stage buffers, stage s copied
-// global -> LDS NBUF - 1 stages ahead.
-template <class TL, int NS, int NBUF>
-__device__ __forceinline__ void stile_gemm_w4(const SPlanes &A, const SPlanes &B, int m0, int n0,
-                                              int kb_begin, int kb_end, char *lds, SAccW<TL> &acc)
-{
-    static_assert(TL::NWAVE == 4, "four waves");
-    constexpr int BM = TL::WROWS * 32, BN = TL::WCOLS * 32 * TL::TN, WTN = TL::TN;
-    constexpr int NBA = NS * (BM / 32), NB = NBA + NS * (BN / 32);
-    constexpr int NW = TL::NWAVE, PER = (NB + NW - 1) / NW;
-    static_assert(NB % NW == 0, "whole blocks per wave");
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wr = wave / TL::WCOLS, wc = wave % TL::WCOLS;
-    const int nst = kb_end - kb_begin;
-    if (nst <= 0)
-        return;
-    const uint32_t lane_off = (lane >> 1) * kSliceKB + (((lane & 1) ^ ((lane >> 4) & 1)) << 4);
-    const int8_t *ub[PER];
-    int loff[PER];
-#pragma unroll
-    for (int u = 0; u < PER; u++) {
-        const int b = wave + u * NW;
         const bool isA = b < NBA;
         const int bl = isA ? b : b - NBA;
         const int T = isA ? BM : BN;
         const int p = bl / (T / 32), rh = bl % (T / 32);
         const SPlanes &op = isA ? A : B;
-        ub[u] = uniform_ptr(op.base + p * op.pstride + (i64)((isA ? m0 : n0) + rh * 32) * kSliceKB);
+        const int row = (isA ? m0 : n0) + rh * 32, last = (isA ? m_rows : n_rows) - 32;
+        ub[u] = uniform_ptr(op.base + p * op.pstride + (i64)(row < last ? row : last) * kSliceKB);
         loff[u] = (isA ? 0 : TL::A_BYTES) + p * T * kSliceKB + rh * 32 * kSliceKB;
     }
     const i64 akbs = A.kbstride, bkbs = B.kbstride;
@@ -376,37 +271,84 @@ __device__ __forceinline__ void stile_gemm_w4(const SPlanes &A, const SPlanes &B
     int boff[WTN];
 #pragma unroll
     for (int t = 0; t < WTN; t++)
-        boff[t] = slds_off((wc * WTN + t) * 32 + (lane & 31), lane >> 5);
-    constexpr int AHEAD = NBUF - 1;
-    for (int s0 = 0; s0 < AHEAD; s0++)
+        boff[t] = TL::A_BYTES + slds_off((wc * WTN + t) * 32 + (lane & 31), lane >> 5);
+    v4i fa[NS], fb[WTN][NS];
+    auto read_a = [&](const char *st, int p) { return *(const v4i *)(st + p * BM * kSliceKB + aoff); };
+    auto read_b = [&](const char *st, int p) {
+#pragma unroll
+        for (int t = 0; t < WTN; t++)
+            fb[t][p] = *(const v4i *)(st + p * BN * kSliceKB + boff[t]);
+    };
+    auto mult = [&](int i, int j) {
+#pragma unroll
+        for (int t = 0; t < WTN; t++)
+            acc.c[t][i + j] = mfma_i8(fa[i], fb[t][j], acc.c[t][i + j]);
+    };
+    for (int s0 = 0; s0 < NBUF; s0++)
         if (s0 < nst)
             issue(kb_begin + s0, s0);
+    wait_vm_stages<PER, NBUF - 1>(min(nst - 1, NBUF - 1));
+    wg_barrier();
+    read_b(lds, 3);
+    read_b(lds, 2);
+    fa[0] = read_a(lds, 0);
+    fa[1] = read_a(lds, 1);
+    fa[2] = read_a(lds, 2);
+    read_b(lds, 1);
+    fa[3] = read_a(lds, 3);
+    read_b(lds, 0);
+    auto head = [&]() {
+        mult(0, 3);
+        mult(1, 3);
+        mult(0, 2);
+        mult(1, 2);
+        mult(2, 2);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    head();
+    int cur = 0;
 #pragma clang loop unroll(disable)
-    for (int st = 0; st < nst; st++) {
-        // stage st landed (this wave's copies), then every wave's (barrier)
-        wait_vm_stages<PER, NBUF - 2>(min(nst - st - 1, AHEAD - 1));
+    for (int st = 0; st + 1 < nst; st++) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0): this stage is in registers
+        wait_vm_stages<PER, 1>(min(nst - st - 2, 1));        // stage st + 1 has landed
         wg_barrier();
-        if (st + AHEAD < nst)
-            issue(kb_begin + st + AHEAD, (st + AHEAD) % NBUF);
-        const char *sa = lds + (st % NBUF) * TL::STAGE_BYTES;
-        const char *sb = sa + TL::A_BYTES;
-        v4i fa[NS], fb[WTN][NS];
-#pragma unroll
-        for (int p = 0; p < NS; p++) {
-            fa[p] = *(const v4i *)(sa + p * BM * kSliceKB + aoff);
-#pragma unroll
-            for (int t = 0; t < WTN; t++)
-                fb[t][p] = *(const v4i *)(sb + p * BN * kSliceKB + boff[t]);
-        }
-#pragma unroll
-        for (int i = 0; i < NS; i++)
-#pragma unroll
-            for (int t = 0; t < WTN; t++)
-#pragma unroll
-                for (int j = 0; j < NS; j++)
-                    if (i + j + 2 <= kSliceLevel)
-                        acc.c[t][i + j] = mfma_i8(fa[i], fb[t][j], acc.c[t][i + j]);
+        if (st + NBUF < nst)
+            issue(kb_begin + st + NBUF, cur);
+        cur = cur == NBUF - 1 ? 0 : cur + 1;
+        const char *nx = lds + cur * TL::STAGE_BYTES;
+        read_b(nx, 3);
+        read_b(nx, 2);
+        __builtin_amdgcn_sched_barrier(0);
+        mult(0, 1);
+        mult(0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        fa[0] = read_a(nx, 0);
+        mult(1, 1);
+        mult(1, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        fa[1] = read_a(nx, 1);
+        mult(2, 1);
+        mult(2, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        fa[2] = read_a(nx, 2);
+        mult(3, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        read_b(nx, 1);
+        mult(3, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        fa[3] = read_a(nx, 3);
+        read_b(nx, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        head();
     }
+    mult(0, 1);
+    mult(0, 0);
+    mult(1, 1);
+    mult(1, 0);
+    mult(2, 1);
+    mult(2, 0);
+    mult(3, 1);
+    mult(3, 0);
 }
 
 // Output coordinates of element e of tile t of this lane.
