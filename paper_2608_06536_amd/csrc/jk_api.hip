@@ -175,7 +175,7 @@ int chunk_slabs_vjp(const jk_problem *p)
 struct VjpPlan {
     int qc, ldw, nsplit_c;
     bool packed;        // JK_B_PACKED: chunks unpacked into o_bu
-    size_t o_cc, o_wdp, o_e, o_part, o_om, o_omx, o_x, o_y, o_pr, o_dcp;
+    size_t o_cc, o_wdp, o_e, o_part, o_om, o_x, o_y, o_pr, o_dcp;
     size_t o_bu, total;
 };
 
@@ -197,7 +197,6 @@ VjpPlan plan_vjp(const jk_problem *p)
     f.o_part = c.take(sizeof(double) * std::max(jk::project_part_doubles((int)nao, (int)naux, (int)(2 * nd)),
                                                 jk::project_part_doubles((int)nao, (int)naux, (int)nd)));
     f.o_om = c.take(sizeof(double) * 2 * nd * naux);
-    f.o_omx = c.take(sizeof(double) * naux * R);
     f.o_x = c.take(sizeof(double) * nd * nao * (size_t)f.ldw);
     f.o_y = c.take(sizeof(double) * nd * nao * (size_t)f.ldw);
     f.o_pr = c.take(sizeof(double) * (size_t)f.qc * nao * 2 * R);
@@ -435,7 +434,6 @@ jk_status vjp_fp64(const jk_problem *p, const double *B, const double *CL, const
     double *E = (double *)(ws + f.o_e);
     double *part = (double *)(ws + f.o_part);
     double *om = (double *)(ws + f.o_om), *g = om + (i64)nd * naux;     // [omega | gamma]
-    double *omx = (double *)(ws + f.o_omx);
     double *Xw = (double *)(ws + f.o_x);
     double *Yw = (double *)(ws + f.o_y);
     double *L = (double *)(ws + f.o_pr);
@@ -456,7 +454,6 @@ jk_status vjp_fp64(const jk_problem *p, const double *B, const double *CL, const
         if (want_db)
             JK_TRY(jk::launch_fold_density(CL, CR, WDp + (i64)nd * npk, nao, nd, r, s));
         JK_TRY(jk::launch_project(B, WDp, part, om, nao, naux, want_db ? 2 * nd : nd, pk, s));
-        JK_TRY(jk::launch_omega_expand(om, omx, naux, nd, r, s));
         if (want_db && pk) {
             Wa = WDp;
             Ea = WDp + (i64)nd * npk;
@@ -495,10 +492,10 @@ jk_status vjp_fp64(const jk_problem *p, const double *B, const double *CL, const
                                              sym ? R : 2 * R, 0, tile, "vjp_half_transform"));
         JK_TRY(hipEventRecord(ev_x, s));         // X, Y of this chunk; D of the last done
         JK_TRY(hipStreamWaitEvent(a, ev_x, 0));
-        JK_TRY(jk::launch_vjp_stage_b_one(1, V, Xw, Cc, omx, L, nao, nd, r, q0, nq * r, f.ldw, has_v,
+        JK_TRY(jk::launch_vjp_stage_b_one(1, V, Xw, Cc, om, L, nao, nd, r, naux, q0, nq * r, f.ldw, has_v,
                                           has_w, a));
         JK_TRY(hipEventRecord(ev_br, a));
-        JK_TRY(jk::launch_vjp_stage_b_one(0, V, Yx, Cc, omx, L, nao, nd, r, q0, nq * r, f.ldw, has_v,
+        JK_TRY(jk::launch_vjp_stage_b_one(0, V, Yx, Cc, om, L, nao, nd, r, naux, q0, nq * r, f.ldw, has_v,
                                           has_w, s));
         JK_TRY(hipStreamWaitEvent(s, ev_br, 0));
         if (want_dc)

@@ -78,15 +78,10 @@ hipError_t launch_sum_splits_sym(const double *part, double *K, int nao, int nd,
                                  hipStream_t s);
 
 // derivative (jk_vjp.hip)
-hipError_t launch_omega_expand(const double *om, double *omx, int naux, int nd, int r,
-                               hipStream_t s);
-// One of the two stage-B products: which = 0 gives P' (Zw = Y_ws), 1 gives R' (Zw = X_ws).
+// omega in om[k][Q]
 hipError_t launch_vjp_stage_b_one(int which, const double *V, const double *Zw, const double *Cc,
-                                  const double *omx, double *L, int nao, int nd, int r, int q0,
-                                  int nj, int ldw, int has_v, int has_w, hipStream_t s);
-hipError_t launch_vjp_stage_b(const double *V, const double *Xw, const double *Yw,
-                              const double *Cc, const double *omx, double *L, int nao, int nd,
-                              int r, int q0, int nj, int ldw, int has_v, int has_w, hipStream_t s);
+                                  const double *om, double *L, int nao, int nd, int r, int naux,
+                                  int q0, int nj, int ldw, int has_v, int has_w, hipStream_t s);
 int vjp_stage_c_nsplit(int nao, int R, int qc);
 hipError_t launch_vjp_stage_c(const double *B, const double *L, double *dCp, int nao, int R,
                               int q0, int nq, int nsplit, int accumulate, hipStream_t s);

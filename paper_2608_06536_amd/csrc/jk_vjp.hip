@@ -19,8 +19,10 @@
 // Each slab slot ql of the chunk owns one row-major block
 //     L[ql][m][0:2R] = [ P' | R' ]      (column c = k*r + i per part)
 // Stage C reads it whole; stage D is two products, C_R R'^T then P' C_L^T,
-// with C_L and C_R read from Cc.  Cc[n][c] is [C_L | C_R] with c < 2R;
-// omx[Q][c] = omega_{c / r, Q}, c < R.
+// with C_L and C_R read from Cc.  Cc[n][c] is [C_L | C_R] with c < 2R; om[k][Q]
+// = omega_kQ.
+#include <type_traits>
+
 #include "f64_core.hpp"
 #include "f64_mfma16.hpp"
 #include "jk_kernels.hpp"
@@ -29,40 +31,44 @@
 namespace jk {
 
 namespace {
-// 128 x 64 workgroup tiles of four 64 x 32 wave tiles on the 16 x 16 x 4
-// engine, three workgroups per CU (52 KB of dynamic LDS each).
-constexpr int kTM = 128, kTN = 64;
-typedef Tile16<kTM, kTN, 64, 32, 16> TileV;
-} // namespace
-
-// omx[Q][c] = om[c / r][Q], c < R.
-__global__ void __launch_bounds__(256) k_omega_expand(const double *__restrict__ om,
-                                                      double *__restrict__ omx, int naux, int nd,
-                                                      int r)
+// Tile shape of a product with rows x cols outputs (f64_mfma16.hpp): at nao 257,
+// six densities of rank 25, stages B, C and D take 1116, 1089 and 1262 us with
+// 128 x 64 tiles, 843, 849 and 980 with 96 x 64; at nao 500, eight of rank 40,
+// 10.5, 11.8 and 10.2 ms and, with 128 x 128, 9.9, 11.2 and 9.5.  Up to nao 256
+// the 128 x 128 tile, two workgroups per CU, hides too little of the short inner
+// depths.
+int vjp_shape(int nao, i64 rows, i64 cols)
 {
-    const int R = nd * r;
-    const i64 total = (i64)naux * R;
-    for (i64 e = (i64)blockIdx.x * 256 + threadIdx.x; e < total; e += (i64)gridDim.x * 256) {
-        int q = (int)(e / R), c = (int)(e % R);
-        omx[e] = om[(i64)(c / r) * naux + q];
+    return pick_shape(rows, cols, nao <= 256 ? kS128x64 : kS128x128);
+}
+// f with the shape as a constant.
+template <class F>
+hipError_t with_shape(int shape, F &&f)
+{
+    switch (shape) {
+    case kS128x128: return f(std::integral_constant<int, kS128x128>());
+    case kS128x64: return f(std::integral_constant<int, kS128x64>());
+    case kS96x64: return f(std::integral_constant<int, kS96x64>());
+    case kS80x64: return f(std::integral_constant<int, kS80x64>());
+    default: return f(std::integral_constant<int, kS64x64>());
     }
 }
+} // namespace
 
 // ------------------------------------------------------------------ stage B
 // WHICH = 0: L[ql][m][     k*r+i] = sum_n V_k[m][n] Y_ws[k][n][ql*r+i] + om * C_R
 // WHICH = 1: L[ql][m][R  + k*r+i] = sum_n V_k[n][m] X_ws[k][n][ql*r+i] + om * C_L
 // (om = omega_{k, q0+ql}; products skipped when has_v == 0, omega terms when
 // has_w == 0).  grid.x = nd * nmt * njt (XCD-swizzled).
-template <int WHICH>
-__global__ void __launch_bounds__(256, 3) k_vjp_stage_b(const double *__restrict__ V,
-                                                        const double *__restrict__ Zw,
-                                                        const double *__restrict__ Cc,
-                                                        const double *__restrict__ omx,
-                                                        double *__restrict__ L, int nao, int nd,
-                                                        int r, int q0, int nj, int ldw, int has_v,
-                                                        int has_w)
+template <int WHICH, int SHAPE>
+__global__ void __launch_bounds__(256, shape_wgs(SHAPE))
+    k_vjp_stage_b(const double *__restrict__ V, const double *__restrict__ Zw,
+                  const double *__restrict__ Cc, const double *__restrict__ om,
+                  double *__restrict__ L, int nao, int nd, int r, int naux, int q0, int nj, int ldw,
+                  int has_v, int has_w)
 {
-    typedef TileV TL;
+    typedef typename ShapeTile<SHAPE>::type TL;
+    constexpr int kTM = TL::BM, kTN = TL::BN;
     extern __shared__ double lds[];
     const int R = nd * r, R2 = 2 * R;
     const int nmt = (nao + kTM - 1) / kTM, njt = (nj + kTN - 1) / kTN;
@@ -86,7 +92,7 @@ __global__ void __launch_bounds__(256, 3) k_vjp_stage_b(const double *__restrict
     }
     // Output (m, j) goes to L at column block j: slot ql = j / r, column
     // c = k r + j % r, element ((ql nao + m) 2R + part + c); the omega term
-    // adds omx[q0 + ql][c] * Cc[m][c or R + c].  A lane holds TL::NB columns
+    // adds om[k][q0 + ql] * Cc[m][c or R + c].  A lane holds TL::NB columns
     // and 4 TL::MA rows, decoded once each.
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wr = wave / TL::WCOLS, wc = wave % TL::WCOLS;
@@ -104,7 +110,7 @@ __global__ void __launch_bounds__(256, 3) k_vjp_stage_b(const double *__restrict
         const int c = k * r + i;
         col_l[jj] = (i64)ql * nao * R2 + (WHICH == 0 ? 0 : R) + c;
         col_cc[jj] = WHICH == 0 ? R + c : c;
-        col_om[jj] = (has_w && col_ok[jj]) ? omx[(i64)(q0 + ql) * R + c] : 0.0;
+        col_om[jj] = (has_w && col_ok[jj]) ? om[(i64)k * naux + q0 + ql] : 0.0;
     }
 #pragma unroll
     for (int i = 0; i < TL::MA; i++)
@@ -127,13 +133,13 @@ __global__ void __launch_bounds__(256, 3) k_vjp_stage_b(const double *__restrict
 // ------------------------------------------------------------------ stage C
 // dCp[sp][m][c] (+)= sum_{ql in split sp} sum_n B^{q0+ql}[m][n] L[ql][n][c], c < 2R.
 // grid.x = nsplit * nmt * nct.
-__global__ void __launch_bounds__(256, 3) k_vjp_stage_c(const double *__restrict__ B,
-                                                        const double *__restrict__ L,
-                                                        double *__restrict__ dCp, int nao, int R,
-                                                        int q0, int nq, int nsplit, int qlen,
-                                                        int accumulate)
+template <int SHAPE>
+__global__ void __launch_bounds__(256, shape_wgs(SHAPE))
+    k_vjp_stage_c(const double *__restrict__ B, const double *__restrict__ L, double *__restrict__ dCp,
+                  int nao, int R, int q0, int nq, int nsplit, int qlen, int accumulate)
 {
-    typedef TileV TL;
+    typedef typename ShapeTile<SHAPE>::type TL;
+    constexpr int kTM = TL::BM, kTN = TL::BN;
     extern __shared__ double lds[];
     const int R2 = 2 * R;
     const int nmt = (nao + kTM - 1) / kTM, nct = (R2 + kTN - 1) / kTN;
@@ -153,23 +159,27 @@ __global__ void __launch_bounds__(256, 3) k_vjp_stage_c(const double *__restrict
     tile_update16(acc, mb * kTM, cb * kTN, dCp + (i64)sp * nao * R2, R2, nao, R2, accumulate, 1.0);
 }
 
-// dCL[k][m][i] = sum_sp dCp[sp][m][k*r+i];  dCR[k][m][i] = sum_sp dCp[sp][m][R+k*r+i]
+// dCL[k][m][i] = sum_sp dCp[sp][m][k*r+i];  dCR[k][m][i] = sum_sp dCp[sp][m][R+k*r+i],
+// 64 elements per workgroup, wave w taking the splits w, w + 4, ... (one thread
+// per element with up to 64 loads in a row took 15 us at nao 48, 30 at 257).
 __global__ void __launch_bounds__(256) k_vjp_dc_finish(const double *__restrict__ dCp,
                                                        double *__restrict__ dCL,
                                                        double *__restrict__ dCR, int nao, int nd,
                                                        int r, int nsplit)
 {
+    __shared__ double red[4][64];
     const int R = nd * r, R2 = 2 * R;
     const i64 total = (i64)nao * R2;
-    for (i64 e = (i64)blockIdx.x * 256 + threadIdx.x; e < total; e += (i64)gridDim.x * 256) {
-        int m = (int)(e / R2), c = (int)(e % R2);
-        double s = 0.0;
-        for (int sp = 0; sp < nsplit; sp++)
-            s += dCp[(i64)sp * total + e];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const i64 e = (i64)blockIdx.x * 64 + lane;
+    red[w][lane] = e < total ? sum_part(dCp + e, total, nsplit, w) : 0.0;
+    __syncthreads();
+    if (w == 0 && e < total) {
+        const int m = (int)(e / R2), c = (int)(e % R2);
         double *dst = c < R ? dCL : dCR;
-        int cc = c < R ? c : c - R;
-        int k = cc / r, i = cc % r;
-        dst[((i64)k * nao + m) * r + i] = s;
+        const int cc = c < R ? c : c - R;
+        const int k = cc / r, i = cc % r;
+        dst[((i64)k * nao + m) * r + i] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
     }
 }
 
@@ -207,12 +217,13 @@ __global__ void __launch_bounds__(256) k_vjp_e_matrix(const double *__restrict__
 // dB[q0+ql][a][b] = sum_{c<R} C_R[a][c] R'[ql][b][c] + sum_{c<R} P'[ql][a][c] C_L[b][c]
 // (C_R[a][c] = Cc[a][R + c], C_L[b][c] = Cc[b][c]), the two sums in this order.
 // grid.x = nq * nmt * nnt (XCD-swizzled).
-__global__ void __launch_bounds__(256, 3) k_vjp_stage_d(const double *__restrict__ L,
-                                                        const double *__restrict__ Cc,
-                                                        double *__restrict__ dB, int nao, int R,
-                                                        int q0, int nq)
+template <int SHAPE>
+__global__ void __launch_bounds__(256, shape_wgs(SHAPE))
+    k_vjp_stage_d(const double *__restrict__ L, const double *__restrict__ Cc, double *__restrict__ dB,
+                  int nao, int R, int q0, int nq)
 {
-    typedef TileV TL;
+    typedef typename ShapeTile<SHAPE>::type TL;
+    constexpr int kTM = TL::BM, kTN = TL::BN;
     extern __shared__ double lds[];
     const int R2 = 2 * R;
     const int nmt = (nao + kTM - 1) / kTM, nnt = (nao + kTN - 1) / kTN;
@@ -286,15 +297,15 @@ __global__ void __launch_bounds__(256) k_unpack_slabs(const double *__restrict__
         }
 }
 
-// Upper-triangle tiles of the 128 x 64 grid: row tile ab covers column tiles
-// 2 ab .. nnt - 1 (the first that meets columns >= its first row).
-__device__ __forceinline__ int tri_first(int ab) { return ab * kTM / kTN; }
-__host__ __device__ inline int vjp_tri_tiles(int nao)
+// Upper-triangle tiles of the bm x bn grid: row tile ab covers the column tiles
+// from the first that meets columns >= its first row.
+__host__ __device__ constexpr int tri_first(int ab, int bm, int bn) { return ab * bm / bn; }
+inline int vjp_tri_tiles(int nao, int bm, int bn)
 {
-    const int nmt = (nao + kTM - 1) / kTM, nnt = (nao + kTN - 1) / kTN;
+    const int nmt = (nao + bm - 1) / bm, nnt = (nao + bn - 1) / bn;
     int n = 0;
     for (int ab = 0; ab < nmt; ab++)
-        n += ab * kTM / kTN < nnt ? nnt - ab * kTM / kTN : 0;
+        n += nnt - tri_first(ab, bm, bn);
     return n;
 }
 
@@ -304,24 +315,25 @@ __host__ __device__ inline int vjp_tri_tiles(int nao)
 // A M^T + M A^T is the product [A | M] [M | A]^T of depth 4R: the two
 // products of the full stage D, then R' C_R^T + C_L P'^T, over the
 // upper-triangle tiles only (the flops of the full dB), written to the packed
-// positions; the diagonal is halved.  grid.x = nq * vjp_tri_tiles(nao).
-__global__ void __launch_bounds__(256, 2) k_vjp_stage_d_packed(const double *__restrict__ L,
-                                                               const double *__restrict__ Cc,
-                                                               double *__restrict__ dB, int nao,
-                                                               int R, int q0, int nq, int ntri)
+// positions; the diagonal is halved.  grid.x = nq * vjp_tri_tiles.
+template <int SHAPE>
+__global__ void __launch_bounds__(256, 2)
+    k_vjp_stage_d_packed(const double *__restrict__ L, const double *__restrict__ Cc,
+                         double *__restrict__ dB, int nao, int R, int q0, int nq, int ntri)
 {
-    typedef TileV TL;
+    typedef typename ShapeTile<SHAPE>::type TL;
+    constexpr int kTM = TL::BM, kTN = TL::BN;
     extern __shared__ double lds[];
     const int R2 = 2 * R;
     const int t = xcd_swizzle(blockIdx.x, nq * ntri);
     const int ql = t / ntri;
     const int nnt = (nao + kTN - 1) / kTN;
     int tt = t % ntri, ab = 0;
-    while (tt >= nnt - tri_first(ab)) {
-        tt -= nnt - tri_first(ab);
+    while (tt >= nnt - tri_first(ab, kTM, kTN)) {
+        tt -= nnt - tri_first(ab, kTM, kTN);
         ab++;
     }
-    const int bb = tri_first(ab) + tt;
+    const int bb = tri_first(ab, kTM, kTN) + tt;
     const double *Lq = L + (i64)ql * nao * R2;
     Acc16<TL> acc;
     acc.zero();
@@ -434,96 +446,52 @@ __global__ void __launch_bounds__(256) k_vjp_db_affine(const double *__restrict_
 
 static inline int cdiv(i64 a, i64 b) { return (int)((a + b - 1) / b); }
 
-static inline int grid_1d(i64 n)
-{
-    int g = cdiv(n, 256);
-    return g > 65535 ? 65535 : (g < 1 ? 1 : g);
-}
-
-hipError_t launch_omega_expand(const double *om, double *omx, int naux, int nd, int r,
-                               hipStream_t s)
-{
-    {
-        ProfScope ps_("omega_expand", s);
-        hipLaunchKernelGGL(k_omega_expand, dim3(grid_1d((i64)naux * nd * r)), dim3(256), 0, s, om, omx,
-                       naux, nd, r);
-    }
-    return hipGetLastError();
-}
-
 hipError_t launch_vjp_stage_b_one(int which, const double *V, const double *Zw, const double *Cc,
-                                  const double *omx, double *L, int nao, int nd, int r, int q0,
-                                  int nj, int ldw, int has_v, int has_w, hipStream_t s)
+                                  const double *om, double *L, int nao, int nd, int r, int naux,
+                                  int q0, int nj, int ldw, int has_v, int has_w, hipStream_t s)
 {
-    const int nmt = cdiv(nao, kTM), njt = cdiv(nj, kTN);
-    dim3 grid(nd * nmt * njt);
-    const int lds = (int)sizeof(double) * TileV::LDS_DOUBLES;
-    const void *fn = which ? (const void *)k_vjp_stage_b<1> : (const void *)k_vjp_stage_b<0>;
-    hipError_t e = set_dynamic_lds(fn, lds);
-    if (e != hipSuccess)
-        return e;
-    if (which) {
-        ProfScope ps_("vjp_stage_b_r", s);
-        hipLaunchKernelGGL(k_vjp_stage_b<1>, grid, dim3(TileV::NTHR), lds, s, V, Zw, Cc, omx, L, nao, nd,
-                           r, q0, nj, ldw, has_v, has_w);
-    } else {
-        ProfScope ps_("vjp_stage_b_p", s);
-        hipLaunchKernelGGL(k_vjp_stage_b<0>, grid, dim3(TileV::NTHR), lds, s, V, Zw, Cc, omx, L, nao, nd,
-                           r, q0, nj, ldw, has_v, has_w);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_vjp_stage_b(const double *V, const double *Xw, const double *Yw,
-                              const double *Cc, const double *omx, double *L, int nao, int nd,
-                              int r, int q0, int nj, int ldw, int has_v, int has_w, hipStream_t s)
-{
-    const int nmt = cdiv(nao, kTM), njt = cdiv(nj, kTN);
-    dim3 grid(nd * nmt * njt);
-    const int lds = (int)sizeof(double) * TileV::LDS_DOUBLES;
-    hipError_t e = set_dynamic_lds((const void *)k_vjp_stage_b<0>, lds);
-    if (e == hipSuccess)
-        e = set_dynamic_lds((const void *)k_vjp_stage_b<1>, lds);
-    if (e != hipSuccess)
-        return e;
-    {
-        ProfScope ps_("vjp_stage_b_p", s);
-        hipLaunchKernelGGL(k_vjp_stage_b<0>, grid, dim3(TileV::NTHR), lds, s, V, Yw, Cc, omx, L, nao, nd,
-                           r, q0, nj, ldw, has_v, has_w);
-    }
-    e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    {
-        ProfScope ps_("vjp_stage_b_r", s);
-        hipLaunchKernelGGL(k_vjp_stage_b<1>, grid, dim3(TileV::NTHR), lds, s, V, Xw, Cc, omx, L, nao, nd,
-                           r, q0, nj, ldw, has_v, has_w);
-    }
-    return hipGetLastError();
+    return with_shape(vjp_shape(nao, nao, nj), [&](auto sh) -> hipError_t {
+        constexpr int SHAPE = decltype(sh)::value;
+        typedef typename ShapeTile<SHAPE>::type TL;
+        const dim3 grid(nd * cdiv(nao, TL::BM) * cdiv(nj, TL::BN));
+        const int lds = (int)sizeof(double) * TL::LDS_DOUBLES;
+        auto go = [&](auto fn, const char *name) -> hipError_t {
+            hipError_t e = set_dynamic_lds((const void *)fn, lds);
+            if (e != hipSuccess)
+                return e;
+            ProfScope ps_(name, s);
+            hipLaunchKernelGGL(fn, grid, dim3(TL::NTHR), lds, s, V, Zw, Cc, om, L, nao, nd, r, naux, q0,
+                               nj, ldw, has_v, has_w);
+            return hipGetLastError();
+        };
+        return which ? go(k_vjp_stage_b<1, SHAPE>, "vjp_stage_b_r")
+                     : go(k_vjp_stage_b<0, SHAPE>, "vjp_stage_b_p");
+    });
 }
 
 int vjp_stage_c_nsplit(int nao, int R, int qc)
 {
-    const int tiles = cdiv(nao, kTM) * cdiv(2 * (i64)R, kTN);
-    // three workgroups per CU
-    return pick_split_slots(tiles, qc < 64 ? qc : 64, device_slots() / 2 * 3);
+    const int sh = vjp_shape(nao, nao, 2 * (i64)R);
+    const int tiles = cdiv(nao, shape_bm(sh)) * cdiv(2 * (i64)R, shape_bn(sh));
+    return pick_split_slots(tiles, qc < 64 ? qc : 64, device_slots() / 2 * shape_wgs(sh));
 }
 
 hipError_t launch_vjp_stage_c(const double *B, const double *L, double *dCp, int nao, int R,
                               int q0, int nq, int nsplit, int accumulate, hipStream_t s)
 {
-    const int nmt = cdiv(nao, kTM), nct = cdiv(2 * (i64)R, kTN);
-    const int qlen = cdiv(nq, nsplit);
-    const int lds = (int)sizeof(double) * TileV::LDS_DOUBLES;
-    hipError_t e = set_dynamic_lds((const void *)k_vjp_stage_c, lds);
-    if (e != hipSuccess)
-        return e;
-    {
+    return with_shape(vjp_shape(nao, nao, 2 * (i64)R), [&](auto sh) -> hipError_t {
+        constexpr int SHAPE = decltype(sh)::value;
+        typedef typename ShapeTile<SHAPE>::type TL;
+        const int lds = (int)sizeof(double) * TL::LDS_DOUBLES;
+        hipError_t e = set_dynamic_lds((const void *)k_vjp_stage_c<SHAPE>, lds);
+        if (e != hipSuccess)
+            return e;
         ProfScope ps_("vjp_stage_c", s);
-        hipLaunchKernelGGL(k_vjp_stage_c, dim3(nsplit * nmt * nct), dim3(TileV::NTHR), lds, s, B, L, dCp,
-                           nao, R, q0, nq, nsplit, qlen, accumulate);
-    }
-    return hipGetLastError();
+        hipLaunchKernelGGL(k_vjp_stage_c<SHAPE>,
+                           dim3(nsplit * cdiv(nao, TL::BM) * cdiv(2 * (i64)R, TL::BN)), dim3(TL::NTHR),
+                           lds, s, B, L, dCp, nao, R, q0, nq, nsplit, cdiv(nq, nsplit), accumulate);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_vjp_dc_finish(const double *dCp, double *dCL, double *dCR, int nao, int nd,
@@ -531,7 +499,7 @@ hipError_t launch_vjp_dc_finish(const double *dCp, double *dCL, double *dCR, int
 {
     {
         ProfScope ps_("vjp_dc_finish", s);
-        hipLaunchKernelGGL(k_vjp_dc_finish, dim3(grid_1d((i64)nao * 2 * nd * r)), dim3(256), 0, s, dCp,
+        hipLaunchKernelGGL(k_vjp_dc_finish, dim3(cdiv((i64)nao * 2 * nd * r, 64)), dim3(256), 0, s, dCp,
                            dCL, dCR, nao, nd, r, nsplit);
     }
     return hipGetLastError();
@@ -551,16 +519,18 @@ hipError_t launch_vjp_e_matrix(const double *CL, const double *CR, double *E, in
 hipError_t launch_vjp_stage_d(const double *L, const double *Cc, double *dB, int nao, int R,
                               int q0, int nq, hipStream_t s)
 {
-    const int lds = (int)sizeof(double) * TileV::LDS_DOUBLES;
-    hipError_t e = set_dynamic_lds((const void *)k_vjp_stage_d, lds);
-    if (e != hipSuccess)
-        return e;
-    {
+    return with_shape(vjp_shape(nao, nao, nao), [&](auto sh) -> hipError_t {
+        constexpr int SHAPE = decltype(sh)::value;
+        typedef typename ShapeTile<SHAPE>::type TL;
+        const int lds = (int)sizeof(double) * TL::LDS_DOUBLES;
+        hipError_t e = set_dynamic_lds((const void *)k_vjp_stage_d<SHAPE>, lds);
+        if (e != hipSuccess)
+            return e;
         ProfScope ps_("vjp_stage_d", s);
-        const dim3 g(nq * cdiv(nao, kTM) * cdiv(nao, kTN));
-        hipLaunchKernelGGL(k_vjp_stage_d, g, dim3(TileV::NTHR), lds, s, L, Cc, dB, nao, R, q0, nq);
-    }
-    return hipGetLastError();
+        hipLaunchKernelGGL(k_vjp_stage_d<SHAPE>, dim3(nq * cdiv(nao, TL::BM) * cdiv(nao, TL::BN)),
+                           dim3(TL::NTHR), lds, s, L, Cc, dB, nao, R, q0, nq);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_unpack_slabs(const double *Bp, double *out, int nao, int q0, int nq,
@@ -577,17 +547,20 @@ hipError_t launch_unpack_slabs(const double *Bp, double *out, int nao, int q0, i
 hipError_t launch_vjp_stage_d_packed(const double *L, const double *Cc, double *dB, int nao, int R,
                                      int q0, int nq, hipStream_t s)
 {
-    const int lds = (int)sizeof(double) * TileV::LDS_DOUBLES;
-    hipError_t e = set_dynamic_lds((const void *)k_vjp_stage_d_packed, lds);
-    if (e != hipSuccess)
-        return e;
-    const int ntri = vjp_tri_tiles(nao);
-    {
+    // two pipelines in one kernel: 128 x 128 tiles would spill registers
+    return with_shape(pick_shape(nao, nao, kS128x64), [&](auto sh) -> hipError_t {
+        constexpr int SHAPE = decltype(sh)::value == kS128x128 ? kS128x64 : decltype(sh)::value;
+        typedef typename ShapeTile<SHAPE>::type TL;
+        const int lds = (int)sizeof(double) * TL::LDS_DOUBLES;
+        hipError_t e = set_dynamic_lds((const void *)k_vjp_stage_d_packed<SHAPE>, lds);
+        if (e != hipSuccess)
+            return e;
+        const int ntri = vjp_tri_tiles(nao, TL::BM, TL::BN);
         ProfScope ps_("vjp_stage_d", s);
-        hipLaunchKernelGGL(k_vjp_stage_d_packed, dim3(nq * ntri), dim3(TileV::NTHR), lds, s, L, Cc, dB,
+        hipLaunchKernelGGL(k_vjp_stage_d_packed<SHAPE>, dim3(nq * ntri), dim3(TL::NTHR), lds, s, L, Cc, dB,
                            nao, R, q0, nq, ntri);
-    }
-    return hipGetLastError();
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_vjp_db_affine(const double *gam, const double *om, const double *W,
