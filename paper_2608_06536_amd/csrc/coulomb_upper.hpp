@@ -77,6 +77,35 @@ __device__ inline void fold_density_tile(const double *__restrict__ CL, const do
     });
 }
 
+// E[k][a][b] = D_k[a][b] - 2 D_k[b][a], D_k = CL_k CR_k^T (the derivative's affine
+// term): two products per 64 x 64 tile, sum_i CL[a][i] CR[b][i] - 2 sum_i
+// CR[a][i] CL[b][i].
+__device__ inline void e_matrix_tile(const double *__restrict__ CL, const double *__restrict__ CR,
+                                     double *__restrict__ E, int nao, int r, int tile, double *lds)
+{
+    typedef TileDensity TL;
+    const int nt = cdiv_i(nao, 64);
+    const int k = tile / (nt * nt), rem = tile % (nt * nt);
+    const int mb = rem / nt, nb = rem % nt;
+    OpKC l{CL + (i64)k * nao * r, r, nao, r};
+    OpKC q{CR + (i64)k * nao * r, r, nao, r};
+    Acc<TL> d, dt;
+    d.zero();
+    dt.zero();
+    tile_gemm<TL>(l, q, mb * 64, nb * 64, 0, r, lds, d);
+    tile_gemm<TL>(q, l, mb * 64, nb * 64, 0, r, lds, dt);
+#pragma unroll
+    for (int i = 0; i < TL::MA; i++)
+#pragma unroll
+        for (int j = 0; j < TL::NB; j++)
+            d.c[i][j] -= 2.0 * dt.c[i][j];
+    double *Ek = E + (i64)k * nao * nao;
+    tile_foreach(d, mb * 64, nb * 64, [&](int m, int n, double v) {
+        if (m < nao && n < nao)
+            Ek[(i64)m * nao + n] = v;
+    });
+}
+
 // S_k from a given matrix A_k (a cotangent, or D_k): one 32 x 32 tile pair
 // (bi <= bj) through LDS, so that the tile and its mirror image are both read
 // as rows.  256 threads; T is 32 x 33 doubles.
@@ -347,11 +376,12 @@ inline int cu_tiles(int nao, int nd, int NK, int runs)
 // NK densities of group kg: wave w takes 64 NP positions and the slabs of one
 // slice, 16 loads in flight per lane; the slices' sums meet in LDS (red: 8
 // x NK x 64 doubles, a run of 64 positions at a time) and each is written at
-// (m, n) and (n, m).
+// (m, n) and (n, m).  g's first row is density kfirst.
 template <int NK, int NP>
 __device__ __forceinline__ void coulomb_tile(const double *__restrict__ B, const double *__restrict__ g,
                                     double *__restrict__ J, int nao, int naux, int nd, int packed,
-                                    int tile, double *red, double scale = 1.0, int accumulate = 0)
+                                    int tile, double *red, double scale = 1.0, int accumulate = 0,
+                                    int kfirst = 0)
 {
     constexpr int U = 16 / NP;
     const int lg = cu_slices_log2(nao), SL = 1 << lg, P = (512 >> lg) * NP;
@@ -381,7 +411,7 @@ __device__ __forceinline__ void coulomb_tile(const double *__restrict__ B, const
     const double *gk[NK];
 #pragma unroll
     for (int k = 0; k < NK; k++)
-        gk[k] = g + (i64)(k0 + k < nd ? k0 + k : nd - 1) * naux;
+        gk[k] = g + (i64)((k0 + k < nd ? k0 + k : nd - 1) - kfirst) * naux;
     double a[NP][NK];
 #pragma unroll
     for (int j = 0; j < NP; j++)

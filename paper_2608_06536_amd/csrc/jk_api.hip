@@ -338,17 +338,19 @@ struct BuildOut {
     double cj = 0.0;
 };
 
-// The Coulomb part: gamma_kQ = <D_k, B^Q> in FP64 (D folded onto the upper
-// triangle), then out (+)= scale sum_Q gamma_kQ B^Q.
-jk_status coulomb_part(const FwdPlan &f, int nao, int naux, int nd, int r, const double *B,
-                       const double *CL, const double *CR, double *out, double scale,
-                       int accumulate, char *ws, hipStream_t s)
+// The Coulomb part after launch_prep folded the densities: gamma_kQ = <D_k, B^Q>
+// in FP64, then out (+)= scale sum_Q gamma_kQ B^Q.
+jk_status coulomb_part(const FwdPlan &f, int nao, int naux, int nd, const double *B, double *out,
+                       double scale, int accumulate, char *ws, hipStream_t s)
 {
-    double *S = (double *)(ws + f.o_s);
-    double *g = (double *)(ws + f.o_g);
-    JK_TRY(jk::launch_fold_density(CL, CR, S, nao, nd, r, s));
-    JK_TRY(jk::launch_project(B, S, (double *)(ws + f.o_part), g, nao, naux, nd, f.packed, s));
-    JK_TRY(jk::launch_coulomb(B, g, out, nao, naux, nd, f.packed, s, scale, accumulate));
+    const double *S = (const double *)(ws + f.o_s);
+    double *part = (double *)(ws + f.o_part), *g = (double *)(ws + f.o_g);
+    const bool sums = jk::coulomb_sums_gamma(nao, naux, nd);
+    JK_TRY(jk::launch_project(B, S, part, g, nao, naux, nd, f.packed, s, !sums));
+    if (sums)
+        JK_TRY(jk::launch_coulomb_sum(B, part, out, nao, naux, nd, f.packed, s, scale, accumulate));
+    else
+        JK_TRY(jk::launch_coulomb(B, g, out, nao, naux, nd, f.packed, s, scale, accumulate));
     return JK_OK;
 }
 
@@ -367,12 +369,16 @@ jk_status build_fp64(const jk_problem *p, const double *B, const KSeg *seg, int 
     double *Xw = (double *)(ws + f.o_x);
     double *Yw = (double *)(ws + f.o_y);
 
-    if (!fused && (w & JK_WANT_J)) {
-        jk_status st = coulomb_part(f, nao, naux, nd, r, B, CL, CR, o.J, 1.0, 0, ws, s);
+    const bool want_k = fused ? nseg > 0 : (w & JK_WANT_K) != 0;
+    const bool want_j = fused ? o.cj != 0.0 || !want_k : (w & JK_WANT_J) != 0;
+    JK_TRY(jk::launch_prep({CL, CR, want_k ? Cc : nullptr, want_j ? (double *)(ws + f.o_s) : nullptr, nullptr,
+                            nullptr, nullptr, nao, nd, r},
+                           s));
+    if (!fused && want_j) {
+        jk_status st = coulomb_part(f, nao, naux, nd, B, o.J, 1.0, 0, ws, s);
         if (st != JK_OK)
             return st;
     }
-    const bool want_k = fused ? nseg > 0 : (w & JK_WANT_K) != 0;
     if (want_k) {
         // K accumulates over the Q-chunks of every segment in nsplit partial
         // buffers (or in the output itself when nsplit == 1), summed in fixed
@@ -383,7 +389,6 @@ jk_status build_fp64(const jk_problem *p, const double *B, const KSeg *seg, int 
         const int ns = sym ? f.nsplit_sym : f.nsplit;
         double *Kp = ns > 1 ? (double *)(ws + f.o_kp) : Kout;
         double *Yx = sym ? Xw : Yw;
-        JK_TRY(jk::launch_pack_c(CL, CR, Cc, nao, nd, r, s));
         bool first = true;
         for (int sgi = 0; sgi < nseg; sgi++) {
             const KSeg &sg = seg[sgi];
@@ -404,11 +409,10 @@ jk_status build_fp64(const jk_problem *p, const double *B, const KSeg *seg, int 
         else if (ns > 1)
             JK_TRY(jk::launch_sum_splits(Kp, Kout, (i64)nd * npos, ns, s));
     }
-    if (fused && (o.cj != 0.0 || !want_k)) {
+    if (fused && want_j) {
         // F (+)= cj J (J is symmetric, so the order against the mirror does
         // not matter); with no exchange term this writes F = cj J.
-        jk_status st = coulomb_part(f, nao, naux, nd, r, B, CL, CR, o.F, o.cj, want_k ? 1 : 0, ws,
-                                    s);
+        jk_status st = coulomb_part(f, nao, naux, nd, B, o.F, o.cj, want_k ? 1 : 0, ws, s);
         if (st != JK_OK)
             return st;
     }
@@ -443,25 +447,17 @@ jk_status vjp_fp64(const jk_problem *p, const double *B, const double *CL, const
     const bool sym = CL == CR;
     double *Yx = sym ? Xw : Yw;
 
-    JK_TRY(jk::launch_pack_c(CL, CR, Cc, nao, nd, r, s));
     // omega_kQ = <W_k, B^Q>; for dB also gamma_kQ = <D_k, B^Q>, in one pass over
     // B, and E_k = D_k - 2 D_k^T.  On the packed positions E folds to -(D_k +
     // D_k^T), the folded density itself with its sign changed.
-    const double *Wa = W, *Ea = E;
-    double esign = 1.0;
-    if (has_w) {
-        JK_TRY(jk::launch_sym_pack(W, WDp, nao, nd, s));
-        if (want_db)
-            JK_TRY(jk::launch_fold_density(CL, CR, WDp + (i64)nd * npk, nao, nd, r, s));
+    const bool affine = has_w && want_db;
+    JK_TRY(jk::launch_prep({CL, CR, Cc, affine ? WDp + (i64)nd * npk : nullptr, W, WDp,
+                            affine && !pk ? E : nullptr, nao, nd, r},
+                           s));
+    if (has_w)
         JK_TRY(jk::launch_project(B, WDp, part, om, nao, naux, want_db ? 2 * nd : nd, pk, s));
-        if (want_db && pk) {
-            Wa = WDp;
-            Ea = WDp + (i64)nd * npk;
-            esign = -1.0;
-        } else if (want_db) {
-            JK_TRY(jk::launch_vjp_e_matrix(CL, CR, E, nao, nd, r, s));
-        }
-    }
+    const double *Wa = pk ? WDp : W, *Ea = pk ? WDp + (i64)nd * npk : E;
+    const double esign = pk ? -1.0 : 1.0;
     // Stage B's two products run side by side on two streams:
     //   main: HT(c), B[P'](c), C(c), D(c), affine(c)
     //   aux:  B[R'](c)
@@ -555,17 +551,20 @@ jk_status build_mixed(const jk_problem *p, const double *B, const KSeg *seg, int
     const int w = want(p);
     const bool fused = o.F != nullptr;
     double *K = fused ? o.F : o.K;
+    double *Cc = (double *)(ws + f.o_cc);
     // gamma and J stay FP64 (the same kernels as the FP64 path).
-    if (!fused && (w & JK_WANT_J)) {
-        jk_status st = coulomb_part(f, nao, naux, nd, r, B, CL, CR, o.J, 1.0, 0, ws, s);
+    const bool want_k = fused ? nseg > 0 : (w & JK_WANT_K) != 0;
+    const bool want_j = fused ? o.cj != 0.0 || !want_k : (w & JK_WANT_J) != 0;
+    JK_TRY(jk::launch_prep({CL, CR, want_k ? Cc : nullptr, want_j ? (double *)(ws + f.o_s) : nullptr, nullptr,
+                            nullptr, nullptr, nao, nd, r},
+                           s));
+    if (!fused && want_j) {
+        jk_status st = coulomb_part(f, nao, naux, nd, B, o.J, 1.0, 0, ws, s);
         if (st != JK_OK)
             return st;
     }
-    const bool want_k = fused ? nseg > 0 : (w & JK_WANT_K) != 0;
     auto fock_j = [&]() -> jk_status {
-        if (fused && (o.cj != 0.0 || !want_k))
-            return coulomb_part(f, nao, naux, nd, r, B, CL, CR, o.F, o.cj, want_k ? 1 : 0, ws, s);
-        return JK_OK;
+        return fused && want_j ? coulomb_part(f, nao, naux, nd, B, o.F, o.cj, want_k ? 1 : 0, ws, s) : JK_OK;
     };
     if (!want_k)
         return fock_j();
@@ -587,7 +586,6 @@ jk_status build_mixed(const jk_problem *p, const double *B, const KSeg *seg, int
     if (pre && nseg != 1)
         return JK_EINVAL;
     const SliceLayout SL = slice_layout(p);
-    double *Cc = (double *)(ws + f.o_cc);
     int8_t *Cp = (int8_t *)(ws + x.o_cp);
     int *eC = (int *)(ws + x.o_ec);
     // The same factor for both sides (C_L = C_R): X only, K on the upper
@@ -677,7 +675,6 @@ jk_status build_mixed(const jk_problem *p, const double *B, const KSeg *seg, int
             return st_;                                                                            \
     } while (0)
 
-    JK_TRY(jk::launch_pack_c(CL, CR, Cc, nao, nd, r, s));
     // digits of [C_L | C_R]: row c, inner n, element Cc[n][c]
     JK_TRY(jk::launch_slice_rows(Cc, 0, 1, R2, 1, R2, nao, x.cp, x.kp / KB, Cp, cps, ckb, eC, s));
     JK_TRY(hipEventRecord(fork, s));

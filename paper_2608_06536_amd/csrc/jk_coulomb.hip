@@ -5,20 +5,27 @@
 
 namespace jk {
 
-__global__ void __launch_bounds__(256) k_fold_density(const double *__restrict__ CL,
-                                                      const double *__restrict__ CR,
-                                                      double *__restrict__ S, int nao, int r)
+constexpr int kFuseGamma = 4096;
+
+// What a build needs before it reads B, independent of each other, as one
+// launch: ranges of workgroups for the derivative's E, the folded densities, the
+// folded cotangent and [C_L | C_R].  Each takes a few microseconds, as does a
+// launch: nao 48 38.0 -> 34.5 us for a build, with gamma's last sum in the J pass.
+__global__ void __launch_bounds__(256) k_prep(PrepArgs a, int ne, int nf, int ns)
 {
     __shared__ double lds[TileDensity::LDS_DOUBLES];
-    fold_density_tile(CL, CR, S, nao, r, blockIdx.x, lds);
-}
-
-__global__ void __launch_bounds__(256) k_sym_pack(const double *__restrict__ A,
-                                                  double *__restrict__ S, int nao)
-{
-    __shared__ double T[32][33];
-    const int nt = sym_pack_tiles(nao);
-    sym_pack_tile(A, S, nao, blockIdx.x / nt, blockIdx.x % nt, T);
+    static_assert(TileDensity::LDS_DOUBLES >= 32 * 33, "sym_pack_tile");
+    int b = blockIdx.x;
+    if (b < ne) {
+        e_matrix_tile(a.CL, a.CR, a.E, a.nao, a.r, b, lds);
+    } else if ((b -= ne) < nf) {
+        fold_density_tile(a.CL, a.CR, a.S, a.nao, a.r, b, lds);
+    } else if ((b -= nf) < ns) {
+        const int nt = sym_pack_tiles(a.nao);
+        sym_pack_tile(a.W, a.SW, a.nao, b / nt, b % nt, (double (*)[33])lds);
+    } else {
+        pack_tile(a.CL, a.CR, a.Cc, a.nao, a.nd, a.r, b - ns);
+    }
 }
 
 template <int NK>
@@ -47,21 +54,40 @@ __global__ void __launch_bounds__(512) k_coulomb(const double *__restrict__ B,
     coulomb_tile<NK, NP>(B, g, J, nao, naux, nd, packed, blockIdx.x, red, scale, accumulate);
 }
 
-hipError_t launch_fold_density(const double *CL, const double *CR, double *S, int nao, int nd, int r,
-                               hipStream_t s)
+// The same with gamma's partial sums added up here, by every workgroup for the
+// slabs and densities it reads (kFuseGamma numbers of LDS at most).
+template <int NK>
+__global__ void __launch_bounds__(512) k_coulomb_sum(const double *__restrict__ B,
+                                                     const double *__restrict__ part,
+                                                     double *__restrict__ J, int nao, int naux, int nd,
+                                                     int packed, int ndp, int npb, double scale,
+                                                     int accumulate)
 {
-    {
-        ProfScope ps_("density", s);
-        hipLaunchKernelGGL(k_fold_density, dim3(fold_tiles(nao, nd)), dim3(256), 0, s, CL, CR, S, nao, r);
+    __shared__ double red[8 * NK * 64], g[kFuseGamma];
+    const int nt = cdiv_i(pk_size(nao), 64);         // 64 positions per workgroup
+    const int k0 = (int)blockIdx.x / nt * NK;
+    for (int e = threadIdx.x; e < naux * NK; e += 512) {
+        const int q = e / NK, k = e % NK;
+        double w[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            w[u] = reduce_part(part + (i64)q * ndp + k0 + k, (i64)naux * ndp, npb, u);
+        g[k * naux + q] = ((w[0] + w[1]) + w[2]) + w[3];
     }
-    return hipGetLastError();
+    __syncthreads();
+    coulomb_tile<NK, 1>(B, g, J, nao, naux, nd, packed, blockIdx.x, red, scale, accumulate, k0);
 }
 
-hipError_t launch_sym_pack(const double *A, double *S, int nao, int nmat, hipStream_t s)
+hipError_t launch_prep(const PrepArgs &a, hipStream_t s)
 {
+    const int nt = cdiv_i(a.nao, 64);
+    const int ne = a.E ? a.nd * nt * nt : 0, nf = a.S ? fold_tiles(a.nao, a.nd) : 0;
+    const int ns = a.W ? a.nd * sym_pack_tiles(a.nao) : 0, nc = a.Cc ? pack_tiles(a.nao, a.nd, a.r) : 0;
+    if (ne + nf + ns + nc == 0)
+        return hipSuccess;
     {
-        ProfScope ps_("sym_pack", s);
-        hipLaunchKernelGGL(k_sym_pack, dim3(nmat * sym_pack_tiles(nao)), dim3(256), 0, s, A, S, nao);
+        ProfScope ps_("prep", s);
+        hipLaunchKernelGGL(k_prep, dim3(ne + nf + ns + nc), dim3(256), 0, s, a, ne, nf, ns);
     }
     return hipGetLastError();
 }
@@ -72,7 +98,7 @@ size_t project_part_doubles(int nao, int naux, int nd)
 }
 
 hipError_t launch_project(const double *B, const double *S, double *part, double *g, int nao, int naux,
-                          int nd, int packed, hipStream_t s)
+                          int nd, int packed, hipStream_t s, bool reduce)
 {
     {
         ProfScope ps_(nd > 8 ? "project16" : "project", s);
@@ -85,7 +111,7 @@ hipError_t launch_project(const double *B, const double *S, double *part, double
         width_dispatch<16>(pj_width(nd), go);
     }
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
+    if (e != hipSuccess || !reduce)
         return e;
     {
         ProfScope ps_("project_reduce", s);
@@ -112,6 +138,29 @@ hipError_t launch_coulomb(const double *B, const double *g, double *J, int nao, 
                                    nao, naux, nd, packed, scale, accumulate);
         };
         width_dispatch<16>(w, go);
+    }
+    return hipGetLastError();
+}
+
+// At most 8 partial sums (nao 127) and kFuseGamma numbers: larger builds keep the
+// sum in a launch of its own, where every number is summed once.
+bool coulomb_sums_gamma(int nao, int naux, int nd)
+{
+    return pj_blocks(nao, naux) <= 8 && (i64)naux * pj_width(nd) <= kFuseGamma && cu_runs(nao) == 1 &&
+           cu_slices_log2(nao) == 3;
+}
+
+hipError_t launch_coulomb_sum(const double *B, const double *part, double *J, int nao, int naux, int nd,
+                              int packed, hipStream_t s, double scale, int accumulate)
+{
+    {
+        ProfScope ps_("coulomb", s);
+        const int w = pj_width(nd);
+        width_dispatch<16>(w, [&](auto nk) {
+            hipLaunchKernelGGL(k_coulomb_sum<decltype(nk)::value>, dim3(cu_tiles(nao, nd, w, 1)), dim3(512),
+                               0, s, B, part, J, nao, naux, nd, packed, pj_groups(nd) * w,
+                               pj_blocks(nao, naux), scale, accumulate);
+        });
     }
     return hipGetLastError();
 }

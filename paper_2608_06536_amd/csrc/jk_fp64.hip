@@ -10,13 +10,6 @@
 
 namespace jk {
 
-__global__ void __launch_bounds__(256) k_pack_c(const double *__restrict__ CL,
-                                                const double *__restrict__ CR, double *__restrict__ Cc,
-                                                int nao, int nd, int r)
-{
-    pack_tile(CL, CR, Cc, nao, nd, r, blockIdx.x);
-}
-
 __global__ void __launch_bounds__(256, 3) k_half_transform(const double *__restrict__ B,
                                                            const double *__restrict__ Cc,
                                                            double *__restrict__ Xw,
@@ -206,17 +199,6 @@ int pick_split_slots(int tiles, int smax, int slots)
         }
     }
     return best;
-}
-
-hipError_t launch_pack_c(const double *CL, const double *CR, double *Cc, int nao, int nd, int r,
-                         hipStream_t s)
-{
-    {
-        ProfScope ps_("pack_c", s);
-        hipLaunchKernelGGL(k_pack_c, dim3(pack_tiles(nao, nd, r)), dim3(256), 0, s, CL, CR, Cc, nao,
-                           nd, r);
-    }
-    return hipGetLastError();
 }
 
 // Dynamic LDS above 64 KB needs a per-kernel attribute, set once per

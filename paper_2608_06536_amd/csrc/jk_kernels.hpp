@@ -35,22 +35,33 @@ hipError_t set_dynamic_lds(const void *fn, int bytes);
 // Same with an explicit number of concurrent workgroup slots.
 int pick_split_slots(int tiles, int smax, int slots);
 
-hipError_t launch_pack_c(const double *CL, const double *CR, double *Cc, int nao, int nd, int r,
-                         hipStream_t s);
 // gamma and J on the upper triangles of the slabs (coulomb_upper.hpp), full
 // squares or packed slabs.  S_k: matrices folded onto the packed positions
 // (A[m][n] + A[n][m] above the diagonal), from the factors or from given
 // matrices (nmat of them).  project: g[k][Q] = sum_p B^Q[p] S_k[p], all nd
 // matrices; part holds project_part_doubles doubles.  coulomb: J (+)= scale *
 // sum_Q g B^Q in full; accumulate adds to what J holds.
-hipError_t launch_fold_density(const double *CL, const double *CR, double *S, int nao, int nd, int r,
-                               hipStream_t s);
-hipError_t launch_sym_pack(const double *A, double *S, int nao, int nmat, hipStream_t s);
+// What a build needs before it reads B; null pointers are left out.
+struct PrepArgs {
+    const double *CL, *CR;
+    double *Cc;             // [C_L | C_R] as one nao x 2 nd r matrix
+    double *S;              // folded densities
+    const double *W;        // cotangent, folded into SW
+    double *SW;
+    double *E;              // D - 2 D^T
+    int nao, nd, r;
+};
+hipError_t launch_prep(const PrepArgs &a, hipStream_t s);
 size_t project_part_doubles(int nao, int naux, int nd);
 hipError_t launch_project(const double *B, const double *S, double *part, double *g, int nao, int naux,
-                          int nd, int packed, hipStream_t s);
+                          int nd, int packed, hipStream_t s, bool reduce = true);
 hipError_t launch_coulomb(const double *B, const double *g, double *J, int nao, int naux, int nd,
                           int packed, hipStream_t s, double scale = 1.0, int accumulate = 0);
+// J from the partial sums of a projection with reduce = false, where
+// coulomb_sums_gamma says so: the same numbers.
+bool coulomb_sums_gamma(int nao, int naux, int nd);
+hipError_t launch_coulomb_sum(const double *B, const double *part, double *J, int nao, int naux, int nd,
+                              int packed, hipStream_t s, double scale = 1.0, int accumulate = 0);
 // packed: B holds packed upper-triangle slabs (nao (nao + 1) / 2 doubles).
 // tile (full slabs only; jk_tune.h): 0 = 128 x 64 workgroup tiles of four
 // waves, 1 = 64 x 64, 2 = 128 x 64 of eight waves (4x4x4 engine); 3 = 128 x 128,
@@ -87,9 +98,6 @@ hipError_t launch_vjp_stage_c(const double *B, const double *L, double *dCp, int
                               int q0, int nq, int nsplit, int accumulate, hipStream_t s);
 hipError_t launch_vjp_dc_finish(const double *dCp, double *dCL, double *dCR, int nao, int nd,
                                 int r, int nsplit, hipStream_t s);
-// E_k = D_k - 2 D_k^T from the factors
-hipError_t launch_vjp_e_matrix(const double *CL, const double *CR, double *E, int nao, int nd, int r,
-                               hipStream_t s);
 hipError_t launch_vjp_stage_d(const double *L, const double *Cc, double *dB, int nao, int R,
                               int q0, int nq, hipStream_t s);
 // Packed B (jk.h JK_B_PACKED): full squares of slabs q0 .. q0 + nq - 1 into

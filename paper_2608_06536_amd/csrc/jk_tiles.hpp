@@ -196,6 +196,23 @@ __device__ inline void pack_tile(const double *__restrict__ CL, const double *__
 // consecutive entries (Q, k) of one partial block; wave w of the four sums
 // the blocks pb = w, w + 4, ... (coalesced 512-byte reads), and the four wave
 // sums are added in wave order.
+// Its share of the partials pb = w, w + 4, ...
+__device__ __forceinline__ double reduce_part(const double *__restrict__ src, i64 total, int npb, int w)
+{
+    double s = 0.0;
+    int pb = w;
+    for (; pb + 12 < npb; pb += 16) {
+        const double v0 = src[(i64)pb * total], v1 = src[(i64)(pb + 4) * total];
+        const double v2 = src[(i64)(pb + 8) * total], v3 = src[(i64)(pb + 12) * total];
+        s += v0;
+        s += v1;
+        s += v2;
+        s += v3;
+    }
+    for (; pb < npb; pb += 4)
+        s += src[(i64)pb * total];
+    return s;
+}
 __device__ inline void reduce_tile(const double *__restrict__ part, double *__restrict__ g, int naux,
                                    int nd, int ndp, int npb, int tile)
 {
@@ -203,22 +220,7 @@ __device__ inline void reduce_tile(const double *__restrict__ part, double *__re
     const i64 total = (i64)naux * ndp;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const i64 e = (i64)tile * 64 + lane;
-    double s = 0.0;
-    if (e < total) {
-        const double *src = part + e;
-        int pb = w;
-        for (; pb + 12 < npb; pb += 16) {
-            const double v0 = src[(i64)pb * total], v1 = src[(i64)(pb + 4) * total];
-            const double v2 = src[(i64)(pb + 8) * total], v3 = src[(i64)(pb + 12) * total];
-            s += v0;
-            s += v1;
-            s += v2;
-            s += v3;
-        }
-        for (; pb < npb; pb += 4)
-            s += src[(i64)pb * total];
-    }
-    red[w][lane] = s;
+    red[w][lane] = e < total ? reduce_part(part + e, total, npb, w) : 0.0;
     __syncthreads();
     if (w == 0 && e < total) {
         const int q = (int)(e / ndp), k = (int)(e % ndp);

@@ -183,36 +183,6 @@ __global__ void __launch_bounds__(256) k_vjp_dc_finish(const double *__restrict_
     }
 }
 
-// E[k][a][b] = D_k[a][b] - 2 D_k[b][a], D_k = CL_k CR_k^T: two products per
-// 64 x 64 tile, sum_i CL[a][i] CR[b][i] - 2 sum_i CR[a][i] CL[b][i].
-__global__ void __launch_bounds__(256) k_vjp_e_matrix(const double *__restrict__ CL,
-                                                      const double *__restrict__ CR,
-                                                      double *__restrict__ E, int nao, int r)
-{
-    typedef TileDensity TL;
-    __shared__ double lds[TL::LDS_DOUBLES];
-    const int nt = cdiv_i(nao, 64);
-    const int k = blockIdx.x / (nt * nt), rem = blockIdx.x % (nt * nt);
-    const int mb = rem / nt, nb = rem % nt;
-    OpKC l{CL + (i64)k * nao * r, r, nao, r};
-    OpKC q{CR + (i64)k * nao * r, r, nao, r};
-    Acc<TL> d, dt;
-    d.zero();
-    dt.zero();
-    tile_gemm<TL>(l, q, mb * 64, nb * 64, 0, r, lds, d);
-    tile_gemm<TL>(q, l, mb * 64, nb * 64, 0, r, lds, dt);
-#pragma unroll
-    for (int i = 0; i < TL::MA; i++)
-#pragma unroll
-        for (int j = 0; j < TL::NB; j++)
-            d.c[i][j] -= 2.0 * dt.c[i][j];
-    double *Ek = E + (i64)k * nao * nao;
-    tile_foreach(d, mb * 64, nb * 64, [&](int m, int n, double v) {
-        if (m < nao && n < nao)
-            Ek[(i64)m * nao + n] = v;
-    });
-}
-
 // ------------------------------------------------------------------ stage D
 // dB[q0+ql][a][b] = sum_{c<R} C_R[a][c] R'[ql][b][c] + sum_{c<R} P'[ql][a][c] C_L[b][c]
 // (C_R[a][c] = Cc[a][R + c], C_L[b][c] = Cc[b][c]), the two sums in this order.
@@ -501,17 +471,6 @@ hipError_t launch_vjp_dc_finish(const double *dCp, double *dCL, double *dCR, int
         ProfScope ps_("vjp_dc_finish", s);
         hipLaunchKernelGGL(k_vjp_dc_finish, dim3(cdiv((i64)nao * 2 * nd * r, 64)), dim3(256), 0, s, dCp,
                            dCL, dCR, nao, nd, r, nsplit);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_vjp_e_matrix(const double *CL, const double *CR, double *E, int nao, int nd, int r,
-                               hipStream_t s)
-{
-    {
-        ProfScope ps_("vjp_e_matrix", s);
-        const int nt = cdiv(nao, 64);
-        hipLaunchKernelGGL(k_vjp_e_matrix, dim3(nd * nt * nt), dim3(256), 0, s, CL, CR, E, nao, r);
     }
     return hipGetLastError();
 }

@@ -35,6 +35,8 @@ def _pack(B):
     (44, 15, 1, 2), (45, 16, 3, 4),        # 990 and 1035 positions: one block and two
     (64, 129, 5, 3), (65, 33, 9, 2),       # 64-tiles of the folded density; widths 8 and 16
     (50, 131, 17, 1),                      # two groups of 16
+    (127, 40, 1, 2), (128, 40, 1, 2),      # gamma summed by the J pass: 8 partial sums, 9
+    (20, 4096, 1, 1), (20, 4097, 1, 1), (24, 256, 9, 2), (24, 257, 9, 2),  # its LDS full, and past it
     (361, 20, 2, 3), (362, 37, 4, 2),      # one and four runs of positions per wave
     (370, 19, 16, 1),                      # several blocks of positions per workgroup
     (540, 11, 1, 2), (760, 7, 2, 2), (1080, 6, 1, 1),   # 4, 2, 1 slab slices
