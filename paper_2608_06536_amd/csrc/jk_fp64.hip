@@ -80,19 +80,30 @@ __global__ void __launch_bounds__(256, shape_wgs(kS128x128))
                      ncol);
 }
 
-// Packed slabs on the 16 x 16 x 4 engine (plan tiles 3 and 4): 128 x 64 tiles
-// per slab, three workgroups per CU.
-__global__ void __launch_bounds__(256, 4) k_half_transform16_packed(const double *__restrict__ B,
-                                                                    const double *__restrict__ Cc,
-                                                                    double *__restrict__ Xw,
-                                                                    double *__restrict__ Yw,
-                                                                    int nao, int nd, int r, int q0,
-                                                                    int nq, int ldw, int ncol)
+template <int BN>
+__global__ void __launch_bounds__(256, 4)
+    k_half_transform16n(const double *__restrict__ B, const double *__restrict__ Cc,
+                        double *__restrict__ Xw, double *__restrict__ Yw, int nao, int nd, int r,
+                        int q0, int nq, int ldw, int ncol)
+{
+    typedef typename HtNarrow<BN>::flat TL;
+    extern __shared__ double lds_dyn[];
+    const int n = ht_flat_tiles<TL>(nao, ncol, nq);
+    ht_tile_flat<TL>(B, Cc, Xw, Yw, nao, nd, r, q0, nq, ldw, xcd_swizzle(blockIdx.x, n), lds_dyn,
+                     ncol);
+}
+
+// Packed slabs on the 16 x 16 x 4 engine (plan tiles 3 and 4): tiles of 64 rows
+// per slab, four workgroups per CU.
+template <class TL>
+__global__ void __launch_bounds__(256, 4)
+    k_half_transform16_packed(const double *__restrict__ B, const double *__restrict__ Cc,
+                              double *__restrict__ Xw, double *__restrict__ Yw, int nao, int nd, int r,
+                              int q0, int nq, int ldw, int ncol)
 {
     extern __shared__ double lds_dyn[];
-    const int n = nq * cdiv_i(nao, TileHalf16::BM) * cdiv_i(ncol, TileHalf16::BN);
-    ht_tile16_packed<TileHalf16>(B, Cc, Xw, Yw, nao, nd, r, q0, ldw, xcd_swizzle(blockIdx.x, n),
-                                 lds_dyn, ncol);
+    const int n = nq * cdiv_i(nao, TL::BM) * cdiv_i(ncol, TL::BN);
+    ht_tile16_packed<TL>(B, Cc, Xw, Yw, nao, nd, r, q0, ldw, xcd_swizzle(blockIdx.x, n), lds_dyn, ncol);
 }
 
 // The same on packed slabs (jk.h JK_B_PACKED).
@@ -224,16 +235,16 @@ namespace {
 typedef void (*HtKernel)(const double *, const double *, double *, double *, int, int, int, int, int,
                          int, int);
 template <class TL>
-hipError_t launch_ht16(const void *fn, HtKernel k, const double *B, const double *Cc, double *Xw,
+hipError_t launch_ht16(HtKernel k, int ntiles, const double *B, const double *Cc, double *Xw,
                        double *Yw, int nao, int nd, int r, int q0, int nq, int ldw, int ncol,
                        hipStream_t s, const char *prof)
 {
     const int lds = (int)sizeof(double) * TL::LDS_DOUBLES;
-    hipError_t e = set_dynamic_lds(fn, lds);
+    hipError_t e = set_dynamic_lds((const void *)k, lds);
     if (e != hipSuccess)
         return e;
     ProfScope ps_(prof, s);
-    hipLaunchKernelGGL(k, dim3(ht_flat_tiles<TL>(nao, ncol, nq)), dim3(TL::NTHR), lds, s, B, Cc, Xw, Yw,
+    hipLaunchKernelGGL(k, dim3(ntiles), dim3(TL::NTHR), lds, s, B, Cc, Xw, Yw,
                        nao, nd, r, q0, nq, ldw, ncol);
     return hipSuccess;
 }
@@ -248,40 +259,45 @@ hipError_t launch_half_transform(const double *B, const double *Cc, double *Xw, 
     // packed slabs: one buffer resource per slab
     if (!packed && tile >= 3 && !buf_extent_ok((i64)nq * nao * nao))
         tile = 2;                                 // chunk beyond the buffer loads' 4 GiB reach
+    auto flat = [&](auto tl, HtKernel k) {
+        typedef decltype(tl) TL;
+        return launch_ht16<TL>(k, ht_flat_tiles<TL>(nao, ncol, nq), B, Cc, Xw, Yw, nao, nd, r, q0, nq, ldw,
+                               ncol, s, prof);
+    };
+    auto slabs = [&](auto tl) {
+        typedef decltype(tl) TL;
+        return launch_ht16<TL>(k_half_transform16_packed<TL>, nq * cdiv(nao, TL::BM) * cdiv(ncol, TL::BN), B,
+                               Cc, Xw, Yw, nao, nd, r, q0, nq, ldw, ncol, s, "half_transform_packed");
+    };
     if (packed && tile >= 3) {
-        const int lds = (int)sizeof(double) * TileHalf16::LDS_DOUBLES;
-        hipError_t e = set_dynamic_lds((const void *)k_half_transform16_packed, lds);
+        hipError_t e;
+        switch (ht_cols(ncol, true)) {
+        case 16: e = slabs(HtNarrow<16>::packed()); break;
+        case 32: e = slabs(HtNarrow<32>::packed()); break;
+        case 48: e = slabs(HtNarrow<48>::packed()); break;
+        default: e = slabs(TileHalf16());
+        }
         if (e != hipSuccess)
             return e;
-        ProfScope ps_("half_transform_packed", s);
-        hipLaunchKernelGGL(k_half_transform16_packed,
-                           dim3(nq * cdiv(nao, TileHalf16::BM) * cdiv(ncol, TileHalf16::BN)),
-                           dim3(TileHalf16::NTHR), lds, s, B, Cc, Xw, Yw, nao, nd, r, q0, nq, ldw,
-                           ncol);
     } else if (packed) {
         ProfScope ps_("half_transform_packed", s);
         hipLaunchKernelGGL(k_half_transform_packed, dim3(ht_tiles_cols(nao, ncol, nq)), dim3(256), 0,
                            s, B, Cc, Xw, Yw, nao, nd, r, q0, nq, ldw, ncol);
     } else if (tile == 3 || tile == 4) {
-        const int shape = tile == 3 ? kS128x128 : ht_shape(nao);
-        hipError_t e = hipErrorInvalidValue;
-        switch (shape) {
-        case kS128x128:
-            e = launch_ht16<ShapeTile<kS128x128>::type>((const void *)k_half_transform16a,
-                                                        k_half_transform16a, B, Cc, Xw, Yw, nao, nd, r,
-                                                        q0, nq, ldw, ncol, s, prof);
-            break;
-        case kS128x64:
-            e = launch_ht16<ShapeTile<kS128x64>::type>((const void *)k_half_transform16<kS128x64>,
-                                                       k_half_transform16<kS128x64>, B, Cc, Xw, Yw, nao,
-                                                       nd, r, q0, nq, ldw, ncol, s, prof);
-            break;
-        case kS64x64:
-            e = launch_ht16<ShapeTile<kS64x64>::type>((const void *)k_half_transform16<kS64x64>,
-                                                      k_half_transform16<kS64x64>, B, Cc, Xw, Yw, nao,
-                                                      nd, r, q0, nq, ldw, ncol, s, prof);
-            break;
-        }
+        hipError_t e;
+        const int bn = tile == 3 ? 128 : ht_cols(ncol, false);
+        if (bn == 128)
+            e = flat(ShapeTile<kS128x128>::type(), k_half_transform16a);
+        else if (bn == 16)
+            e = flat(HtNarrow<16>::flat(), k_half_transform16n<16>);
+        else if (bn == 32)
+            e = flat(HtNarrow<32>::flat(), k_half_transform16n<32>);
+        else if (bn == 48)
+            e = flat(HtNarrow<48>::flat(), k_half_transform16n<48>);
+        else if (ht_shape(nao) == kS128x64)
+            e = flat(ShapeTile<kS128x64>::type(), k_half_transform16<kS128x64>);
+        else
+            e = flat(ShapeTile<kS64x64>::type(), k_half_transform16<kS64x64>);
         if (e != hipSuccess)
             return e;
     } else if (tile == 2) {

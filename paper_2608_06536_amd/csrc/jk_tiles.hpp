@@ -35,7 +35,8 @@ typedef Tile<64, 64, 32, 32, 16> TileDensity;
 // four workgroups per CU; wins at small nao where 128-row tiles waste rows.
 typedef Tile<64, 64, 32, 32, 16> TileHalf64;
 // The half-transform on the 16 x 16 x 4 engine (jk_tune.h tile 4): shape by
-// ht_shape over stacked slabs; packed slabs take 64 x 64 tiles per slab.
+// ht_shape over stacked slabs, packed slabs 64 x 64 tiles per slab; narrower
+// columns where ht_cols says so.
 typedef ShapeTile<kS64x64>::type TileHalf16;
 
 // Shape of the half-transform over stacked slabs (the rows are one matrix, so
@@ -45,6 +46,31 @@ typedef ShapeTile<kS64x64>::type TileHalf16;
 // 128 x 64 beyond, whose wave tiles read less per product (374: 3.08 ms against
 // 3.13, 500: 10.1 against 10.3).
 inline int ht_shape(int nao) { return nao <= 256 ? kS64x64 : kS128x64; }
+// Narrow column tiles, the four waves on top of each other: 128 rows over stacked
+// slabs, 64 of a packed slab.
+template <int BN>
+struct HtNarrow {
+    typedef Tile16<128, BN, 32, BN, 16> flat;
+    typedef Tile16<64, BN, 16, BN, 16> packed;
+};
+// Columns of the half-transform's tiles for ncol factor columns: the least padded
+// columns over the rate of a width, 64 unless another is 3% better (a wave of a
+// narrower tile reads more LDS per product).  us at nao 400, naux 1000, by width
+// 64 / 48 / 32 / 16: 16 columns 352 / 300 / 275 / 269 (packed slabs 413 / 329 /
+// 241 / 216), 48 columns 362 / 318 / 379 / 375 (431 / 348 / 458 / 459), 96
+// columns 657 / 527 / 541 / 620 (823 / 650 / 678 / 837), 112 columns 663 / 751 /
+// 721 / 728, 160 columns 973 / 995 / 891 / 1009.
+inline int ht_cols(int ncol, bool packed)
+{
+    const int width[4] = {64, 48, 32, 16};
+    const double rate[2][4] = {{1.0, 0.92, 0.9, 0.78}, {1.0, 0.97, 0.91, 0.6}};
+    auto cost = [&](int i) { return (ncol + width[i] - 1) / width[i] * width[i] / rate[packed][i]; };
+    int best = 0;
+    for (int i = 1; i < 4; i++)
+        if (cost(i) < 0.97 * cost(0) && cost(i) < cost(best))
+            best = i;
+    return width[best];
+}
 
 __host__ __device__ inline int cdiv_i(i64 a, i64 b) { return (int)((a + b - 1) / b); }
 
