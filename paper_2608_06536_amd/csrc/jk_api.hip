@@ -942,9 +942,11 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
                 return (int)std::min<i64>(plans[g].f.qc, p[g].naux - q0);
             };
             if (mixed) {
-                int nj = 1, maxnao = 1;
+                // registers (packed) or lanes of the longest row
+                int nj = 1, lanes = 8, maxnao = 1;
                 for (int g = 0; g < G; g++) {
                     nj = std::max(nj, slicer_blocks(plans[g].x.kp));
+                    lanes = std::max(lanes, jk::mixed_slice_lanes(plans[g].x.kp));
                     maxnao = std::max(maxnao, (int)p[g].nao);
                 }
                 if (packed)      // bands of 8 rows through LDS; arg = 16 x LDS bytes + blocks
@@ -953,8 +955,8 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
                         16 * (int)sizeof(double) * 8 * maxnao + nj);
                 else
                     add(jk::kPhaseMSliceB, c,
-                        [&](int g) { return (int)((nq_of(g) * p[g].nao + 3) / 4); }, in_step,
-                        nj);
+                        [&](int g) { return (int)((nq_of(g) * p[g].nao * lanes + 255) / 256); }, in_step,
+                        lanes);
                 add(jk::kPhaseMHalf, c,
                     [&](int g) {
                         return jk::mixed_ht_tiles(nq_of(g) * (int)p[g].nao,

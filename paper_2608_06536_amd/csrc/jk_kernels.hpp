@@ -126,6 +126,8 @@ hipError_t launch_slice_rows(const double *src, i64 bs, i64 rs, i64 ks, int nb, 
                              hipStream_t s);
 hipError_t launch_slice_b(const double *src, i64 bs, i64 rs, int nb, int nr, int nk, int rp, int nkb,
                           int8_t *out, i64 pstride, i64 kbstride, int *exps, hipStream_t s);
+// lanes of the one-pass slicer per row of kp inner bytes (0: rows too long for it)
+int mixed_slice_lanes(int kp);
 // widths 2 nd r of X/Y the mixed path takes
 int mixed_rowmax_ok(int R2);
 // XY's digit planes; the row exponents (left in exps) from nsp partial maxima.

@@ -36,6 +36,9 @@ constexpr int kMhM = 128, kMhN = 64;
 
 inline int cdiv(i64 a, i64 b) { return (int)((a + b - 1) / b); }
 
+// Two doubles at any element: 16-byte loads need 4-byte alignment only.
+typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+
 __device__ __forceinline__ void write_digits(int8_t *dst, i64 pstride, const int8_t (*d)[kNS])
 {
 #pragma unroll
@@ -99,56 +102,68 @@ __global__ void __launch_bounds__(256) k_slice_rows(const double *__restrict__ s
     slice_row8(src, bs, rs, ks, nr, nk, rp, nkb, out, pstride, kbstride, exps, row, t & 7);
 }
 
-// One-pass slicer for unit-stride rows of at most 256 * NJ elements: one wave
-// per row holds the row in registers (lane l: elements 4 l + 256 j + u),
-// reduces the maximum across the wave, then writes the digits.
-template <int NJ>
+// One-pass slicer for unit-stride rows of at most 32 LPR elements: LPR lanes
+// hold a row in registers (lane l of the row: elements 4 l + 4 LPR j + u, j < 8),
+// reduce its maximum among them, then write the digits.  A wave takes 64 / LPR
+// consecutive rows, so that each of its plane writes covers 64 / LPR x 32
+// consecutive bytes of LPR / 8 inner blocks.  Bound by memory, 12 bytes per
+// element: 5.3 TB/s at nao 300, 4.9 at 250, 5.2 at 500 (one row per wave, in
+// 32-byte pieces: 3.8, 3.6 and 4.0).
+constexpr int kSliceNJ = 8;
+template <int LPR>
 __device__ __forceinline__ void slice_row_wave(const double *__restrict__ src, i64 bs, i64 rs,
                                                int nr, int nk, int rp, int nkb,
                                                int8_t *__restrict__ out, i64 pstride, i64 kbstride,
                                                int *__restrict__ exps, i64 row)
 {
-    const int lane = threadIdx.x & 63;
+    const int sub = threadIdx.x & (LPR - 1);
     const int b = (int)(row / rp), m = (int)(row % rp);
     const bool live = m < nr;
-    // loads are unconditional (clamped addresses), masked afterwards; rows
-    // that start on 16 bytes with nk % 4 == 0 use 16-byte loads
     const double *s = src + (i64)b * bs + (i64)(live ? m : nr - 1) * rs;
-    const bool vec = ((((uintptr_t)s) & 15) == 0) && (nk & 3) == 0;
-    double v[NJ][4];
+    double v[kSliceNJ][4];
     double mx = 0.0;
 #pragma unroll
-    for (int j = 0; j < NJ; j++) {
-        const int k0 = 256 * j + 4 * lane;
-        double x[4];
-        if (vec) {
-            const int kc = k0 < nk ? k0 : nk - 4;
-            const double2 lo = *(const double2 *)(s + kc), hi = *(const double2 *)(s + kc + 2);
-            x[0] = lo.x;
-            x[1] = lo.y;
-            x[2] = hi.x;
-            x[3] = hi.y;
-        } else {
+    for (int j = 0; j < kSliceNJ; j++) {
+        if (4 * LPR * j >= nk) {                 // the same for every lane
 #pragma unroll
             for (int u = 0; u < 4; u++)
-                x[u] = s[(k0 + u) < nk ? k0 + u : nk - 1];
+                v[j][u] = 0.0;
+            continue;
         }
+        const int k0 = 4 * LPR * j + 4 * sub;
+        if (k0 + 4 <= nk) {
+            const d2 lo = *(const d2 *)(s + k0), hi = *(const d2 *)(s + k0 + 2);
+            v[j][0] = lo[0];
+            v[j][1] = lo[1];
+            v[j][2] = hi[0];
+            v[j][3] = hi[1];
+        } else {
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
-            v[j][u] = (live && k0 + u < nk) ? x[u] : 0.0;
-            mx = fmax(mx, fabs(v[j][u]));
+            for (int u = 0; u < 4; u++) {
+                const double x = s[(k0 + u) < nk ? k0 + u : nk - 1];
+                v[j][u] = k0 + u < nk ? x : 0.0;
+            }
         }
+        if (!live)
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+                v[j][u] = 0.0;
     }
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1)
+    for (int j = 0; j < kSliceNJ; j++)
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            mx = fmax(mx, fabs(v[j][u]));
+#pragma unroll
+    for (int o = LPR / 2; o >= 1; o >>= 1)
         mx = fmax(mx, __shfl_xor(mx, o));
     const int e = row_exponent(mx);
-    if (lane == 0)
+    if (sub == 0)
         exps[row] = live ? e : 0;
-    int8_t *dst = out + row * kSliceKB + 4 * (lane & 7);
+    int8_t *dst = out + row * kSliceKB + 4 * (sub & 7);
 #pragma unroll
-    for (int j = 0; j < NJ; j++) {
-        const int kb = 8 * j + (lane >> 3);
+    for (int j = 0; j < kSliceNJ; j++) {
+        const int kb = LPR / 8 * j + (sub >> 3);
         if (kb < nkb) {
             int8_t d[4][kNS];
 #pragma unroll
@@ -159,17 +174,22 @@ __device__ __forceinline__ void slice_row_wave(const double *__restrict__ src, i
     }
 }
 
-template <int NJ>
+template <int LPR>
 __global__ void __launch_bounds__(256) k_slice_rows_wave(const double *__restrict__ src, i64 bs,
                                                          i64 rs, int nb, int nr, int nk, int rp,
                                                          int nkb, int8_t *__restrict__ out,
                                                          i64 pstride, i64 kbstride,
                                                          int *__restrict__ exps)
 {
-    const i64 row = (i64)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= (i64)nb * rp)        // whole waves leave together
+    const i64 row = (i64)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
+    if (row >= (i64)nb * rp)        // whole rows of lanes leave together
         return;
-    slice_row_wave<NJ>(src, bs, rs, nr, nk, rp, nkb, out, pstride, kbstride, exps, row);
+    slice_row_wave<LPR>(src, bs, rs, nr, nk, rp, nkb, out, pstride, kbstride, exps, row);
+}
+// Lanes per row for rows of nkb 32-byte inner blocks; 0: longer than 2048.
+inline int slice_lanes(int nkb)
+{
+    return nkb <= 8 ? 8 : nkb <= 16 ? 16 : nkb <= 32 ? 32 : nkb <= 64 ? 64 : 0;
 }
 
 // The same for packed symmetric slabs (jk.h JK_B_PACKED).  A workgroup takes
@@ -289,12 +309,12 @@ __device__ __forceinline__ void slice_xy_block(const double *__restrict__ XY, in
     double x[4];
     const int q0 = j0 / r, i0 = j0 - q0 * r;
     const double *p0 = s + (i64)q0 * nao * R2 + i0;
-    if (j0 + 3 < nj && i0 + 3 < r && (((uintptr_t)p0) & 15) == 0) {
-        const double2 lo = *(const double2 *)p0, hi = *(const double2 *)(p0 + 2);
-        x[0] = lo.x;
-        x[1] = lo.y;
-        x[2] = hi.x;
-        x[3] = hi.y;
+    if (j0 + 3 < nj && i0 + 3 < r) {
+        const d2 lo = *(const d2 *)p0, hi = *(const d2 *)(p0 + 2);
+        x[0] = lo[0];
+        x[1] = lo[1];
+        x[2] = hi[0];
+        x[3] = hi[1];
     } else {
 #pragma unroll
         for (int u = 0; u < 4; u++) {
@@ -459,10 +479,14 @@ __device__ __forceinline__ void rowmax_pm_block(const uint32_t *__restrict__ pm,
         const int slot = key - cb * kMhN / r;
         const uint32_t *p = pm + ((i64)cb * nslot + slot) * rows + mc;
         int ql = q0 + w;
-        for (; ql + 12 < q1; ql += 16) {
-            const uint32_t v0 = p[(i64)ql * nao], v1 = p[(i64)(ql + 4) * nao];
-            const uint32_t v2 = p[(i64)(ql + 8) * nao], v3 = p[(i64)(ql + 12) * nao];
-            mx = max(mx, max(max(v0, v1), max(v2, v3)));
+        for (; ql + 60 < q1; ql += 64) {         // 16 loads in flight
+            uint32_t v[16];
+#pragma unroll
+            for (int u = 0; u < 16; u++)
+                v[u] = p[(i64)(ql + 4 * u) * nao];
+#pragma unroll
+            for (int u = 0; u < 16; u++)
+                mx = max(mx, v[u]);
         }
         for (; ql < q1; ql += 4)
             mx = max(mx, p[(i64)ql * nao]);
@@ -634,7 +658,7 @@ __global__ void __launch_bounds__(256) k_bm_slice_c(const BMember *__restrict__ 
                threadIdx.x & 7);
 }
 
-template <int NJ>
+template <int LPR>
 __global__ void __launch_bounds__(256) k_bm_slice_b(const BMember *__restrict__ M,
                                                     const int *__restrict__ tab, int c)
 {
@@ -642,11 +666,11 @@ __global__ void __launch_bounds__(256) k_bm_slice_b(const BMember *__restrict__ 
     const BMember &m = M[find_member(tab, blockIdx.x, loc)];
     int q0, nq;
     chunk_of(m, c, q0, nq);
-    const i64 row = (i64)loc * 4 + (threadIdx.x >> 6);
-    if (row >= (i64)nq * m.nao)      // whole waves leave together
+    const i64 row = (i64)loc * (256 / LPR) + threadIdx.x / LPR;
+    if (row >= (i64)nq * m.nao)      // whole rows of lanes leave together
         return;
-    slice_row_wave<NJ>(m.B + (i64)q0 * m.npos, m.npos, m.nao, m.nao, m.nao, m.nao, m.kp / kSliceKB,
-                       m.Bp, m.bps, m.bkb, m.eB, row);
+    slice_row_wave<LPR>(m.B + (i64)q0 * m.npos, m.npos, m.nao, m.nao, m.nao, m.nao, m.kp / kSliceKB,
+                        m.Bp, m.bps, m.bkb, m.eB, row);
 }
 
 // The chunk's packed slabs (jk.h JK_B_PACKED), bands of kBand rows; the
@@ -749,27 +773,28 @@ hipError_t launch_slice_rows(const double *src, i64 bs, i64 rs, i64 ks, int nb, 
 hipError_t launch_slice_b(const double *src, i64 bs, i64 rs, int nb, int nr, int nk, int rp, int nkb,
                           int8_t *out, i64 pstride, i64 kbstride, int *exps, hipStream_t s)
 {
-    const int nj = cdiv(nkb, 8);
-    if (nj > 8)     // long rows: generic two-pass slicer
+    const int lanes = slice_lanes(nkb);
+    if (lanes == 0)     // long rows: generic two-pass slicer
         return launch_slice_rows(src, bs, rs, 1, nb, nr, nk, rp, nkb, out, pstride, kbstride, exps, s);
-    const dim3 g(cdiv((i64)nb * rp, 4));
+    const dim3 g(cdiv((i64)nb * rp, 256 / lanes));
     {
         ProfScope ps_("slice_b", s);
-        if (nj <= 1)
-            hipLaunchKernelGGL(k_slice_rows_wave<1>, g, dim3(256), 0, s, src, bs, rs, nb, nr, nk, rp,
-                               nkb, out, pstride, kbstride, exps);
-        else if (nj <= 2)
-            hipLaunchKernelGGL(k_slice_rows_wave<2>, g, dim3(256), 0, s, src, bs, rs, nb, nr, nk, rp,
-                               nkb, out, pstride, kbstride, exps);
-        else if (nj <= 4)
-            hipLaunchKernelGGL(k_slice_rows_wave<4>, g, dim3(256), 0, s, src, bs, rs, nb, nr, nk, rp,
-                               nkb, out, pstride, kbstride, exps);
+        auto go = [&](auto k) {
+            hipLaunchKernelGGL(k, g, dim3(256), 0, s, src, bs, rs, nb, nr, nk, rp, nkb, out, pstride,
+                               kbstride, exps);
+        };
+        if (lanes == 8)
+            go(k_slice_rows_wave<8>);
+        else if (lanes == 16)
+            go(k_slice_rows_wave<16>);
+        else if (lanes == 32)
+            go(k_slice_rows_wave<32>);
         else
-            hipLaunchKernelGGL(k_slice_rows_wave<8>, g, dim3(256), 0, s, src, bs, rs, nb, nr, nk, rp,
-                               nkb, out, pstride, kbstride, exps);
+            go(k_slice_rows_wave<64>);
     }
     return hipGetLastError();
 }
+int mixed_slice_lanes(int kp) { return slice_lanes(kp / kSliceKB); }
 
 // Dynamic LDS above 64 KB needs a per-kernel attribute, set once per
 // (kernel, device).
@@ -949,14 +974,14 @@ hipError_t launch_batched_mixed_phase(int phase, const BMember *M, const int *ta
     }
     case kPhaseMSliceB: {
         ProfScope ps_("bm_slice_b", s);
-        if (arg <= 1)
-            hipLaunchKernelGGL(k_bm_slice_b<1>, g, dim3(256), 0, s, M, tab, step);
-        else if (arg <= 2)
-            hipLaunchKernelGGL(k_bm_slice_b<2>, g, dim3(256), 0, s, M, tab, step);
-        else if (arg <= 4)
-            hipLaunchKernelGGL(k_bm_slice_b<4>, g, dim3(256), 0, s, M, tab, step);
-        else if (arg <= 8)
+        if (arg == 8)
             hipLaunchKernelGGL(k_bm_slice_b<8>, g, dim3(256), 0, s, M, tab, step);
+        else if (arg == 16)
+            hipLaunchKernelGGL(k_bm_slice_b<16>, g, dim3(256), 0, s, M, tab, step);
+        else if (arg == 32)
+            hipLaunchKernelGGL(k_bm_slice_b<32>, g, dim3(256), 0, s, M, tab, step);
+        else if (arg == 64)
+            hipLaunchKernelGGL(k_bm_slice_b<64>, g, dim3(256), 0, s, M, tab, step);
         else
             return hipErrorInvalidValue;
         break;
