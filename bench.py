@@ -59,9 +59,6 @@ def measured_traffic(kernel, plan):
     return None
 
 
-# Derivative launches that run concurrently on two streams (stage B's two
-# products): their HIP-event times include the concurrent launch.
-OVERLAPPED = {"vjp_stage_b_p", "vjp_stage_b_r"}
 # Launch names of one kernel function: the derivative's half-transforms are
 # the build's kernel on chunks of their own.
 SAME_KERNEL = {"vjp_half_transform": "half_transform"}
@@ -76,8 +73,7 @@ def kernel_models(p, nd, nao, naux, R):
         "half_transform": ("mfma", 4.0 * naux * n2 * R, "flop"),       # the build's
         "vjp_half_transform": ("mfma", 4.0 * naux * n2 * R, "flop"),   # the derivative's
         "exchange": ("mfma", 2.0 * naux * n2 * R, "flop"),
-        "vjp_stage_b_p": ("mfma", 2.0 * naux * n2 * R, "flop"),
-        "vjp_stage_b_r": ("mfma", 2.0 * naux * n2 * R, "flop"),
+        "vjp_stage_b": ("mfma", 4.0 * naux * n2 * R, "flop"),
         "vjp_stage_c": ("mfma", 4.0 * naux * n2 * R, "flop"),
         "vjp_stage_d": ("mfma", 4.0 * naux * n2 * R, "flop"),
         "coulomb": ("hbm", 8.0 * naux * nao * (nao + 1) / 2, "byte"),   # B's upper triangles
@@ -518,18 +514,14 @@ def main():
                 ent["tflops"] = round(tot / (ms * 1e-3) / 1e12, 2)
             else:
                 ent["gbs"] = round(tot / (ms * 1e-3) / 1e9, 1)
-        if name in OVERLAPPED:
-            ent["overlapped"] = True
         per_kernel[name] = ent
-    # The roofline kernel: the kernel function with the most time among those
-    # that never share the GPU with another launch (an overlapped launch's
-    # event time includes the other launch's work); its build launches (one
-    # fixed chunk plan, the one the counter records cover) give the figures.
+    # The roofline kernel: the kernel function with the most time; its build
+    # launches (one fixed chunk plan, the one the counter records cover) give
+    # the figures.
     fn_ms = {}
     for name, (ms, _) in kern.items():
-        if name not in OVERLAPPED:
-            fn = SAME_KERNEL.get(name, name)
-            fn_ms[fn] = fn_ms.get(fn, 0.0) + ms
+        fn = SAME_KERNEL.get(name, name)
+        fn_ms[fn] = fn_ms.get(fn, 0.0) + ms
     dom = max(fn_ms, key=fn_ms.get)
     bound, amount, unit = models.get(dom, ("mfma", float("nan"), "flop"))
     dom_ms, dom_cnt = kern[dom]

@@ -458,18 +458,6 @@ jk_status vjp_fp64(const jk_problem *p, const double *B, const double *CL, const
         JK_TRY(jk::launch_project(B, WDp, part, om, nao, naux, want_db ? 2 * nd : nd, pk, s));
     const double *Wa = pk ? WDp : W, *Ea = pk ? WDp + (i64)nd * npk : E;
     const double esign = pk ? -1.0 : 1.0;
-    // Stage B's two products run side by side on two streams:
-    //   main: HT(c), B[P'](c), C(c), D(c), affine(c)
-    //   aux:  B[R'](c)
-    // aux's B[R'](c) waits for HT(c) (it reads X), whose event main records
-    // after every reader of chunk c - 1's slab blocks; main waits for B[R'](c)
-    // before stage C.  Stage C beside stage D (on the second stream) took 2%
-    // longer than the two in sequence.
-    hipStream_t a = nullptr;
-    JK_TRY(aux_stream(&a));
-    EventSet ev;
-    JK_TRY(ev.create(2));
-    hipEvent_t ev_x = ev.ev[0], ev_br = ev.ev[1];
     const int tile = plan_tuning(p).ht_tile;
     for (int q0 = 0; q0 < naux; q0 += f.qc) {
         const int nq = (naux - q0) < f.qc ? (naux - q0) : f.qc;
@@ -486,14 +474,8 @@ jk_status vjp_fp64(const jk_problem *p, const double *B, const double *CL, const
         if (has_v)
             JK_TRY(jk::launch_half_transform(Bs, Cc, Xw, Yw, nao, nd, r, qs, nq, f.ldw, s,
                                              sym ? R : 2 * R, 0, tile, "vjp_half_transform"));
-        JK_TRY(hipEventRecord(ev_x, s));         // X, Y of this chunk; D of the last done
-        JK_TRY(hipStreamWaitEvent(a, ev_x, 0));
-        JK_TRY(jk::launch_vjp_stage_b_one(1, V, Xw, Cc, om, L, nao, nd, r, naux, q0, nq * r, f.ldw, has_v,
-                                          has_w, a));
-        JK_TRY(hipEventRecord(ev_br, a));
-        JK_TRY(jk::launch_vjp_stage_b_one(0, V, Yx, Cc, om, L, nao, nd, r, naux, q0, nq * r, f.ldw, has_v,
-                                          has_w, s));
-        JK_TRY(hipStreamWaitEvent(s, ev_br, 0));
+        JK_TRY(jk::launch_vjp_stage_b(V, Xw, Yx, Cc, om, L, nao, nd, r, naux, q0, nq * r, f.ldw, has_v, has_w,
+                                      s));
         if (want_dc)
             JK_TRY(jk::launch_vjp_stage_c(Bs, L, dCp, nao, R, qs, nq, f.nsplit_c, q0 > 0, s));
         if (want_db) {
@@ -623,15 +605,24 @@ jk_status build_mixed(const jk_problem *p, const double *B, const KSeg *seg, int
     //   Bp/eB[c]   written by slice_b(c),  read by ht(c)
     //   XY/PM[c]   written by ht(c),       read by rowmax/slice_xy(c)
     //   XYp/eXY[c] written by slice_xy(c), read by ex(c)
-    hipStream_t a = nullptr;
-    JK_TRY(aux_stream(&a));
+    // A single chunk is one chain of launches and stays on s (events between
+    // the streams take longer than small launches).
+    hipStream_t a = s;
     EventSet E;
-    JK_TRY(E.create(9));
+    if (nchunk > 1) {
+        JK_TRY(aux_stream(&a));
+        JK_TRY(E.create(9));
+    }
+    const bool two = nchunk > 1;
+    auto record = [&](hipEvent_t ev, hipStream_t st) { return two ? hipEventRecord(ev, st) : hipSuccess; };
+    auto wait = [&](hipStream_t st, hipEvent_t ev) {
+        return two ? hipStreamWaitEvent(st, ev, 0) : hipSuccess;
+    };
     hipEvent_t fork = E.ev[0], sb[2] = {E.ev[1], E.ev[2]}, ht[2] = {E.ev[3], E.ev[4]},
                sx[2] = {E.ev[5], E.ev[6]}, ex[2] = {E.ev[7], E.ev[8]};
     auto slice_b = [&](int c) -> jk_status {
         if (pre) {              // prepared planes: nothing to make
-            JK_TRY(hipEventRecord(sb[c & 1], a));
+            JK_TRY(record(sb[c & 1], a));
             return JK_OK;
         }
         if (f.packed)
@@ -640,32 +631,32 @@ jk_status build_mixed(const jk_problem *p, const double *B, const KSeg *seg, int
         else
             JK_TRY(jk::launch_slice_b(chunks[c].B, npos, nao, nq_of(c), nao, nao, nao,
                                       x.kp / KB, Bp(c), bps, bkb, eB(c), a));
-        JK_TRY(hipEventRecord(sb[c & 1], a));
+        JK_TRY(record(sb[c & 1], a));
         return JK_OK;
     };
     auto slice_xy = [&](int c) -> jk_status {
         JK_TRY(jk::launch_xy_rowmax_pm(PM(c), nao, nq_of(c), nkey, r, x.rows, x.mp, MX(c), x.nsp, a));
         JK_TRY(jk::launch_slice_xy(XY(c), nao, nkey, r, x.mp, nq_of(c) * r, nkb_of(c), XYp(c), xps, xkb,
                                    MX(c), x.nsp, eXY(c), a));
-        JK_TRY(hipEventRecord(sx[c & 1], a));
+        JK_TRY(record(sx[c & 1], a));
         return JK_OK;
     };
     auto half = [&](int c) -> jk_status {
-        JK_TRY(hipStreamWaitEvent(s, sb[c & 1], 0));
+        JK_TRY(wait(s, sb[c & 1]));
         if (c >= 2)
-            JK_TRY(hipStreamWaitEvent(s, sx[c & 1], 0));    // XY[c] free
+            JK_TRY(wait(s, sx[c & 1]));    // XY[c] free
         JK_TRY(jk::launch_ht_mixed(Bp(c), bps, bkb, eB(c), Cp, cps, ckb, eC, XY(c), nao, ncol, nq_of(c),
                                    cpx, x.kp / KB, PM(c), x.rows, r, s));
-        JK_TRY(hipEventRecord(ht[c & 1], s));
+        JK_TRY(record(ht[c & 1], s));
         return JK_OK;
     };
     auto exch = [&](int c) -> jk_status {
-        JK_TRY(hipStreamWaitEvent(s, sx[c & 1], 0));
+        JK_TRY(wait(s, sx[c & 1]));
         const int8_t *Xp = XYp(c), *Yp = sym ? Xp : XYp(c) + (i64)nd * x.mp * KB;
         const int *eX = eXY(c), *eY = sym ? eX : eXY(c) + (size_t)nd * x.mp;
         JK_TRY(jk::launch_ex_mixed(Xp, Yp, xps, xkb, eX, eY, Kp, nao, nd, x.mp, nkb_of(c), nsplit, c > 0, s,
                                    sym, chunks[c].scale));
-        JK_TRY(hipEventRecord(ex[c & 1], s));
+        JK_TRY(record(ex[c & 1], s));
         return JK_OK;
     };
 #define JK_STEP(expr)                                                                              \
@@ -675,28 +666,27 @@ jk_status build_mixed(const jk_problem *p, const double *B, const KSeg *seg, int
             return st_;                                                                            \
     } while (0)
 
-    // digits of [C_L | C_R]: row c, inner n, element Cc[n][c]
-    JK_TRY(jk::launch_slice_rows(Cc, 0, 1, R2, 1, R2, nao, x.cp, x.kp / KB, Cp, cps, ckb, eC, s));
-    JK_TRY(hipEventRecord(fork, s));
-    JK_TRY(hipStreamWaitEvent(a, fork, 0));
+    JK_TRY(jk::launch_slice_c(Cc, R2, nao, x.cp, x.kp / KB, Cp, cps, ckb, eC, s));
+    JK_TRY(record(fork, s));
+    JK_TRY(wait(a, fork));
     JK_STEP(slice_b(0));
     if (nchunk > 1)
         JK_STEP(slice_b(1));
     JK_STEP(half(0));
-    JK_TRY(hipStreamWaitEvent(a, ht[0], 0));
+    JK_TRY(wait(a, ht[0]));
     JK_STEP(slice_xy(0));
     for (int c = 0; c < nchunk; c++) {
         if (c + 1 < nchunk)
             JK_STEP(half(c + 1));
         JK_STEP(exch(c));
         if (c + 2 < nchunk) {
-            JK_TRY(hipStreamWaitEvent(a, ht[c & 1], 0));     // Bp[c] free
+            JK_TRY(wait(a, ht[c & 1]));     // Bp[c] free
             JK_STEP(slice_b(c + 2));
         }
         if (c + 1 < nchunk) {
-            JK_TRY(hipStreamWaitEvent(a, ht[(c + 1) & 1], 0));
+            JK_TRY(wait(a, ht[(c + 1) & 1]));
             if (c >= 1)
-                JK_TRY(hipStreamWaitEvent(a, ex[(c + 1) & 1], 0));   // XYp[c+1] free
+                JK_TRY(wait(a, ex[(c + 1) & 1]));   // XYp[c+1] free
             JK_STEP(slice_xy(c + 1));
         }
     }
@@ -934,7 +924,7 @@ BSchedule make_schedule(int32_t nprob, const jk_problem *p, const std::vector<ch
         add(jk::kPhasePack, 0,
             [&](int g) { return jk::pack_tiles((int)p[g].nao, (int)p[g].ndens, (int)p[g].rank); }, all);
         if (mixed)
-            add(jk::kPhaseMSliceC, 0, [&](int g) { return (plans[g].x.cp + 31) / 32; }, all);
+            add(jk::kPhaseMSliceC, 0, [&](int g) { return (plans[g].x.cp + 3) / 4; }, all);
         for (int c = 0; c < maxsteps; c++) {
             auto in_step = [&](int g) { return (i64)c * plans[g].f.qc < p[g].naux; };
             auto nq_of = [&](int g) {

@@ -89,10 +89,10 @@ hipError_t launch_sum_splits_sym(const double *part, double *K, int nao, int nd,
                                  hipStream_t s);
 
 // derivative (jk_vjp.hip)
-// omega in om[k][Q]
-hipError_t launch_vjp_stage_b_one(int which, const double *V, const double *Zw, const double *Cc,
-                                  const double *om, double *L, int nao, int nd, int r, int naux,
-                                  int q0, int nj, int ldw, int has_v, int has_w, hipStream_t s);
+// both of stage B's products; omega in om[k][Q]
+hipError_t launch_vjp_stage_b(const double *V, const double *Xw, const double *Yw, const double *Cc,
+                              const double *om, double *L, int nao, int nd, int r, int naux, int q0,
+                              int nj, int ldw, int has_v, int has_w, hipStream_t s);
 int vjp_stage_c_nsplit(int nao, int R, int qc);
 hipError_t launch_vjp_stage_c(const double *B, const double *L, double *dCp, int nao, int R,
                               int q0, int nq, int nsplit, int accumulate, hipStream_t s);
@@ -124,6 +124,9 @@ int mixed_k_block();
 hipError_t launch_slice_rows(const double *src, i64 bs, i64 rs, i64 ks, int nb, int nr, int nk,
                              int rp, int nkb, int8_t *out, i64 pstride, i64 kbstride, int *exps,
                              hipStream_t s);
+// digits of [C_L | C_R]: row c, inner n, element Cc[n][c]
+hipError_t launch_slice_c(const double *Cc, int R2, int nao, int cp, int nkb, int8_t *out, i64 pstride,
+                          i64 kbstride, int *exps, hipStream_t s);
 hipError_t launch_slice_b(const double *src, i64 bs, i64 rs, int nb, int nr, int nk, int rp, int nkb,
                           int8_t *out, i64 pstride, i64 kbstride, int *exps, hipStream_t s);
 // lanes of the one-pass slicer per row of kp inner bytes (0: rows too long for it)

@@ -109,9 +109,10 @@ __global__ void __launch_bounds__(256) k_slice_rows(const double *__restrict__ s
 // consecutive bytes of LPR / 8 inner blocks.  Bound by memory, 12 bytes per
 // element: 5.3 TB/s at nao 300, 4.9 at 250, 5.2 at 500 (one row per wave, in
 // 32-byte pieces: 3.8, 3.6 and 4.0).
+// ks != 1 (the factors, whose rows are columns of [C_L | C_R]): element loads.
 constexpr int kSliceNJ = 8;
-template <int LPR>
-__device__ __forceinline__ void slice_row_wave(const double *__restrict__ src, i64 bs, i64 rs,
+template <int LPR, bool UNIT = true>
+__device__ __forceinline__ void slice_row_wave(const double *__restrict__ src, i64 bs, i64 rs, i64 ks,
                                                int nr, int nk, int rp, int nkb,
                                                int8_t *__restrict__ out, i64 pstride, i64 kbstride,
                                                int *__restrict__ exps, i64 row)
@@ -131,7 +132,7 @@ __device__ __forceinline__ void slice_row_wave(const double *__restrict__ src, i
             continue;
         }
         const int k0 = 4 * LPR * j + 4 * sub;
-        if (k0 + 4 <= nk) {
+        if (UNIT && k0 + 4 <= nk) {
             const d2 lo = *(const d2 *)(s + k0), hi = *(const d2 *)(s + k0 + 2);
             v[j][0] = lo[0];
             v[j][1] = lo[1];
@@ -140,7 +141,7 @@ __device__ __forceinline__ void slice_row_wave(const double *__restrict__ src, i
         } else {
 #pragma unroll
             for (int u = 0; u < 4; u++) {
-                const double x = s[(k0 + u) < nk ? k0 + u : nk - 1];
+                const double x = s[(UNIT ? 1 : ks) * ((k0 + u) < nk ? k0 + u : nk - 1)];
                 v[j][u] = k0 + u < nk ? x : 0.0;
             }
         }
@@ -184,7 +185,19 @@ __global__ void __launch_bounds__(256) k_slice_rows_wave(const double *__restric
     const i64 row = (i64)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
     if (row >= (i64)nb * rp)        // whole rows of lanes leave together
         return;
-    slice_row_wave<LPR>(src, bs, rs, nr, nk, rp, nkb, out, pstride, kbstride, exps, row);
+    slice_row_wave<LPR>(src, bs, rs, 1, nr, nk, rp, nkb, out, pstride, kbstride, exps, row);
+}
+
+// The factors: row c, inner n, element src[n ks + c], one wave per row (few
+// rows: 8 lanes per row and two passes took 26 us for 480 columns at nao 300).
+__global__ void __launch_bounds__(256) k_slice_cols(const double *__restrict__ src, i64 ks, int nr, int nk,
+                                                    int rp, int nkb, int8_t *__restrict__ out,
+                                                    i64 pstride, i64 kbstride, int *__restrict__ exps)
+{
+    const i64 row = (i64)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row >= rp)
+        return;
+    slice_row_wave<64, false>(src, 0, 1, ks, nr, nk, rp, nkb, out, pstride, kbstride, exps, row);
 }
 // Lanes per row for rows of nkb 32-byte inner blocks; 0: longer than 2048.
 inline int slice_lanes(int nkb)
@@ -650,12 +663,12 @@ __global__ void __launch_bounds__(256) k_bm_slice_c(const BMember *__restrict__ 
 {
     int loc;
     const BMember &m = M[find_member(tab, blockIdx.x, loc)];
-    const i64 row = (i64)loc * 32 + (threadIdx.x >> 3);
-    if (row >= m.cp)                 // whole 8-lane row groups leave together
+    const i64 row = (i64)loc * 4 + (threadIdx.x >> 6);
+    if (row >= m.cp)                 // whole waves leave together
         return;
     const int R2 = 2 * m.nd * m.r;
-    slice_row8(m.Cc, 0, 1, R2, R2, m.nao, m.cp, m.kp / kSliceKB, m.Cp, m.cps, m.ckb, m.eC, row,
-               threadIdx.x & 7);
+    slice_row_wave<64, false>(m.Cc, 0, 1, R2, R2, m.nao, m.cp, m.kp / kSliceKB, m.Cp, m.cps, m.ckb, m.eC,
+                              row);
 }
 
 template <int LPR>
@@ -669,7 +682,7 @@ __global__ void __launch_bounds__(256) k_bm_slice_b(const BMember *__restrict__ 
     const i64 row = (i64)loc * (256 / LPR) + threadIdx.x / LPR;
     if (row >= (i64)nq * m.nao)      // whole rows of lanes leave together
         return;
-    slice_row_wave<LPR>(m.B + (i64)q0 * m.npos, m.npos, m.nao, m.nao, m.nao, m.nao, m.kp / kSliceKB,
+    slice_row_wave<LPR>(m.B + (i64)q0 * m.npos, m.npos, m.nao, 1, m.nao, m.nao, m.nao, m.kp / kSliceKB,
                         m.Bp, m.bps, m.bkb, m.eB, row);
 }
 
@@ -791,6 +804,18 @@ hipError_t launch_slice_b(const double *src, i64 bs, i64 rs, int nb, int nr, int
             go(k_slice_rows_wave<32>);
         else
             go(k_slice_rows_wave<64>);
+    }
+    return hipGetLastError();
+}
+hipError_t launch_slice_c(const double *Cc, int R2, int nao, int cp, int nkb, int8_t *out, i64 pstride,
+                          i64 kbstride, int *exps, hipStream_t s)
+{
+    if (slice_lanes(nkb) == 0)
+        return launch_slice_rows(Cc, 0, 1, R2, 1, R2, nao, cp, nkb, out, pstride, kbstride, exps, s);
+    {
+        ProfScope ps_("slice_rows", s);
+        hipLaunchKernelGGL(k_slice_cols, dim3(cdiv(cp, 4)), dim3(256), 0, s, Cc, R2, R2, nao, cp, nkb, out,
+                           pstride, kbstride, exps);
     }
     return hipGetLastError();
 }

@@ -56,23 +56,29 @@ hipError_t with_shape(int shape, F &&f)
 } // namespace
 
 // ------------------------------------------------------------------ stage B
-// WHICH = 0: L[ql][m][     k*r+i] = sum_n V_k[m][n] Y_ws[k][n][ql*r+i] + om * C_R
-// WHICH = 1: L[ql][m][R  + k*r+i] = sum_n V_k[n][m] X_ws[k][n][ql*r+i] + om * C_L
+// L[ql][m][    k*r+i] = sum_n V_k[m][n] Y_ws[k][n][ql*r+i] + om * C_R   (P')
+// L[ql][m][R + k*r+i] = sum_n V_k[n][m] X_ws[k][n][ql*r+i] + om * C_L   (R')
 // (om = omega_{k, q0+ql}; products skipped when has_v == 0, omega terms when
-// has_w == 0).  grid.x = nd * nmt * njt (XCD-swizzled).
-template <int WHICH, int SHAPE>
+// has_w == 0), both in one grid, so that the last workgroups of one run beside
+// the other's: grid.x = 2 * nd * nmt * njt (XCD-swizzled).  Two launches on two
+// streams did the same at large sizes; the events between the streams took 15
+// us of 100 at nao 48.
+template <int SHAPE>
 __global__ void __launch_bounds__(256, shape_wgs(SHAPE))
-    k_vjp_stage_b(const double *__restrict__ V, const double *__restrict__ Zw,
-                  const double *__restrict__ Cc, const double *__restrict__ om,
-                  double *__restrict__ L, int nao, int nd, int r, int naux, int q0, int nj, int ldw,
-                  int has_v, int has_w)
+    k_vjp_stage_b(const double *__restrict__ V, const double *__restrict__ Xw,
+                  const double *__restrict__ Yw, const double *__restrict__ Cc,
+                  const double *__restrict__ om, double *__restrict__ L, int nao, int nd, int r,
+                  int naux, int q0, int nj, int ldw, int has_v, int has_w)
 {
     typedef typename ShapeTile<SHAPE>::type TL;
     constexpr int kTM = TL::BM, kTN = TL::BN;
     extern __shared__ double lds[];
     const int R = nd * r, R2 = 2 * R;
     const int nmt = (nao + kTM - 1) / kTM, njt = (nj + kTN - 1) / kTN;
-    const int t = xcd_swizzle(blockIdx.x, nd * nmt * njt);
+    const int half = nd * nmt * njt;
+    int t = xcd_swizzle(blockIdx.x, 2 * half);
+    const int which = t >= half;                     // R'
+    t -= which ? half : 0;
     // row tiles fastest: the nmt tiles of a column block share its X/Y block,
     // read once from HBM while V_k's row panels stay in L2
     const int k = t / (nmt * njt), rem = t % (nmt * njt);
@@ -81,12 +87,12 @@ __global__ void __launch_bounds__(256, shape_wgs(SHAPE))
     acc.zero();
     if (has_v) {
         const double *Vk = V + (i64)k * nao * nao;
-        BufIC b{Zw + (i64)k * nao * ldw, ldw, nj, nao};
-        if (WHICH == 0) {
-            BufKC a{Vk, nao, nao, nao};
+        BufIC b{(which ? Xw : Yw) + (i64)k * nao * ldw, ldw, nj, nao};
+        if (which) {
+            BufIC a{Vk, nao, nao, nao};
             tile_gemm16<TL>(a, b, mb * kTM, jb * kTN, 0, nao, lds, acc);
         } else {
-            BufIC a{Vk, nao, nao, nao};
+            BufKC a{Vk, nao, nao, nao};
             tile_gemm16<TL>(a, b, mb * kTM, jb * kTN, 0, nao, lds, acc);
         }
     }
@@ -108,8 +114,8 @@ __global__ void __launch_bounds__(256, shape_wgs(SHAPE))
         col_ok[jj] = j < nj;
         const int ql = j / r, i = j - ql * r;
         const int c = k * r + i;
-        col_l[jj] = (i64)ql * nao * R2 + (WHICH == 0 ? 0 : R) + c;
-        col_cc[jj] = WHICH == 0 ? R + c : c;
+        col_l[jj] = (i64)ql * nao * R2 + (which ? R : 0) + c;
+        col_cc[jj] = which ? c : R + c;
         col_om[jj] = (has_w && col_ok[jj]) ? om[(i64)k * naux + q0 + ql] : 0.0;
     }
 #pragma unroll
@@ -416,26 +422,22 @@ __global__ void __launch_bounds__(256) k_vjp_db_affine(const double *__restrict_
 
 static inline int cdiv(i64 a, i64 b) { return (int)((a + b - 1) / b); }
 
-hipError_t launch_vjp_stage_b_one(int which, const double *V, const double *Zw, const double *Cc,
-                                  const double *om, double *L, int nao, int nd, int r, int naux,
-                                  int q0, int nj, int ldw, int has_v, int has_w, hipStream_t s)
+hipError_t launch_vjp_stage_b(const double *V, const double *Xw, const double *Yw, const double *Cc,
+                              const double *om, double *L, int nao, int nd, int r, int naux, int q0,
+                              int nj, int ldw, int has_v, int has_w, hipStream_t s)
 {
     return with_shape(vjp_shape(nao, nao, nj), [&](auto sh) -> hipError_t {
         constexpr int SHAPE = decltype(sh)::value;
         typedef typename ShapeTile<SHAPE>::type TL;
-        const dim3 grid(nd * cdiv(nao, TL::BM) * cdiv(nj, TL::BN));
         const int lds = (int)sizeof(double) * TL::LDS_DOUBLES;
-        auto go = [&](auto fn, const char *name) -> hipError_t {
-            hipError_t e = set_dynamic_lds((const void *)fn, lds);
-            if (e != hipSuccess)
-                return e;
-            ProfScope ps_(name, s);
-            hipLaunchKernelGGL(fn, grid, dim3(TL::NTHR), lds, s, V, Zw, Cc, om, L, nao, nd, r, naux, q0,
-                               nj, ldw, has_v, has_w);
-            return hipGetLastError();
-        };
-        return which ? go(k_vjp_stage_b<1, SHAPE>, "vjp_stage_b_r")
-                     : go(k_vjp_stage_b<0, SHAPE>, "vjp_stage_b_p");
+        hipError_t e = set_dynamic_lds((const void *)k_vjp_stage_b<SHAPE>, lds);
+        if (e != hipSuccess)
+            return e;
+        ProfScope ps_("vjp_stage_b", s);
+        hipLaunchKernelGGL(k_vjp_stage_b<SHAPE>, dim3(2 * nd * cdiv(nao, TL::BM) * cdiv(nj, TL::BN)),
+                           dim3(TL::NTHR), lds, s, V, Xw, Yw, Cc, om, L, nao, nd, r, naux, q0, nj, ldw,
+                           has_v, has_w);
+        return hipGetLastError();
     });
 }
 
