@@ -126,7 +126,9 @@ struct FwdPlan {
     size_t o_cc, o_s, o_part, o_g, o_x, o_y, o_kp, total;
 };
 
-FwdPlan plan_forward(const jk_problem *p, size_t budget = kChunkBudget)
+// batched: gamma's groups of columns run in one launch, each with partial sums
+// of its own.
+FwdPlan plan_forward(const jk_problem *p, size_t budget = kChunkBudget, bool batched = false)
 {
     FwdPlan f;
     const i64 nao = p->nao, nd = p->ndens, r = p->rank, R = nd * r;
@@ -139,7 +141,8 @@ FwdPlan plan_forward(const jk_problem *p, size_t budget = kChunkBudget)
     f.o_cc = c.take(sizeof(double) * nao * 2 * R);
     // gamma: the folded densities and the partial sums over blocks of positions
     f.o_s = c.take(sizeof(double) * nd * jk::pk_size((int)nao));
-    f.o_part = c.take(sizeof(double) * jk::project_part_doubles((int)nao, (int)p->naux, (int)nd));
+    f.o_part = c.take(sizeof(double) * jk::project_part_doubles((int)nao, (int)p->naux, (int)nd) *
+                      (batched ? jk::pj_groups((int)nd) : 1));
     f.o_g = c.take(sizeof(double) * nd * p->naux);
     f.o_x = c.take(sizeof(double) * nd * nao * (size_t)f.ldw);
     f.o_y = c.take(sizeof(double) * nd * nao * (size_t)f.ldw);
@@ -232,10 +235,10 @@ struct MixPlan {
 
 inline i64 pad_to(i64 x, i64 m) { return ((x + m - 1) / m) * m; }
 
-MixPlan plan_mixed(const jk_problem *p, size_t budget = kChunkBudget)
+MixPlan plan_mixed(const jk_problem *p, size_t budget = kChunkBudget, bool batched = false)
 {
     MixPlan x;
-    x.f = plan_forward(p, budget);
+    x.f = plan_forward(p, budget, batched);
     const i64 nao = p->nao, nd = p->ndens, r = p->rank, R = nd * r;
     x.ns = jk::mixed_nslice();
     x.mp = (int)pad_to(nao, jk::mixed_row_pad());
@@ -785,14 +788,14 @@ BPlan batched_plan(const jk_problem *p, bool sym_in)
     BPlan b;
     const size_t budget = batched_budget(p);
     if (p->precision == JK_MIXED) {
-        b.x = plan_mixed(p, budget);
+        b.x = plan_mixed(p, budget, true);
         b.f = b.x.f;
         b.sym = sym_in ? 1 : 0;
         b.nsplit = b.sym ? b.x.nsplit_sym : b.x.nsplit;
         b.total = b.x.total;
         return b;
     }
-    b.f = plan_forward(p, budget);
+    b.f = plan_forward(p, budget, true);
     // tiles 3 and 4 run as the 16x16x4 tile over stacked slabs when the
     // chunk's slabs stay within a buffer resource's reach; 2 runs as 0.
     // Packed slabs always take the 16x16x4 engine's per-slab tile.

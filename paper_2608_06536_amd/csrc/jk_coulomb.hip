@@ -94,32 +94,39 @@ hipError_t launch_prep(const PrepArgs &a, hipStream_t s)
 
 size_t project_part_doubles(int nao, int naux, int nd)
 {
-    return (size_t)pj_blocks(nao, naux) * naux * pj_groups(nd) * pj_width(nd);
+    return (size_t)pj_blocks(nao, naux) * naux * pj_width(nd);
 }
 
 hipError_t launch_project(const double *B, const double *S, double *part, double *g, int nao, int naux,
                           int nd, int packed, hipStream_t s, bool reduce)
 {
-    {
-        ProfScope ps_(nd > 8 ? "project16" : "project", s);
-        const PjGeom geo = pj_geom(nao, naux, nd);
-        const dim3 grid(pj_tiles(geo, naux));
-        auto go = [&](auto nk) {
-            hipLaunchKernelGGL(k_project<decltype(nk)::value>, grid, dim3(256), 0, s, B, S, part, nao,
-                               naux, nd, packed, geo);
-        };
-        width_dispatch<16>(pj_width(nd), go);
+    // one group of columns at a time, each through the same partial sums
+    for (int k0 = 0; k0 < nd; k0 += 16) {
+        const int n = nd - k0 < 16 ? nd - k0 : 16;
+        const double *Sk = S + (i64)k0 * pk_size(nao);
+        const PjGeom geo = pj_geom(nao, naux, n);
+        {
+            ProfScope ps_(nd > 8 ? "project16" : "project", s);
+            width_dispatch<16>(pj_width(n), [&](auto nk) {
+                hipLaunchKernelGGL(k_project<decltype(nk)::value>, dim3(pj_tiles(geo, naux)), dim3(256), 0, s,
+                                   B, Sk, part, nao, naux, n, packed, geo);
+            });
+        }
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+        if (!reduce)
+            continue;
+        {
+            ProfScope ps_("project_reduce", s);
+            hipLaunchKernelGGL(k_project_reduce, dim3(reduce_tiles(naux, pj_width(n))), dim3(256), 0, s, part,
+                               g + (i64)k0 * naux, naux, n, pj_width(n), geo.nbg);
+        }
+        e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !reduce)
-        return e;
-    {
-        ProfScope ps_("project_reduce", s);
-        const int ndp = pj_groups(nd) * pj_width(nd);
-        hipLaunchKernelGGL(k_project_reduce, dim3(reduce_tiles(naux, ndp)), dim3(256), 0, s, part, g, naux,
-                           nd, ndp, pj_blocks(nao, naux));
-    }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 hipError_t launch_coulomb(const double *B, const double *g, double *J, int nao, int naux, int nd,
@@ -142,11 +149,12 @@ hipError_t launch_coulomb(const double *B, const double *g, double *J, int nao, 
     return hipGetLastError();
 }
 
-// At most 8 partial sums (nao 127) and kFuseGamma numbers: larger builds keep the
-// sum in a launch of its own, where every number is summed once.
+// At most 8 partial sums (nao 127), one group of columns and kFuseGamma numbers:
+// larger builds keep the sum in a launch of its own, where every number is
+// summed once.
 bool coulomb_sums_gamma(int nao, int naux, int nd)
 {
-    return pj_blocks(nao, naux) <= 8 && (i64)naux * pj_width(nd) <= kFuseGamma && cu_runs(nao) == 1 &&
+    return nd <= 16 && pj_blocks(nao, naux) <= 8 && (i64)naux * pj_width(nd) <= kFuseGamma && cu_runs(nao) == 1 &&
            cu_slices_log2(nao) == 3;
 }
 
@@ -158,7 +166,7 @@ hipError_t launch_coulomb_sum(const double *B, const double *part, double *J, in
         const int w = pj_width(nd);
         width_dispatch<16>(w, [&](auto nk) {
             hipLaunchKernelGGL(k_coulomb_sum<decltype(nk)::value>, dim3(cu_tiles(nao, nd, w, 1)), dim3(512),
-                               0, s, B, part, J, nao, naux, nd, packed, pj_groups(nd) * w,
+                               0, s, B, part, J, nao, naux, nd, packed, w,
                                pj_blocks(nao, naux), scale, accumulate);
         });
     }

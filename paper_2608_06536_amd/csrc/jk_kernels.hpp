@@ -39,7 +39,7 @@ int pick_split_slots(int tiles, int smax, int slots);
 // squares or packed slabs.  S_k: matrices folded onto the packed positions
 // (A[m][n] + A[n][m] above the diagonal), from the factors or from given
 // matrices (nmat of them).  project: g[k][Q] = sum_p B^Q[p] S_k[p], all nd
-// matrices; part holds project_part_doubles doubles.  coulomb: J (+)= scale *
+// matrices, in groups of 16 that share part (project_part_doubles doubles).  coulomb: J (+)= scale *
 // sum_Q g B^Q in full; accumulate adds to what J holds.
 // What a build needs before it reads B; null pointers are left out.
 struct PrepArgs {
