@@ -21,6 +21,7 @@
 // Stage C reads it whole; stage D is two products, C_R R'^T then P' C_L^T,
 // with C_L and C_R read from Cc.  Cc[n][c] is [C_L | C_R] with c < 2R; om[k][Q]
 // = omega_kQ.
+#include <algorithm>
 #include <type_traits>
 
 #include "f64_core.hpp"
@@ -441,11 +442,22 @@ hipError_t launch_vjp_stage_b(const double *V, const double *Xw, const double *Y
     });
 }
 
+// Up to 64 splits of the slabs; up to 128 where 64 leave the workgroup slots less
+// than 90% full and 128 do not (nao 150: 151 -> 115 us) or 64 reach at most half
+// of the CUs (nao 80: 29 -> 22).  Elsewhere more splits only add partial sums
+// (nao 112: 61 -> 65; nao 257: 832 -> 955).
 int vjp_stage_c_nsplit(int nao, int R, int qc)
 {
     const int sh = vjp_shape(nao, nao, 2 * (i64)R);
     const int tiles = cdiv(nao, shape_bm(sh)) * cdiv(2 * (i64)R, shape_bn(sh));
-    return pick_split_slots(tiles, qc < 64 ? qc : 64, device_slots() / 2 * shape_wgs(sh));
+    const int ncu = device_slots() / 2, slots = ncu * shape_wgs(sh);
+    auto full = [&](int s) {
+        const i64 w = (i64)tiles * s, rounds = (w + slots - 1) / slots;
+        return 10 * w >= 9 * rounds * slots;
+    };
+    const int few = pick_split_slots(tiles, std::min(qc, 64), slots);
+    const int more = pick_split_slots(tiles, std::min(qc, 128), slots);
+    return (!full(few) && full(more)) || tiles * 64 <= ncu / 2 ? more : few;
 }
 
 hipError_t launch_vjp_stage_c(const double *B, const double *L, double *dCp, int nao, int R,
